@@ -331,7 +331,8 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   auto ev_after = [&](int64_t jj) -> hipEvent_t& { return w.lev[(size_t)((jj + 1) % kEv)]; };
   int32_t flags0 = 0;
   const int k0 = first_kernel(g, o, pol.has_origin, pol.has_rorigin, &flags0);
-  BfsBase b = make_base(g, w, lv, pa, timed, o->count_arcs != 0);
+  const bool canonical = o->canonical_parents && pa;  // every parent is written afterwards
+  BfsBase b = make_base(g, w, lv, canonical ? nullptr : pa, timed, o->count_arcs != 0);
   // single-workgroup multi-level launches: not with per-launch events (their
   // levels would share one launch's time), and with a tree its workgroup holds
   b.solo = !o->no_solo && !events && (o->policy != GSW_POLICY_TREE || w.tree_nodes <= kSoloTree) ? kSoloMaxLevels : 0;
@@ -382,7 +383,7 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
     nf_prev = r.nf;
   }
   w.ring_used = d + 1;
-  if (o->canonical_parents && pa) GSW_TRY(launch_canonical_parents(g, lv, pa, s));
+  if (canonical) GSW_TRY(launch_canonical_parents(g, w, lv, pa, s));
   return GSW_OK;
 }
 

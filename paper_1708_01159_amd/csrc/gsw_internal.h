@@ -357,7 +357,9 @@ int32_t level_kernel_grid(int64_t n, int64_t nw);
 // Workgroups of that launch that run a level of `kernel` with n_in frontier entries.
 int32_t level_participants(int kernel, int64_t n_in, const BfsBase& b);
 gsw_status launch_isolated(const gsw_graph* g, unsigned long long* iso, hipStream_t s);
-gsw_status launch_canonical_parents(const gsw_graph* g, const int32_t* level, int32_t* parent,
+// Writes every vertex's parent (the search itself then needs none); uses the
+// workspace's first queue, after the search.
+gsw_status launch_canonical_parents(const gsw_graph* g, const Workspace& w, const int32_t* level, int32_t* parent,
                                     hipStream_t s);
 gsw_status launch_build_origin(const int64_t* offs, int64_t n, int32_t* origin, hipStream_t s);
 // Whether the single-source workspace ranks the head (out-degree standard deviation above the mean).

@@ -1933,23 +1933,157 @@ __global__ void __launch_bounds__(kBlock) k_build_head_ranked(const int64_t* __r
   }
 }
 
-// parent[v] = the smallest u with an arc u -> v one level up (rows of the
-// in-arcs, any order).
+// Canonical parents: parent[v] = the smallest u with an arc u -> v one level
+// up (rows of the in-arcs, any order; -1 for an unreached v, v itself for the
+// source).  Every arc's column has to be read, since a row need not be
+// sorted, but a neighbour's level only where its id would lower the minimum:
+// on ascending rows that is up to the first hit, so every walk begins with
+// few arcs and shares what they found before it goes on.  (The level reads
+// are 4-byte gathers, some 150 G/s, and bound a pass that issues one per
+// arc.)  No lane or wave is left with one long row: rows of up to kCanonLane arcs are walked by their own lane, up to
+// kCanonMid by a quarter of the wave (16 lanes, four rows at a time), up to
+// kCanonLong by the wave, and a longer one by its wave only up to a multiple
+// of kCanonChunk arcs of the column array; the kCanonChunk-arc windows from
+// there on are noted in window_row for k_canonical_windows, one wave per
+// window.  R-MAT scale 20
+// (31.4 M arcs): 81 + 21 us; one lane per row took 9.1 ms.
+constexpr int64_t kCanonLane = 16;
+constexpr int kCanonGroup = 16;
+constexpr int64_t kCanonMid = 128;
+constexpr int64_t kCanonLong = 1024;
+constexpr int64_t kCanonChunk = 1024;
+constexpr int64_t kCanonFirst = 256;  // arcs of a long row that its own wave walks at least
+constexpr int32_t kCanonNone = 0x7fffffff;
+
+// First window of long row [beg, end) that a wave of its own walks.
+__device__ __forceinline__ int64_t canon_first_window(int64_t beg) {
+  return (beg + kCanonFirst + kCanonChunk - 1) / kCanonChunk;
+}
+
+template <int kLanes>
+__device__ __forceinline__ int32_t canon_min(int32_t best) {
+#pragma unroll
+  for (int off = kLanes / 2; off > 0; off >>= 1) best = min(best, __shfl_xor(best, off));
+  return best;
+}
+
+// The smaller of best and the smallest u on arcs e0, e0 + step, ... below
+// end with level[u] == up; kB arcs in flight per lane.
+template <int kB>
+__device__ __forceinline__ int32_t canon_walk(const int32_t* __restrict__ cols, const int32_t* __restrict__ level,
+                                              int64_t e0, int64_t end, int step, int32_t up, int32_t best) {
+  for (int64_t e = e0; e < end; e += (int64_t)kB * step) {
+    int32_t u[kB], l[kB];
+#pragma unroll
+    for (int q = 0; q < kB; ++q) u[q] = e + (int64_t)q * step < end ? cols[e + (int64_t)q * step] : kCanonNone;
+#pragma unroll
+    for (int q = 0; q < kB; ++q) l[q] = u[q] < best ? level[u[q]] : -1;
+#pragma unroll
+    for (int q = 0; q < kB; ++q)
+      if (l[q] == up && u[q] < best) best = u[q];
+  }
+  return best;
+}
+
 __global__ void __launch_bounds__(kBlock) k_canonical_parents(const int64_t* __restrict__ offs,
                                                               const int32_t* __restrict__ cols,
                                                               const int32_t* __restrict__ level,
-                                                              int32_t* __restrict__ parent,
-                                                              int64_t n) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int32_t lv = level[v];
-  if (lv <= 0) return;
-  int32_t best = 0x7fffffff;
-  for (int64_t e = offs[v]; e < offs[v + 1]; ++e) {
-    const int32_t u = cols[e];
-    if (u < best && level[u] == lv - 1) best = u;
+                                                              int32_t* __restrict__ parent, int64_t n,
+                                                              int32_t* __restrict__ window_row, int64_t windows) {
+  const int lane = lane_id();
+  const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+  for (int64_t w = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6; w * 64 < n; w += nwaves) {
+    const int64_t v = w * 64 + lane;
+    const int32_t lv = v < n ? level[v] : 0;
+    int64_t beg = 0, end = 0;
+    if (lv > 0) {
+      beg = offs[v];
+      end = offs[v + 1];
+    }
+    const int64_t deg = end - beg;
+    if (v < n && lv <= 0) parent[v] = lv < 0 ? -1 : (int32_t)v;
+    if (lv > 0 && deg <= kCanonLane) parent[v] = canon_walk<4>(cols, level, beg, end, 1, lv - 1, kCanonNone);
+    // 16 lanes per row, the wave's next four such rows at a time
+    u64 mid = __ballot(deg > kCanonLane && deg <= kCanonMid);
+    while (mid != 0ull) {
+      const int g = lane / kCanonGroup;
+      const int owner = g < __popcll(mid) ? nth_set_bit(mid, g) : -1;
+      const int src = owner < 0 ? 0 : owner;
+      const int64_t rb = __shfl((long long)beg, src);
+      const int64_t re = __shfl((long long)end, src);
+      const int32_t up = __shfl(lv, src) - 1;
+      int32_t best = kCanonNone;
+      const int64_t r0 = rb + lane % kCanonGroup;
+      if (owner >= 0) best = canon_walk<1>(cols, level, r0, re < rb + kCanonGroup ? re : rb + kCanonGroup,
+                                           kCanonGroup, up, best);
+      best = canon_min<kCanonGroup>(best);
+      if (owner >= 0) best = canon_walk<4>(cols, level, r0 + kCanonGroup, re, kCanonGroup, up, best);
+      best = canon_min<kCanonGroup>(best);
+      if (owner >= 0 && lane % kCanonGroup == 0) parent[w * 64 + owner] = best;
+#pragma unroll
+      for (int k = 0; k < 64 / kCanonGroup; ++k) mid &= mid - 1ull;
+    }
+    u64 longs = __ballot(deg > kCanonMid);
+    while (longs != 0ull) {
+      const int owner = __ffsll((long long)longs) - 1;
+      longs &= longs - 1ull;
+      const int64_t rb = __shfl((long long)beg, owner);
+      const int64_t re = __shfl((long long)end, owner);
+      const int32_t up = __shfl(lv, owner) - 1;
+      int64_t w1 = (re + kCanonChunk - 1) / kCanonChunk;  // windows w0 .. w1 - 1 begin inside the row
+      const int64_t w0 = re - rb > kCanonLong ? canon_first_window(rb) : w1;
+      if (w1 > windows) w1 = windows;
+      for (int64_t c = w0 + lane; c < w1; c += 64) window_row[c] = (int32_t)(w * 64 + owner);
+      const int64_t own = w0 * kCanonChunk < re ? w0 * kCanonChunk : re;
+      int32_t best = canon_min<64>(canon_walk<1>(cols, level, rb + lane, rb + 64, 64, up, kCanonNone));
+      best = canon_walk<8>(cols, level, rb + 64 + lane, own, 64, up, best);
+      if (w1 * kCanonChunk < re)  // windows that the array has no room for
+        best = canon_walk<8>(cols, level, (w1 > w0 ? w1 : w0) * kCanonChunk + lane, re, 64, up, best);
+      best = canon_min<64>(best);
+      if (lane == 0) parent[w * 64 + owner] = best;  // an upper bound for its windows
+    }
   }
-  parent[v] = best;
+}
+
+// The windows of long rows, a wave each, joined by atomicMin.  A lane reads
+// the noted row of one of the wave's windows and checks it against the row's
+// bounds: a word that k_canonical_parents did not write names no row that
+// holds the window, so the array needs no clearing.
+__global__ void __launch_bounds__(kBlock) k_canonical_windows(const int64_t* __restrict__ offs,
+                                                              const int32_t* __restrict__ cols,
+                                                              const int32_t* __restrict__ level, int32_t* parent,
+                                                              int64_t n, const int32_t* __restrict__ window_row,
+                                                              int64_t windows) {
+  const int lane = lane_id();
+  const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+  const int64_t first = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+  for (int64_t w0 = first; w0 < windows; w0 += 64 * nwaves) {
+    const int64_t w = w0 + lane * nwaves;
+    int32_t v = w < windows ? window_row[w] : -1;
+    int64_t end = 0;
+    int32_t up = 0;
+    if (v >= 0 && v < n) {
+      const int64_t beg = offs[v];
+      end = offs[v + 1];
+      up = level[v] - 1;
+      if (end - beg <= kCanonLong || w < canon_first_window(beg) || w * kCanonChunk >= end || up < 0) v = -1;
+    } else {
+      v = -1;
+    }
+    u64 mine = __ballot(v >= 0);
+    while (mine != 0ull) {
+      const int k = __ffsll((long long)mine) - 1;
+      mine &= mine - 1ull;
+      const int32_t row = __shfl(v, k);
+      const int64_t rb = (w0 + k * nwaves) * kCanonChunk;
+      const int64_t re = __shfl((long long)end, k);
+      const int32_t had = parent[row];
+      int32_t best = canon_walk<8>(cols, level, rb + lane, rb + kCanonChunk < re ? rb + kCanonChunk : re, 64,
+                                   __shfl(up, k), had);
+      best = canon_min<64>(best);
+      if (lane == 0 && best < had) atomicMin(parent + row, best);
+    }
+  }
 }
 
 __global__ void __launch_bounds__(kBlock) k_build_origin(const int64_t* __restrict__ offs,
@@ -2027,11 +2161,20 @@ gsw_status launch_isolated(const gsw_graph* g, unsigned long long* iso, hipStrea
   return GSW_OK;
 }
 
-gsw_status launch_canonical_parents(const gsw_graph* g, const int32_t* level, int32_t* parent,
+gsw_status launch_canonical_parents(const gsw_graph* g, const Workspace& w, const int32_t* level, int32_t* parent,
                                     hipStream_t s) {
-  hipLaunchKernelGGL(k_canonical_parents, dim3((unsigned)cdiv(g->n, kBlock)), dim3(kBlock), 0, s,
-                     g->roffs, g->rcols, level, parent, g->n);
+  // the search is over: its first queue holds the windows' rows
+  int32_t* window_row = w.q[0];
+  const int64_t cap = g->n * kQueueBins;
+  const int64_t windows = cdiv(g->nnz, kCanonChunk) < cap ? cdiv(g->nnz, kCanonChunk) : cap;
+  hipLaunchKernelGGL(k_canonical_parents, dim3((unsigned)cdiv(g->n, kBlock)), dim3(kBlock), 0, s, g->roffs, g->rcols,
+                     level, parent, g->n, window_row, windows);
   GSW_HIP(hipGetLastError());
+  if (g->gfeat[12] > (double)kCanonLong) {  // the largest in-degree: some row may be long
+    hipLaunchKernelGGL(k_canonical_windows, dim3(persistent_grid(cdiv(windows, kWaves))), dim3(kBlock), 0, s,
+                       g->roffs, g->rcols, level, parent, g->n, (const int32_t*)window_row, windows);
+    GSW_HIP(hipGetLastError());
+  }
   return GSW_OK;
 }
 

@@ -197,7 +197,8 @@ gsw_status run_source(gsw_graph* g, const Workspace& w, const gsw_bfs_opts* o, c
   GSW_HIP(hipMemsetAsync(w.d_ring, 0, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long), s));
   int32_t flags0 = 0;
   const int k0 = first_kernel(g, o, has_origin, has_rorigin, &flags0);
-  const BfsBase b = make_base(g, w, lv, pa, timed, o->count_arcs != 0);  // solo launches off
+  const bool canonical = o->canonical_parents && pa;  // every parent is written afterwards
+  const BfsBase b = make_base(g, w, lv, canonical ? nullptr : pa, timed, o->count_arcs != 0);  // solo launches off
   GSW_TRY(launch_init(g, b, iso, src, k0, flags0, s));
   const int32_t cap = o->max_workgroups > 0 && o->max_workgroups < b.grid_max ? o->max_workgroups : b.grid_max;
   int32_t j = 0;
@@ -217,7 +218,7 @@ gsw_status run_source(gsw_graph* g, const Workspace& w, const gsw_bfs_opts* o, c
     if (ended) break;
     if (d == d0) return fail(GSW_EHIP, "level %lld posted no record in %d launches", (long long)d, kBatch);
   }
-  if (o->canonical_parents && pa) GSW_TRY(launch_canonical_parents(g, lv, pa, s));
+  if (canonical) GSW_TRY(launch_canonical_parents(g, w, lv, pa, s));
   return GSW_OK;
 }
 
