@@ -28,9 +28,13 @@
 // (L2) before loading a neighbour's mask.  Rows are walked by the vertex's
 // group up to kMsLong arcs, by the whole wave up to kMsHeavy arcs, and
 // beyond that in kMsChunk-arc chunks spread over the grid (top-down; a
-// bottom-up walk stops early and stays with one wave).  Levels are kept
-// vertex-major ([n][B] bytes, each lane updating its own 64-byte run word by
-// word) and transposed to [B][n] at the end.
+// bottom-up walk stops early and stays with one wave).  A batch keeps its
+// levels as bit planes in the masks' layout: a vertex found at level L has
+// its source's bit set in the planes of L's binary digits, so a level writes
+// one word per set digit and lane (about 1.4 lines of 128 bytes per vertex
+// for 1024 sources, where 8-byte updates of a vertex-major byte row touched
+// 1 KiB), only the planes in use are ever cleared, and the [B][n] bytes are
+// written once, from the planes, at the end.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -53,6 +57,9 @@ constexpr int kMsStatStride = 32;  // u64 words between counters
 constexpr int kMsLong = 32;        // rows longer than this are walked by the whole wave
 constexpr int kMsHeavy = 1024;     // top-down: rows longer than this go through the chunk list
 constexpr int kMsChunk = 256;      // arcs per chunk of a heavy row
+constexpr int kMsPlanes = 7;       // digits of the largest int8 level
+constexpr int kMsPlanesInit = 3;   // planes the init kernel clears: levels up to 7
+static_assert((1 << kMsPlanes) - 1 == GSW_MSBFS_LEVEL_CAP, "the planes hold every int8 level");
 constexpr int kMaxWords = GSW_MSBFS_MAX_SOURCES / 64;  // mask words per vertex at most
 constexpr int kMaxSlots = GSW_MSBFS_MAX_SOURCES;
 
@@ -87,14 +94,14 @@ struct MsArgs {
   const int32_t* __restrict__ cols;
   u64* vis;
   const u64* __restrict__ fr;   // depth-d masks
-  u64* frn;                     // depth-(d+1) masks; holds depth d-1's until rewritten
+  u64* frn;                     // depth-(d+1) masks (a row holds them where its fbm_n bit is set)
   u64* nx;                      // top-down accumulator, zero between levels
   const u64* __restrict__ fbm;  // bit v: v is in some source's depth-d frontier
   u64* fbm_n;                   // the same for depth d+1 (holds depth d-1's until rewritten)
   u64* tbm;                     // bit v: the top-down pass touched nx[v] (zero between levels)
   const u64* __restrict__ heavy;  // chunk list of rows longer than kMsHeavy
   int64_t n_heavy;
-  int8_t* lev;                  // [n][B] levels, vertex-major
+  u64* plane;                   // [kMsPlanes][n][W] binary digits of the levels (null for a session)
   u64* stats;                   // [kMsStats] rows: vertices with new bits, their degree sum
   u64* slot_ef;                 // [kMsStats][kMaxSlots]: per source, degree sum of its new frontier
   u64* active;                  // [kMsStats][kMaxWords]: OR of the new frontier masks
@@ -105,7 +112,7 @@ struct MsArgs {
   const long long* start;
   MsCtl* ctl;
   int64_t n;
-  int32_t W, B;  // words per vertex, level bytes per vertex
+  int32_t W;  // words per vertex
 };
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
@@ -118,16 +125,9 @@ __device__ __forceinline__ u64 valid_bits(int j, int W, int B) {
 }
 
 
-// 8 bits -> 8 bytes holding 0x01 where the bit is set.
-__device__ __forceinline__ u64 bits_to_bytes(u64 c) {
-  c = (c | (c << 28)) & 0x0000000F0000000Full;
-  c = (c | (c << 14)) & 0x0003000300030003ull;
-  c = (c | (c << 7)) & 0x0101010101010101ull;
-  return c;
-}
-
-// Levels d+1 for the sources in `m` (word j) at vertex v.  Only v's group
-// writes v's levels, so the batch's 8-byte read-modify-writes need no atomics.
+// Level d+1 for the sources in `m` (word j) at vertex v.  Only v's group
+// writes v's words, so the planes need no atomics.  Past the cap nothing is
+// written: such sources are rerun or the call fails.
 __device__ __forceinline__ void write_levels(const MsArgs& a, long long d, int64_t v, int j, u64 m) {
   if (a.dist) {
     while (m) {
@@ -138,14 +138,10 @@ __device__ __forceinline__ void write_levels(const MsArgs& a, long long d, int64
     }
     return;
   }
-  u64* row = reinterpret_cast<u64*>(a.lev + v * (int64_t)a.B + (int64_t)j * 64);
-  const u64 val = (u64)(uint8_t)(d + 1 > 127 ? 127 : d + 1) * 0x0101010101010101ull;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const u64 c = (m >> (8 * k)) & 0xffull;
-    if (!c) continue;
-    const u64 bm = bits_to_bytes(c) * 0xffull;
-    row[k] = (row[k] & ~bm) | (val & bm);
+  if (d + 1 > GSW_MSBFS_LEVEL_CAP) return;
+  for (int dig = (int)(d + 1); dig != 0; dig &= dig - 1) {
+    const int p = __ffs(dig) - 1;
+    a.plane[((int64_t)p * a.n + v) * a.W + j] |= m;
   }
 }
 
@@ -209,40 +205,40 @@ __device__ __forceinline__ Wave wave_of(int G) {
 }
 
 // ------------------------------------------------------------------ init
-// Masks of n vertices (bits of sources >= nsrc start visited), the bitmaps
-// and levels [n][brow] set to -1 (brow = 64 W, so rows are whole 8-byte
-// words).  Both frontier mask buffers start at zero: later levels rewrite a
-// vertex's next-frontier masks only where they are or were nonzero.
-__global__ void __launch_bounds__(kMsBlock) k_ms_init(u64* vis, u64* fr, u64* frn, u64* nx, u64* bms,
-                                                      int8_t* lev, int64_t n, int W, int nsrc, int brow) {
+// Visited masks (bits of sources >= nsrc start visited), accumulators, the
+// first kMsPlanesInit level planes and the bitmaps.  The frontier masks are
+// not cleared: a vertex's row is read only where its frontier bit is set, and
+// was then written whole.
+__global__ void __launch_bounds__(kMsBlock) k_ms_init(u64* vis, u64* nx, u64* plane, u64* bms, int64_t n, int W,
+                                                      int nsrc) {
   const int64_t stride = (int64_t)gridDim.x * kMsBlock;
   const int64_t gid = (int64_t)blockIdx.x * kMsBlock + threadIdx.x;
   const int64_t words = n * W;
   for (int64_t i = gid; i < words; i += stride) {
-    const int j = (int)(i % W);
-    vis[i] = ~valid_bits(j, W, nsrc);
-    fr[i] = 0ull;
-    frn[i] = 0ull;
+    vis[i] = (nsrc & 63) ? ~valid_bits((int)(i % W), W, nsrc) : 0ull;
     nx[i] = 0ull;
+#pragma unroll
+    for (int p = 0; p < kMsPlanesInit; ++p) plane[(int64_t)p * words + i] = 0ull;
   }
   const int64_t nb = 3 * ((n + 63) / 64);
   for (int64_t i = gid; i < nb; i += stride) bms[i] = 0ull;
-  const int64_t lw = n * (int64_t)brow / 8;
-  u64* l8 = reinterpret_cast<u64*>(lev);
-  for (int64_t i = gid; i < lw; i += stride) l8[i] = ~0ull;
 }
 
-// Sources are set after init (a separate launch, so no ordering issue).
-__global__ void k_ms_sources(u64* vis, u64* fr, u64* fbm, int8_t* lev, int W, int B,
-                             const int32_t* __restrict__ src, int nsrc) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nsrc) return;
-  const int64_t s = src[i];
-  const u64 bit = 1ull << (i & 63);
-  atomicOr(vis + s * W + (i >> 6), bit);
-  atomicOr(fr + s * W + (i >> 6), bit);
-  atomicOr(fbm + (s >> 6), 1ull << (s & 63));
-  lev[s * (int64_t)B + i] = 0;
+// Sources are set after init, by one workgroup: their frontier rows are
+// cleared whole, then their bits are set (several sources may share a
+// vertex).  A source's level 0 has no digit.
+constexpr int kMsSeedBlock = 1024;
+__global__ void __launch_bounds__(kMsSeedBlock) k_ms_sources(u64* vis, u64* fr, u64* fbm, int W,
+                                                             const int32_t* __restrict__ src, int nsrc) {
+  for (int i = threadIdx.x; i < nsrc * W; i += kMsSeedBlock) fr[(int64_t)src[i / W] * W + i % W] = 0ull;
+  __syncthreads();
+  for (int i = threadIdx.x; i < nsrc; i += kMsSeedBlock) {
+    const int64_t s = src[i];
+    const u64 bit = 1ull << (i & 63);
+    atomicOr(vis + s * W + (i >> 6), bit);
+    atomicOr(fr + s * W + (i >> 6), bit);
+    atomicOr(fbm + (s >> 6), 1ull << (s & 63));
+  }
 }
 
 // Chunk list of the rows longer than kMsHeavy: entry (v << 32 | c) stands
@@ -298,10 +294,24 @@ __device__ __forceinline__ void push_arcs(const MsArgs& a, u64 f, int j, int64_t
   }
 }
 
+// A level d + 1 = 2^p beyond the planes that the init kernel cleared is the
+// first to use plane p, which is cleared here, before the level's update.
+__device__ __forceinline__ void clear_plane(const MsArgs& a, long long d) {
+  const long long lv = d + 1;
+  if (!a.plane || lv < (1 << kMsPlanesInit) || lv > GSW_MSBFS_LEVEL_CAP || (lv & (lv - 1)) != 0) return;
+  const int64_t words = a.n * a.W;
+  u64* p = a.plane + (int64_t)(__ffsll(lv) - 1) * words;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x)
+    p[i] = 0ull;
+}
+
 // Every frontier vertex u of a top-down source: lane j pushes
 // fr[u][j] & pmask[j] along u's arcs.
 __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a, int G) {
-  if (!a.ctl->any_push) return;
+  const bool any_push = a.ctl->any_push != 0;
+  if (!any_push && !a.ctl->any_pull) return;
+  clear_plane(a, a.ctl->d);
+  if (!any_push) return;
   const Wave w = wave_of(G);
   const int j = w.j;
   const u64 pm = j < a.W ? a.ctl->pmask[j] : 0ull;
@@ -352,8 +362,7 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a, int G) {
 
 // ------------------------------------------------------ bottom-up + update
 // Each 64-vertex word: the vertices with possible work are all of them when
-// some source pulls, else those the top-down pass touched or whose stale
-// next-frontier masks must be cleared.  For such a vertex v: the bottom-up
+// some source pulls, else those the top-down pass touched.  For such a vertex v: the bottom-up
 // sources it still needs (~vis & qmask) are looked up in the neighbours'
 // frontier masks (frontier bit first), stopping once all are covered; what
 // the top-down pass left in nx (minus vis) joins them.  v's group is the only
@@ -379,9 +388,8 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
   for (int64_t wd = w.wave; wd < nwords; wd += w.nwaves) {
     const int64_t base = wd * 64;
     const u64 valid = base + 64 <= a.n ? ~0ull : ((1ull << (a.n - base)) - 1ull);
-    const u64 stale = a.fbm_n[wd];
     const u64 touched = any_push ? a.tbm[wd] : 0ull;
-    const u64 work = (any_pull ? ~0ull : (touched | stale)) & valid;
+    const u64 work = (any_pull ? ~0ull : touched) & valid;
     u64 nbits = 0ull;
     const int cnt = __popcll(work);
     for (int r0 = 0; r0 < cnt; r0 += w.gpw) {
@@ -447,7 +455,7 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
             atomicAdd(&s_ef[j * 64 + bt], deg);
           }
         }
-        if (nb || ((stale >> bit) & 1ull)) a.frn[i] = nb;
+        if (grp_new) a.frn[i] = nb;  // the row whole: its frontier bit is set below
         act |= nb;
       }
       if (grp_new && j == 0) {
@@ -562,43 +570,116 @@ __global__ void __launch_bounds__(256) k_ms_finalize(MsCtl* ctl, u64* stats, u64
   if (t == 0) __hip_atomic_store(rec, (u64)d + 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// [n][B] -> [nsrc][n] levels through 64x64-byte LDS tiles.
-// A 128-vertex x 128-source tile moved as 4-byte words, so both the reads
-// (128 source bytes of a vertex) and the writes (128 vertex bytes of a
-// source) cover whole 128-byte lines.  B is a multiple of 64, so every input
-// word is whole and aligned; with B = 64 the upper half of the tile is empty.
-constexpr int kTr = 128;
-__global__ void __launch_bounds__(256) k_ms_transpose(const int8_t* __restrict__ in,
-                                                      int8_t* __restrict__ out, int64_t n, int B,
-                                                      int nsrc) {
-  constexpr int kW = kTr / 4;  // words per tile row
-  __shared__ uint32_t tile[kTr][kW + 1];  // [vertex][word of 4 sources], padded
-  const int64_t v0 = (int64_t)blockIdx.x * kTr;
-  const int s0 = blockIdx.y * kTr;
-  for (int i = threadIdx.x; i < kTr * kW; i += 256) {
-    const int r = i / kW, wd = i % kW;
-    const int64_t v = v0 + r;
-    const int s = s0 + 4 * wd;
-    tile[r][wd] = v < n && s < B ? *reinterpret_cast<const uint32_t*>(in + v * B + s) : 0xffffffffu;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < kTr * kW; i += 256) {
-    const int sr = i / kW, wd = i % kW;  // source s0 + sr, vertices v0 + 4 wd .. + 3
-    const int s = s0 + sr;
-    if (s >= nsrc) continue;
-    const int sh = 8 * (sr & 3);
-    uint32_t x = 0u;
+// Level planes -> [nsrc][n] bytes.  A thread takes four consecutive vertices
+// and half a mask word, that is 4 x 32 levels, which it gathers in registers
+// plane by plane (a digit's four bits spread to four bytes by a 24-bit
+// multiply) and turns with byte permutes into dwords of four vertices of one
+// source, stored along the source's row.  The planes come through LDS so that
+// whole 128-byte lines are read, the next one's words on their way while one
+// is spread; a workgroup's tile has at least 128 vertices (1024 threads at
+// G = 16), so that it writes whole lines too.  R-MAT scale 20, 1024 sources:
+// 308 us for 1.6 GB, which is what a plain copy of those bytes takes; whole
+// words per thread (149 VGPRs) without the prefetch 643 us, 64-vertex tiles
+// 477 us, and the 128 x 128 byte transpose that this replaces 549 us.
+__device__ __forceinline__ uint32_t nibble(uint32_t w, int q) { return (w >> (4 * q)) & 15u; }
+// bits 0..3 of x -> bit 0 of bytes 0..3, shifted left by less than three (the
+// product's partial sums do not overlap, and its factors fit 24 bits)
+__device__ __forceinline__ uint32_t spread4(uint32_t x, uint32_t factor) { return __umul24(x, factor); }
+
+constexpr int out_block(int G) { return G >= 16 ? 1024 : 512; }
+constexpr int out_tile(int G) { return 2 * out_block(G) / G; }  // vertices
+template <int G>
+__global__ void __launch_bounds__(out_block(G)) k_ms_levels_out(const u64* __restrict__ plane,
+                                                             const u64* __restrict__ vis, int8_t* __restrict__ out,
+                                                             int64_t n, int W, int planes, int nsrc) {
+  constexpr int T = out_tile(G), Q = T / 4;
+  constexpr int pitch = G | 1;
+  __shared__ u64 tile[2][T * pitch];
+  const int64_t v0 = (int64_t)blockIdx.x * T;
+  const int vg = threadIdx.x % Q, j = threadIdx.x / Q % G, half = threadIdx.x / Q / G;
+  uint32_t acc[4][8];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x |= ((tile[4 * wd + k][sr >> 2] >> sh) & 0xffu) << (8 * k);
-    const int64_t v = v0 + 4 * wd;
-    int8_t* dst = out + (int64_t)s * n + v;
-    if (v + 3 < n && (reinterpret_cast<uintptr_t>(dst) & 3u) == 0u) {
-      *reinterpret_cast<uint32_t*>(dst) = x;
-    } else {
+  for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (v + k < n) dst[k] = (int8_t)((x >> (8 * k)) & 0xffu);
+    for (int q = 0; q < 8; ++q) acc[k][q] = 0u;
+  const int have = (int)(n - v0 < T ? n - v0 : T);
+  // this thread's word and two vertices of the tile's loads
+  const int lj = threadIdx.x % G, lv = threadIdx.x / G;
+  auto fetch = [&](int p, u64 (&w)[2]) {  // the last plane is the visited mask
+    const u64* src = (p < planes ? plane + (int64_t)p * n * W : vis) + v0 * W;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int v = lv + i * (T / 2);
+      w[i] = lj < W && v < have ? src[v * W + lj] : 0ull;
     }
+  };
+  u64 w[2];
+  fetch(0, w);
+  for (int p = 0; p <= planes; ++p) {
+    u64* t = tile[p & 1];
+    if (lj < W)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int v = lv + i * (T / 2);
+        t[((v & 3) * Q + (v >> 2)) * pitch + lj] = w[i];
+      }
+    if (p < planes) fetch(p + 1, w);
+    __syncthreads();  // (the other buffer's readers are past the last barrier)
+    if (j < W) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t h = (uint32_t)(t[(k * Q + vg) * pitch + j] >> (32 * half));
+        if (p == planes) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {  // 0xff where not visited
+            const uint32_t x = spread4(nibble(~h, q), 0x204081u) & 0x01010101u;
+            acc[k][q] |= (x << 8) - x;
+          }
+        } else if (p < 3) {
+          const uint32_t f = 0x204081u << p, m = 0x01010101u << p;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc[k][q] |= spread4(nibble(h, q), f) & m;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc[k][q] |= (spread4(nibble(h, q), 0x204081u) & 0x01010101u) << p;
+        }
+      }
+    }
+  }
+  const int64_t v = v0 + 4 * vg;
+  const int s0 = 64 * j + 32 * half;
+  if (s0 >= nsrc || v >= n) return;
+  const int rows = nsrc - s0 < 32 ? nsrc - s0 : 32;  // rows of this thread's sources, at least 1
+  int8_t* dst = out + (int64_t)s0 * n + v;
+  if (v + 3 >= n) {  // the last vertices, byte by byte
+    for (int64_t k = 0; v + k < n; ++k) {
+      const int64_t at = (v + k) * W + j;
+      const uint32_t seen = (uint32_t)(vis[at] >> (32 * half));
+      uint32_t dig[kMsPlanes];
+#pragma unroll
+      for (int p = 0; p < kMsPlanes; ++p)
+        dig[p] = p < planes ? (uint32_t)(plane[(int64_t)p * n * W + at] >> (32 * half)) : 0u;
+      for (int r = 0; r < rows; ++r) {
+        int lev = 0;
+#pragma unroll
+        for (int p = 0; p < kMsPlanes; ++p) lev |= (int)((dig[p] >> r) & 1u) << p;
+        dst[(int64_t)r * n + k] = (int8_t)((seen >> r) & 1u ? lev : -1);
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    // 4 x 4 bytes: vertices k, sources r -> dword of source r
+    const uint32_t ab0 = __builtin_amdgcn_perm(acc[1][q], acc[0][q], 0x05010400u);
+    const uint32_t ab1 = __builtin_amdgcn_perm(acc[1][q], acc[0][q], 0x07030602u);
+    const uint32_t cd0 = __builtin_amdgcn_perm(acc[3][q], acc[2][q], 0x05010400u);
+    const uint32_t cd1 = __builtin_amdgcn_perm(acc[3][q], acc[2][q], 0x07030602u);
+    const uint32_t x[4] = {__builtin_amdgcn_perm(cd0, ab0, 0x05040100u), __builtin_amdgcn_perm(cd0, ab0, 0x07060302u),
+                           __builtin_amdgcn_perm(cd1, ab1, 0x05040100u), __builtin_amdgcn_perm(cd1, ab1, 0x07060302u)};
+#pragma unroll
+    for (int r = 0; r < 4; ++r, dst += n)
+      if (4 * q + r < rows) __builtin_memcpy(dst, &x[r], 4);
   }
 }
 
@@ -615,24 +696,32 @@ __global__ void __launch_bounds__(kMsBlock) k_ss_masks(u64* vis, int64_t n, int 
   }
 }
 
-// Admitted slots: the source's bit in vis, in the current frontier and its
-// bitmap, level 0 (stored as 1), and the slot joins the next level top-down.
-__global__ void k_ss_seed(u64* vis, u64* fr, u64* fbm, int32_t* dist, MsCtl* ctl, int64_t n, int W,
-                          const int32_t* __restrict__ src, const int32_t* __restrict__ slot, int count) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const int64_t s = src[i];
-  const int k = slot[i];
-  const u64 bit = 1ull << (k & 63);
-  atomicOr(vis + s * W + (k >> 6), bit);
-  atomicOr(fr + s * W + (k >> 6), bit);
-  atomicOr(fbm + (s >> 6), 1ull << (s & 63));
-  dist[(int64_t)k * n + s] = 1;
-  ctl->pull[k] = 0;
-  ctl->explored[k] = 0ull;
-  atomicOr(&ctl->pmask[k >> 6], bit);
-  atomicAnd(&ctl->qmask[k >> 6], ~bit);
-  ctl->any_push = 1;
+// Admitted slots, by one workgroup: a source that is in no slot's frontier has
+// its frontier row cleared whole; then the source's bit in vis, in the current
+// frontier and its bitmap, level 0 (stored as 1), and the slot joins the next
+// level top-down.
+__global__ void __launch_bounds__(kMsSeedBlock) k_ss_seed(u64* vis, u64* fr, u64* fbm, int32_t* dist, MsCtl* ctl,
+                                                          int64_t n, int W, const int32_t* __restrict__ src,
+                                                          const int32_t* __restrict__ slot, int count) {
+  for (int i = threadIdx.x; i < count * W; i += kMsSeedBlock) {
+    const int64_t s = src[i / W];
+    if (!((fbm[s >> 6] >> (s & 63)) & 1ull)) fr[s * W + i % W] = 0ull;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < count; i += kMsSeedBlock) {
+    const int64_t s = src[i];
+    const int k = slot[i];
+    const u64 bit = 1ull << (k & 63);
+    atomicOr(vis + s * W + (k >> 6), bit);
+    atomicOr(fr + s * W + (k >> 6), bit);
+    atomicOr(fbm + (s >> 6), 1ull << (s & 63));
+    dist[(int64_t)k * n + s] = 1;
+    ctl->pull[k] = 0;
+    ctl->explored[k] = 0ull;
+    atomicOr(&ctl->pmask[k >> 6], bit);
+    atomicAnd(&ctl->qmask[k >> 6], ~bit);
+    ctl->any_push = 1;
+  }
 }
 
 // Sets a session's level counter (in stream order with its levels).
@@ -820,8 +909,8 @@ gsw_status launch_ms_level(MsArgs a, const LevelStats& st, int G, int bs, hipStr
                         a.stats, a.active, a.slot_ef, a.ctl, st.d_ring};
   for (const void* p : need)
     if (!p) return fail(GSW_EINVAL, "batched level launched with a missing buffer");
-  if ((!a.dist && !a.lev) || (a.dist && !a.start) || (a.n_heavy > 0 && !a.heavy) || a.W < 1 ||
-      a.W > kMaxWords || a.B != 64 * a.W || G < a.W || G > 16 || (G & (G - 1)) != 0 ||
+  if ((!a.dist && !a.plane) || (a.dist && !a.start) || (a.n_heavy > 0 && !a.heavy) || a.W < 1 ||
+      a.W > kMaxWords || G < a.W || G > 16 || (G & (G - 1)) != 0 ||
       (bs != 128 && bs != 256 && bs != 512))
     return fail(GSW_EINVAL, "batched level launched with inconsistent arguments");
   const unsigned grid = ms_grid(a.n, bs);
@@ -836,11 +925,11 @@ gsw_status launch_ms_level(MsArgs a, const LevelStats& st, int G, int bs, hipStr
 
 struct MsWorkspace {
   int64_t n = 0;
-  int W = 0, B = 0;
+  int W = 0;
   int bs = 0;  // block size the captured graph was made with
   u64 *vis = nullptr, *fr = nullptr, *frn = nullptr, *nx = nullptr;
   u64* bms = nullptr;  // 3 bitmaps of ceil(n/64) words: frontier (two) and touched
-  int8_t* lev = nullptr;
+  u64* plane = nullptr;  // kMsPlanes level planes in the masks' layout
   int32_t* src = nullptr;
   LevelStats st;
   // two levels (even, odd: the mask and bitmap buffers swap roles) captured
@@ -857,7 +946,7 @@ void ms_free(MsWorkspace* m) {
   if (m->exec) (void)hipGraphExecDestroy(m->exec);
   if (m->graph) (void)hipGraphDestroy(m->graph);
   if (m->cap) (void)hipStreamDestroy(m->cap);
-  void* p[] = {m->vis, m->fr, m->frn, m->nx, m->bms, m->lev, m->src};
+  void* p[] = {m->vis, m->fr, m->frn, m->nx, m->bms, m->plane, m->src};
   for (void* x : p)
     if (x) (void)hipFree(x);
   stats_free(&m->st);
@@ -873,7 +962,6 @@ gsw_status ms_ensure(gsw_graph* g, int W, hipStream_t s) {
   if (!m) return fail(GSW_ENOMEM, "host allocation failed");
   m->n = g->n;
   m->W = W;
-  m->B = W * 64;
   const size_t mb = (size_t)g->n * W * sizeof(u64);
   struct Item {
     void** p;
@@ -883,8 +971,8 @@ gsw_status ms_ensure(gsw_graph* g, int W, hipStream_t s) {
                {(void**)&m->frn, mb},
                {(void**)&m->nx, mb},
                {(void**)&m->bms, 3 * (size_t)cdiv(g->n, 64) * sizeof(u64)},
-               {(void**)&m->lev, (size_t)g->n * m->B},
-               {(void**)&m->src, (size_t)m->B * sizeof(int32_t)}};
+               {(void**)&m->plane, kMsPlanes * mb},
+               {(void**)&m->src, (size_t)W * 64 * sizeof(int32_t)}};
   gsw_status st = GSW_OK;
   for (auto& it : items) {
     if (hipMalloc(it.p, it.bytes) != hipSuccess) {
@@ -920,11 +1008,10 @@ MsArgs ms_args(const gsw_graph* g, const MsWorkspace* m, bool odd) {
   a.tbm = m->bms + 2 * nw;
   a.heavy = g->heavy;
   a.n_heavy = g->n_heavy;
-  a.lev = m->lev;
+  a.plane = m->plane;
   a.ctl = m->st.ctl;
   a.n = g->n;
   a.W = m->W;
-  a.B = m->B;
   return a;
 }
 
@@ -1021,9 +1108,7 @@ gsw_status gsw_msbfs(const gsw_graph* cg, const int32_t* sources, int32_t n_sour
   const hipStream_t s = pick_stream(g, o->stream);
   GSW_TRY(ms_ensure(g, W, s));
   MsWorkspace* m = g->ms;
-  const int B = W * 64;  // level bytes per vertex in the workspace
   const int G = group_lanes(W);
-  const int64_t nw = cdiv(g->n, 64);
   if (o->graph) GSW_TRY(ms_capture(g, m, G, bs));
   // the ring must not hold records of an earlier call with the same level numbers
   std::memset(m->st.ring, 0, (size_t)kRing * kRecWords * sizeof(u64));
@@ -1034,15 +1119,13 @@ gsw_status gsw_msbfs(const gsw_graph* cg, const int32_t* sources, int32_t n_sour
   GSW_HIP(hipMemcpyAsync(m->st.ctl, m->st.h_ctl, sizeof(MsCtl), hipMemcpyHostToDevice, s));
   GSW_HIP(hipMemcpyAsync(m->src, sources, (size_t)n_sources * sizeof(int32_t), hipMemcpyHostToDevice, s));
   {
-    const int64_t work = std::max<int64_t>(g->n * W, g->n * (int64_t)B / 8);
-    const unsigned grid = (unsigned)std::min<int64_t>(cdiv(work, kMsBlock), 65536);
-    hipLaunchKernelGGL(k_ms_init, dim3(grid), dim3(kMsBlock), 0, s, m->vis, m->fr, m->frn, m->nx, m->bms,
-                       m->lev, g->n, W, n_sources, B);
-    hipLaunchKernelGGL(k_ms_sources, dim3((unsigned)cdiv(n_sources, 256)), dim3(256), 0, s, m->vis,
-                       m->fr, m->bms, m->lev, W, B, (const int32_t*)m->src, n_sources);
+    const unsigned grid = (unsigned)std::min<int64_t>(cdiv(g->n * W, kMsBlock), 65536);
+    hipLaunchKernelGGL(k_ms_init, dim3(grid), dim3(kMsBlock), 0, s, m->vis, m->nx, m->plane, m->bms, g->n, W,
+                       n_sources);
+    hipLaunchKernelGGL(k_ms_sources, dim3(1), dim3(kMsSeedBlock), 0, s, m->vis, m->fr, m->bms, W,
+                       (const int32_t*)m->src, n_sources);
     GSW_HIP(hipGetLastError());
   }
-  (void)nw;
   // Levels are queued up to kAhead beyond the last one whose record the host
   // has read; levels after the last productive one find nothing and change
   // nothing.  The captured graph queues two levels per launch.
@@ -1094,7 +1177,7 @@ gsw_status gsw_msbfs(const gsw_graph* cg, const int32_t* sources, int32_t n_sour
     return st;
   }
   if (n_levels) *n_levels = (int32_t)(d + 1);
-  // [n][B] -> [n_sources][n]
+  // level planes -> [n_sources][n]
   int8_t* out = levels;
   int8_t* tmp = nullptr;
   if (!o->device_ptrs) {
@@ -1104,9 +1187,22 @@ gsw_status gsw_msbfs(const gsw_graph* cg, const int32_t* sources, int32_t n_sour
     }
     out = tmp;
   }
-  hipLaunchKernelGGL(k_ms_transpose, dim3((unsigned)cdiv(g->n, kTr), (unsigned)cdiv(n_sources, kTr)),
-                     dim3(256), 0, s, (const int8_t*)m->lev, out, g->n, B, n_sources);
-  if (hipGetLastError() != hipSuccess) st = fail(GSW_EHIP, "transpose launch failed");
+  // the largest level written: d, whose digits are the planes in use
+  const int top = (int)std::min<int64_t>(d, GSW_MSBFS_LEVEL_CAP);
+  int planes = 0;
+  while (top >> planes) ++planes;
+  auto levels_out = [&](auto kernel, int tile, int block) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(g->n, tile)), dim3(block), 0, s, (const u64*)m->plane,
+                       (const u64*)m->vis, out, g->n, W, planes, n_sources);
+  };
+  switch (G) {
+    case 1: levels_out(k_ms_levels_out<1>, out_tile(1), out_block(1)); break;
+    case 2: levels_out(k_ms_levels_out<2>, out_tile(2), out_block(2)); break;
+    case 4: levels_out(k_ms_levels_out<4>, out_tile(4), out_block(4)); break;
+    case 8: levels_out(k_ms_levels_out<8>, out_tile(8), out_block(8)); break;
+    default: levels_out(k_ms_levels_out<16>, out_tile(16), out_block(16)); break;
+  }
+  if (hipGetLastError() != hipSuccess) st = fail(GSW_EHIP, "writing the levels failed");
   if (st == GSW_OK && !wide.empty()) {
     // the rerun, into the caller's rows (device) or a staging buffer (host)
     const size_t wb = wide.size() * (size_t)g->n * sizeof(int32_t);
@@ -1369,9 +1465,8 @@ gsw_status ss_queue_level(gsw_session* ss, bool* queued_one) {
     std::memcpy(h_start, ss->start_up.data(), (size_t)ss->slots * sizeof(long long));
     GSW_HIP(hipMemcpyAsync(ss->seed, h_seed, 2 * (size_t)ss->slots * sizeof(int32_t), hipMemcpyHostToDevice, s));
     GSW_HIP(hipMemcpyAsync(ss->start_d, h_start, ss->slots * sizeof(long long), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_ss_seed, dim3((unsigned)cdiv(c, 256)), dim3(256), 0, s, ss->vis, ss->fr, ss->fbm[0],
-                       ss->dist, ss->st.ctl, n, W, (const int32_t*)ss->seed, (const int32_t*)(ss->seed + ss->slots),
-                       c);
+    hipLaunchKernelGGL(k_ss_seed, dim3(1), dim3(kMsSeedBlock), 0, s, ss->vis, ss->fr, ss->fbm[0], ss->dist,
+                       ss->st.ctl, n, W, (const int32_t*)ss->seed, (const int32_t*)(ss->seed + ss->slots), c);
   }
   GSW_HIP(hipGetLastError());
   if (!running) {
@@ -1398,7 +1493,6 @@ gsw_status ss_queue_level(gsw_session* ss, bool* queued_one) {
   a.ctl = ss->st.ctl;
   a.n = n;
   a.W = W;
-  a.B = W * 64;
   GSW_TRY(launch_ms_level(a, ss->st, group_lanes(W), kMsBlock, s));
   GSW_HIP(hipGetLastError());
   std::swap(ss->fr, ss->frn);
