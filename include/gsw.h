@@ -363,7 +363,9 @@ gsw_status gsw_bfs_noalloc(const gsw_graph *g, const int32_t *sources, int32_t n
 
 typedef struct {
   float push_to_pull;  /* per source: switch it to bottom-up when its frontier's arcs exceed
-                          this fraction of the arcs it has not reached yet ... */
+                          this fraction of the arcs it has not reached yet (and the sources
+                          that would push all together, when their frontiers' arcs, added
+                          source by source, exceed half this fraction of all arcs) ... */
   float pull_to_push;  /* ... and back to top-down when they fall below this fraction of all arcs */
   int32_t device_ptrs; /* 1: levels (and wide_levels) are device memory; 0: host */
   int32_t graph;       /* 1: replay a captured two-level HIP graph; 0: launch each kernel */

@@ -51,12 +51,14 @@ typedef unsigned long long u64;
 
 constexpr int kMsBlock = 256;     // workgroup size of the helper kernels, default of the level kernels
 constexpr int kMsMaxBlock = 512;  // level kernels: 128, 256 or 512 threads (gsw_msbfs_opts.block_size)
-constexpr int kMsMaxWaves = 8192; // level kernels: wavefronts per launch at most
+constexpr int kMsMaxWaves = 16384; // level kernels: wavefronts per launch at most
+constexpr int kMsFinal = 1024;    // threads of the level's last kernel: one per source slot
 constexpr int kMsStats = 8;        // stat counters, spread like the queue bins
 constexpr int kMsStatStride = 32;  // u64 words between counters
 constexpr int kMsLong = 32;        // rows longer than this are walked by the whole wave
 constexpr int kMsHeavy = 1024;     // top-down: rows longer than this go through the chunk list
 constexpr int kMsChunk = 256;      // arcs per chunk of a heavy row
+constexpr int kMsBitmaps = 4;      // frontier of depth d and d+1, touched, full
 constexpr int kMsPlanes = 7;       // digits of the largest int8 level
 constexpr int kMsPlanesInit = 3;   // planes the init kernel clears: levels up to 7
 static_assert((1 << kMsPlanes) - 1 == GSW_MSBFS_LEVEL_CAP, "the planes hold every int8 level");
@@ -82,6 +84,7 @@ struct MsCtl {
   double to_push;        // top-down again once frontier arcs < to_push x all arcs
   u64 arcs;              // arcs of the graph
   int32_t any_push, any_pull;
+  int32_t direct;        // one mask word: bottom-up lookups skip the frontier bitmap this level
   long long d;           // this level's index (a session counts levels for as long as it lives)
   int32_t pull_ok;       // bottom-up allowed (symmetric graph)
   int32_t nslots, W;
@@ -94,11 +97,12 @@ struct MsArgs {
   const int32_t* __restrict__ cols;
   u64* vis;
   const u64* __restrict__ fr;   // depth-d masks
-  u64* frn;                     // depth-(d+1) masks (a row holds them where its fbm_n bit is set)
+  u64* frn;                     // depth-(d+1) masks (a row holds them where its fbm_n bit is set; W = 1: zero elsewhere)
   u64* nx;                      // top-down accumulator, zero between levels
   const u64* __restrict__ fbm;  // bit v: v is in some source's depth-d frontier
   u64* fbm_n;                   // the same for depth d+1 (holds depth d-1's until rewritten)
-  u64* tbm;                     // bit v: the top-down pass touched nx[v] (zero between levels)
+  u64* tbm;                     // bit v: the first pass touched nx[v] (zero between levels)
+  u64* full;                    // bit v: no source can find v any more (set by bottom-up levels)
   const u64* __restrict__ heavy;  // chunk list of rows longer than kMsHeavy
   int64_t n_heavy;
   u64* plane;                   // [kMsPlanes][n][W] binary digits of the levels (null for a session)
@@ -185,42 +189,44 @@ __device__ __forceinline__ void add_active(const MsArgs& a, int j, u64 act) {
 
 // Wave geometry: groups of G lanes (a power of two <= 16), one vertex per
 // group; the waves of the grid take 64-vertex bitmap words in turn.
+template <int G>
 struct Wave {
-  int G, j, gi, gpw, lane;
-  u64 gmask;  // this lane's group within the wave
+  static constexpr int kGroups = 64 / G;
+  static constexpr uint32_t kGroup = (1u << G) - 1u;  // a group's lanes, from its first
+  int lane, j, gi, first;                            // lane; word; group; the group's first lane
   int64_t wave, nwaves;
+  __device__ __forceinline__ Wave()
+      : lane(lane_id()), j(lane & (G - 1)), gi(lane / G), first(lane & ~(G - 1)),
+        wave(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6),
+        nwaves(((int64_t)gridDim.x * blockDim.x) >> 6) {}
+  // the lanes of this lane's group with p set (bit 0: the group's first)
+  __device__ __forceinline__ uint32_t group(bool p) const {
+    const u64 m = __ballot(p);
+    return ((first < 32 ? (uint32_t)m : (uint32_t)(m >> 32)) >> (first & 31)) & kGroup;
+  }
 };
-
-__device__ __forceinline__ Wave wave_of(int G) {
-  Wave w;
-  w.lane = lane_id();
-  w.G = G;
-  w.j = w.lane & (G - 1);
-  w.gi = w.lane / G;
-  w.gpw = 64 / G;
-  w.gmask = G == 64 ? ~0ull : (((1ull << G) - 1ull) << (w.gi * G));
-  w.wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  w.nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  return w;
-}
 
 // ------------------------------------------------------------------ init
 // Visited masks (bits of sources >= nsrc start visited), accumulators, the
 // first kMsPlanesInit level planes and the bitmaps.  The frontier masks are
-// not cleared: a vertex's row is read only where its frontier bit is set, and
-// was then written whole.
-__global__ void __launch_bounds__(kMsBlock) k_ms_init(u64* vis, u64* nx, u64* plane, u64* bms, int64_t n, int W,
-                                                      int nsrc) {
+// cleared only where there is one word per vertex: a wider row is read only
+// where its vertex's frontier bit is set, and was then written whole.
+__global__ void __launch_bounds__(kMsBlock) k_ms_init(u64* vis, u64* fr, u64* frn, u64* nx, u64* plane, u64* bms,
+                                                      int64_t n, int W, int nsrc) {
   const int64_t stride = (int64_t)gridDim.x * kMsBlock;
   const int64_t gid = (int64_t)blockIdx.x * kMsBlock + threadIdx.x;
   const int64_t words = n * W;
   for (int64_t i = gid; i < words; i += stride) {
     vis[i] = (nsrc & 63) ? ~valid_bits((int)(i % W), W, nsrc) : 0ull;
     nx[i] = 0ull;
+    if (W == 1) {
+      fr[i] = 0ull;
+      frn[i] = 0ull;
+    }
 #pragma unroll
     for (int p = 0; p < kMsPlanesInit; ++p) plane[(int64_t)p * words + i] = 0ull;
   }
-  const int64_t nb = 3 * ((n + 63) / 64);
+  const int64_t nb = kMsBitmaps * ((n + 63) / 64);
   for (int64_t i = gid; i < nb; i += stride) bms[i] = 0ull;
 }
 
@@ -246,7 +252,7 @@ __global__ void __launch_bounds__(kMsSeedBlock) k_ms_sources(u64* vis, u64* fr, 
 // With list == null only the total is added to *cursor.
 __global__ void __launch_bounds__(kMsBlock) k_heavy_build(const int64_t* __restrict__ offs, int64_t n,
                                                           u64* list, u64* cursor) {
-  const Wave w = wave_of(1);
+  const Wave<1> w;
   for (int64_t base = w.wave * 64; base < n; base += w.nwaves * 64) {
     const int64_t v = base + w.lane;
     long long nch = 0;
@@ -305,75 +311,285 @@ __device__ __forceinline__ void clear_plane(const MsArgs& a, long long d) {
     p[i] = 0ull;
 }
 
-// Every frontier vertex u of a top-down source: lane j pushes
-// fr[u][j] & pmask[j] along u's arcs.
-__global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a, int G) {
-  const bool any_push = a.ctl->any_push != 0;
-  if (!any_push && !a.ctl->any_pull) return;
+// ---------------------------------------------------------- bottom-up rows
+// A row's lookup for the sources in `need`: the OR of its frontier neighbours'
+// masks, up to the arc that covers them all.  Its columns and frontier bits
+// are read by many lanes at once, so that only the neighbours in the frontier
+// cost a step, and four of those have their mask lines in flight together:
+// one column, one bit and one line after another, an arc costs some 1.3 us
+// (R-MAT scale 20, 1024 sources: both passes of all levels 7.75 ms that way,
+// 3.2 ms now).
+constexpr int kMsHits = 4;
+
+// The neighbours held in column register c by the group's lanes in `hits`.
+// Every lane of the wave calls it.
+template <int G>
+__device__ __forceinline__ u64 take_hits(const MsArgs& a, const Wave<G>& w, uint32_t hits, int32_t c, u64 need,
+                                         u64 acc) {
+  constexpr int kQ = G < kMsHits ? G : kMsHits;
+  const u64* fr = a.fr + w.j;
+  while (__any(hits != 0u)) {
+    int32_t u[kQ];
+    u64 m[kQ];
+    bool h[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      h[q] = hits != 0u;
+      u[q] = __shfl(c, w.first + (h[q] ? __ffs((int)hits) - 1 : 0));
+      hits &= hits - 1u;
+    }
+    const u64 left = need & ~acc;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) m[q] = h[q] && left ? fr[(uint32_t)u[q] * (uint32_t)a.W] : 0ull;  // n W < 2^32
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) acc |= m[q] & need;
+    if (w.group(acc != need) == 0u) hits = 0u;
+  }
+  return acc;
+}
+
+__device__ __forceinline__ bool in_frontier(const MsArgs& a, int32_t u) {
+  return u >= 0 && ((a.fbm[u >> 6] >> (u & 63)) & 1ull);
+}
+
+// One row [beg, end) per group with `mine` set (uniform over the group): G
+// arcs per step.  Every lane of the wave calls it.
+template <int G>
+__device__ __forceinline__ u64 pull_row_group(const MsArgs& a, const Wave<G>& w, bool mine, u64 need, int64_t beg,
+                                              int64_t end) {
+  u64 acc = 0ull;
+  if constexpr (G <= 2) {  // too few lanes to share a row: each takes eight arcs at a time itself
+    const bool direct = G == 1 && a.ctl->direct;
+    const u64* fr = a.fr + w.j;
+    for (int64_t e = beg; mine && e < end && acc != need; e += 8) {
+      int32_t u[8];
+      u64 f[8], m[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) u[q] = e + q < end ? a.cols[e + q] : -1;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) f[q] = u[q] < 0 ? 0ull : direct ? ~0ull : a.fbm[u[q] >> 6];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) m[q] = (f[q] >> (u[q] & 63)) & 1ull ? fr[(uint32_t)u[q] * (uint32_t)a.W] : 0ull;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc |= m[q] & need;
+    }
+    return acc;
+  }
+  int32_t next = mine && beg + w.j < end ? a.cols[beg + w.j] : -1;
+  while (__any(mine)) {
+    const int32_t c = next;
+    beg += G;
+    next = mine && beg + w.j < end ? a.cols[beg + w.j] : -1;
+    acc = take_hits<G>(a, w, w.group(mine && in_frontier(a, c)), c, need, acc);
+    mine = mine && beg < end && w.group(acc != need) != 0u;
+  }
+  return acc;
+}
+
+// Row [beg, end) with the whole wave, 64 arcs per step: each group looks up
+// the neighbours that its own lanes hold for the same `need` (word j of the
+// row's vertex).  The result is the same in every group.
+template <int G>
+__device__ __forceinline__ u64 pull_row_wave(const MsArgs& a, const Wave<G>& w, u64 need, int64_t beg, int64_t end) {
+  u64 acc = 0ull;
+  int32_t next = beg + w.lane < end ? a.cols[beg + w.lane] : -1;
+  while (beg < end) {
+    const int32_t c = next;
+    beg += 64;
+    next = beg + w.lane < end ? a.cols[beg + w.lane] : -1;
+    acc = take_hits<G>(a, w, w.group(in_frontier(a, c)), c, need, acc);
+#pragma unroll
+    for (int off = G; off < 64; off <<= 1) acc |= __shfl_xor(acc, off);
+    if (__all(acc == need)) break;
+  }
+  return acc;
+}
+
+// Rows longer than this are walked by the whole wave.
+template <int G>
+__device__ constexpr int64_t long_row() {
+  return G <= 2 ? kMsLong : 4 * G;
+}
+
+// One mask word per vertex: rows too long for their own lane, up to kMsMid
+// arcs, are taken four at a time, a quarter of the wave each (16 lanes, four
+// arcs per lane in flight).  Quarter q works on the row of the q-th set lane
+// of `rows`, or on none (owner -1).
+constexpr int64_t kMsMid = 512;
+struct Quarter {
+  int owner, sub;
+  int64_t beg, end;
+  __device__ __forceinline__ Quarter(u64 rows, int64_t lane_beg, int64_t lane_end) {
+    const int q = lane_id() >> 4;
+    sub = lane_id() & 15;
+    owner = q < __popcll(rows) ? nth_set_bit(rows, q) : -1;
+    beg = __shfl((long long)lane_beg, owner < 0 ? 0 : owner);
+    end = __shfl((long long)lane_end, owner < 0 ? 0 : owner);  // (by every lane: any may be read)
+    if (owner < 0) end = beg;
+  }
+};
+__device__ __forceinline__ u64 drop_four(u64 m) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) m &= m - 1ull;
+  return m;
+}
+
+// The rows of the lanes in `rows` for their `need`; returns the lane's own.
+__device__ __forceinline__ u64 pull_rows_quarter(const MsArgs& a, u64 rows, u64 need, int64_t lane_beg,
+                                                 int64_t lane_end) {
+  u64 mine = 0ull;
+  const int lane = lane_id();
+  while (rows) {
+    const Quarter q(rows, lane_beg, lane_end);
+    const u64 want = __shfl(need, q.owner < 0 ? 0 : q.owner);
+    u64 acc = 0ull;
+    int64_t e = q.beg + q.sub;
+    bool more = q.beg < q.end;
+    while (__any(more)) {
+      int32_t u[4];
+      u64 m[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[k] = more && e + 16 * k < q.end ? a.cols[e + 16 * k] : -1;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) m[k] = u[k] < 0 || (!a.ctl->direct && !in_frontier(a, u[k])) ? 0ull : a.fr[u[k]];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc |= m[k] & want;
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) acc |= __shfl_xor(acc, off);
+      e += 64;
+      more = more && e - q.sub < q.end && acc != want;
+    }
+    const int r = __popcll(rows & ((1ull << lane) - 1ull));
+    const u64 got = __shfl(acc, 16 * (r & 3));
+    if (((rows >> lane) & 1ull) && r < 4) mine = got;
+    rows = drop_four(rows);
+  }
+  return mine;
+}
+
+// Pushes the word f of every lane in `rows` along its row.
+__device__ __forceinline__ void push_rows_quarter(const MsArgs& a, u64 rows, u64 f, int64_t lane_beg,
+                                                  int64_t lane_end) {
+  while (rows) {
+    const Quarter q(rows, lane_beg, lane_end);
+    const u64 fw = __shfl(f, q.owner < 0 ? 0 : q.owner);
+    push_arcs(a, fw, 0, q.beg + q.sub, q.end, 16);
+    rows = drop_four(rows);
+  }
+}
+
+// Pushes the words f (word j, the same in every group) along [beg, end) with
+// the whole wave: group gi taking arcs gi, gi + 64/G, ... with all words, or,
+// where only a few words push, all lanes one word after another.
+constexpr int kMsLight = 3;  // words
+constexpr int kMsFew = 16;   // frontier vertices of a bitmap word
+template <int G>
+__device__ __forceinline__ void push_row_wave(const MsArgs& a, const Wave<G>& w, u64 f, int64_t beg, int64_t end) {
+  u64 nz = __ballot(f != 0ull) & Wave<G>::kGroup;
+  if (G > 1 && __popcll(nz) <= kMsLight) {
+    for (; nz; nz &= nz - 1ull) {
+      const int jj = __ffsll((long long)nz) - 1;
+      push_arcs(a, __shfl(f, jj), jj, beg + w.lane, end, 64);
+    }
+  } else if (f) {
+    push_arcs(a, f, w.j, beg + w.gi, end, Wave<G>::kGroups);
+  }
+}
+
+// The level's first pass.  Every frontier vertex u of a top-down source: lane
+// j pushes fr[u][j] & pmask[j] along u's arcs.  A group few of whose words
+// push (a young source has one bit in one word) spreads each such word's row
+// over its lanes instead of leaving it to the word's own lane.  Then the rows
+// of the chunk list, one chunk per wave, so that a hub's row is spread over
+// the grid: top-down as above, and bottom-up for the hub's own needs, joined
+// in its accumulator (the second pass leaves these rows out).
+template <int G>
+__global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
+  const bool any_push = a.ctl->any_push != 0, any_pull = a.ctl->any_pull != 0;
+  if (!any_push && !any_pull) return;
   clear_plane(a, a.ctl->d);
-  if (!any_push) return;
-  const Wave w = wave_of(G);
+  const Wave<G> w;
   const int j = w.j;
   const u64 pm = j < a.W ? a.ctl->pmask[j] : 0ull;
-  const int64_t nwords = (a.n + 63) / 64;
+  const u64 qm = j < a.W ? a.ctl->qmask[j] : 0ull;
+  const int64_t nwords = any_push ? (a.n + 63) / 64 : 0;
   for (int64_t wd = w.wave; wd < nwords; wd += w.nwaves) {
     const u64 word = a.fbm[wd];
     if (!word) continue;
     const int cnt = __popcll(word);
-    for (int r0 = 0; r0 < cnt; r0 += w.gpw) {
+    for (int r0 = 0; r0 < cnt; r0 += Wave<G>::kGroups) {
       const int k = r0 + w.gi;
       const bool has = k < cnt;
       const int64_t u = wd * 64 + (has ? nth_set_bit(word, k) : 0);
       const u64 f = (has && pm) ? (a.fr[u * a.W + j] & pm) : 0ull;
-      const bool act = (__ballot(f != 0ull) & w.gmask) != 0ull;
+      const uint32_t words = w.group(f != 0ull);
       int64_t beg = 0, end = 0;
-      if (act) {
+      if (words) {
         beg = a.offs[u];
         end = a.offs[u + 1];
       }
       const int64_t deg = end - beg;
-      if (f && deg <= kMsLong) push_arcs(a, f, j, beg, end, 1);
-      // medium rows: the whole wave, group gi taking arcs gi, gi + 64/G, ...
-      u64 lm = __ballot(deg > kMsLong && deg <= kMsHeavy && j == 0);
+      const bool own = words && deg <= kMsLong;
+      // few frontier vertices in the word would leave most lanes idle
+      const bool light = G > 1 ? __popc(words) <= kMsLight : cnt <= kMsFew;
+      if (own && !light && f) push_arcs(a, f, j, beg, end, 1);
+      if constexpr (G == 1)
+        push_rows_quarter(a, __ballot(f != 0ull && deg <= kMsMid && (light || deg > kMsLong)), f, beg, end);
+      if constexpr (G > 1) {
+        uint32_t left = own && light ? words : 0u;
+        while (__any(left != 0u)) {
+          const int jj = left ? __ffs((int)left) - 1 : 0;
+          const u64 fw = __shfl(f, w.first + jj);
+          if (left) push_arcs(a, fw, jj, beg + j, end, G);
+          left &= left - 1u;
+        }
+      }
+      // medium rows
+      u64 lm = __ballot(deg > (G == 1 ? kMsMid : kMsLong) && deg <= kMsHeavy && j == 0);
       while (lm) {
         const int src = __ffsll((long long)lm) - 1;
         lm &= lm - 1ull;
         const int64_t b = __shfl((long long)beg, src);
         const int64_t en = __shfl((long long)end, src);
-        const u64 fw = __shfl(f, src + j);
-        if (fw) push_arcs(a, fw, j, b + w.gi, en, w.gpw);
+        push_row_wave<G>(a, w, __shfl(f, src + j), b, en);
       }
     }
   }
-  // heavy rows: the chunk list dealt out one entry per wave, so that the
-  // consecutive chunks of one hub's row go to different waves
   for (int64_t c = w.wave; c < a.n_heavy; c += w.nwaves) {
     const u64 ent = a.heavy[c];
     const int64_t u = (int64_t)(ent >> 32);
-    if (!((a.fbm[u >> 6] >> (u & 63)) & 1ull)) continue;
+    const bool in = (a.fbm[u >> 6] >> (u & 63)) & 1ull;
+    const u64 fw = in && pm ? (a.fr[u * a.W + j] & pm) : 0ull;
+    const u64 need = qm ? ~a.vis[u * a.W + j] & qm : 0ull;
+    const bool push = __any(fw != 0ull), pull = __any(need != 0ull);
+    if (!push && !pull) continue;
     const int64_t ci = (int64_t)(ent & 0xffffffffull);
-    const u64 fw = pm ? (a.fr[u * a.W + j] & pm) : 0ull;
-    if (__ballot(fw != 0ull) == 0ull) continue;
     const int64_t b = a.offs[u] + ci * kMsChunk;
     const int64_t en = std::min<int64_t>(a.offs[u + 1], b + kMsChunk);
-    if (fw) push_arcs(a, fw, j, b + w.gi, en, w.gpw);
+    if (push) push_row_wave<G>(a, w, fw, b, en);
+    if (pull) {
+      const u64 acc = pull_row_wave<G>(a, w, need, b, en);
+      if (w.gi == 0 && acc && !atomicOr(a.nx + u * a.W + j, acc)) atomicOr(a.tbm + (u >> 6), 1ull << (u & 63));
+    }
   }
 }
 
 // ------------------------------------------------------ bottom-up + update
-// Each 64-vertex word: the vertices with possible work are all of them when
-// some source pulls, else those the top-down pass touched.  For such a vertex v: the bottom-up
-// sources it still needs (~vis & qmask) are looked up in the neighbours'
-// frontier masks (frontier bit first), stopping once all are covered; what
-// the top-down pass left in nx (minus vis) joins them.  v's group is the only
-// writer of v's masks and levels; the wave writes the word of the next
-// frontier bitmap whole.  Also accumulates the level's statistics: vertices
-// with new bits and their degrees, per source the degree sum of its new
-// frontier (each source's direction is steered by it), and the OR of the new
-// frontier masks.
-__global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
+// Each 64-vertex word: the vertices with possible work are, when some source
+// pulls, all but those that every source has seen or that have no arcs (noted
+// in a bitmap as they are met: 43% of an R-MAT's vertices from the first such
+// level on, nearly all in the last), else those the first pass touched.  For such a vertex v:
+// the bottom-up sources it still needs (~vis & qmask, minus what the first
+// pass found) are looked up in the neighbours' frontier masks; what the first
+// pass left in nx (minus vis) joins them.  v's group is the only writer of
+// v's masks and levels; the wave writes the word of the next frontier bitmap
+// whole.  Also accumulates the level's statistics: vertices with new bits and
+// their degrees, per source the degree sum of its new frontier (each source's
+// direction is steered by it), and the OR of the new frontier masks.
+template <int G>
+__global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a) {
   __shared__ u64 s_ef[kMaxSlots];
-  const Wave w = wave_of(G);
+  const Wave<G> w;
   const int j = w.j;
   const bool lane_live = j < a.W;
   const MsCtl* ctl = a.ctl;
@@ -388,56 +604,45 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
   for (int64_t wd = w.wave; wd < nwords; wd += w.nwaves) {
     const int64_t base = wd * 64;
     const u64 valid = base + 64 <= a.n ? ~0ull : ((1ull << (a.n - base)) - 1ull);
-    const u64 touched = any_push ? a.tbm[wd] : 0ull;
-    const u64 work = (any_pull ? ~0ull : touched) & valid;
-    u64 nbits = 0ull;
+    const u64 touched = any_push || (any_pull && a.n_heavy > 0) ? a.tbm[wd] : 0ull;
+    const u64 full = any_pull ? a.full[wd] : 0ull;
+    const u64 work = (any_pull ? ~full | touched : touched) & valid;
+    u64 nbits = 0ull, fbits = 0ull;
+    const u64 stale = G == 1 ? a.fbm_n[wd] : 0ull;
     const int cnt = __popcll(work);
-    for (int r0 = 0; r0 < cnt; r0 += w.gpw) {
+    for (int r0 = 0; r0 < cnt || (G == 1 && r0 == 0 && stale); r0 += Wave<G>::kGroups) {
+      // with a lane per vertex the word's vertices stay in place
       const int k = r0 + w.gi;
-      const bool has = k < cnt;
-      const int bit = has ? nth_set_bit(work, k) : 0;
+      const bool has = G == 1 ? (work >> w.lane) & 1ull : k < cnt;
+      const int bit = G == 1 ? w.lane : has ? nth_set_bit(work, k) : 0;
       const int64_t v = base + bit;
       const bool in = has && lane_live;
       const int64_t i = v * a.W + j;
       const u64 x = (in && ((touched >> bit) & 1ull)) ? a.nx[i] : 0ull;
-      const u64 s = (in && (x || qm)) ? a.vis[i] : ~0ull;
-      const u64 need = ~s & qm;
-      const bool want = (__ballot(need != 0ull) & w.gmask) != 0ull;
+      const u64 s = (in && (x || any_pull)) ? a.vis[i] : ~0ull;
+      const u64 need = ~s & qm & ~x;
+      const bool want = w.group(need != 0ull) != 0u;
       int64_t beg = 0, end = 0;
       if (want) {
         beg = a.offs[v];
         end = a.offs[v + 1];
       }
-      const bool lng = end - beg > kMsLong;
-      u64 acc = 0ull;
-      if (want && !lng) {
-        for (int64_t e = beg; e < end; ++e) {
-          const int64_t u = a.cols[e];
-          if (need && ((a.fbm[u >> 6] >> (u & 63)) & 1ull)) acc |= a.fr[u * a.W + j] & need;
-          if ((__ballot(acc == need) & w.gmask) == w.gmask) break;
-        }
-      }
-      u64 lm = __ballot(lng && j == 0);
+      const bool lng = end - beg > long_row<G>();
+      u64 acc = pull_row_group<G>(a, w, want && !lng && beg < end, need, beg, end);
+      if constexpr (G == 1)
+        acc |= pull_rows_quarter(a, __ballot(lng && end - beg <= kMsMid), need, beg, end);
+      u64 lm = __ballot(lng && end - beg > (G == 1 ? kMsMid : 0) && end - beg <= kMsHeavy && j == 0);
       while (lm) {
         const int src = __ffsll((long long)lm) - 1;
         lm &= lm - 1ull;
-        const int64_t b = __shfl((long long)beg, src);
-        const int64_t en = __shfl((long long)end, src);
-        const u64 nw = __shfl(need, src + j);
-        u64 c = 0ull;
-        for (int64_t e0 = b; e0 < en; e0 += w.gpw) {  // same trip count on every lane
-          const int64_t e = e0 + w.gi;
-          if (e < en && nw) {
-            const int64_t u = a.cols[e];
-            if ((a.fbm[u >> 6] >> (u & 63)) & 1ull) c |= a.fr[u * a.W + j] & nw;
-          }
-          for (int off = G; off < 64; off <<= 1) c |= __shfl_xor(c, off);
-          if (__all(c == nw)) break;
-        }
-        if (w.gi * G == src) acc = c;
+        const u64 c = pull_row_wave<G>(a, w, __shfl(need, src + j), __shfl((long long)beg, src),
+                                       __shfl((long long)end, src));
+        if (w.first == src) acc = c;
       }
       const u64 nb = (x & ~s) | acc;  // acc is within ~s
-      const bool grp_new = (__ballot(nb != 0ull) & w.gmask) != 0ull;
+      const bool grp_new = w.group(nb != 0ull) != 0u;
+      // seen by every source, or without arcs
+      if (any_pull && has && ((want && beg == end) || w.group((s | nb) != ~0ull) == 0u)) fbits |= 1ull << bit;
       if (grp_new && !want) {
         beg = a.offs[v];
         end = a.offs[v + 1];
@@ -455,9 +660,10 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
             atomicAdd(&s_ef[j * 64 + bt], deg);
           }
         }
-        if (grp_new) a.frn[i] = nb;  // the row whole: its frontier bit is set below
+        if (G > 1 && grp_new) a.frn[i] = nb;  // the row whole: its frontier bit is set below
         act |= nb;
       }
+      if (G == 1 && (stale || __any(nb != 0ull)) && ((valid >> bit) & 1ull)) a.frn[v] = nb;
       if (grp_new && j == 0) {
         nv += 1;
         ne += deg;
@@ -465,10 +671,14 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
       }
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) nbits |= __shfl_xor(nbits, off);
+    for (int off = 32; off > 0; off >>= 1) {
+      nbits |= __shfl_xor(nbits, off);
+      fbits |= __shfl_xor(fbits, off);
+    }
     if (w.lane == 0) {
       a.fbm_n[wd] = nbits;
       if (touched) a.tbm[wd] = 0ull;
+      if (fbits) a.full[wd] = full | fbits;
     }
   }
   add_stats(a, nv, ne);
@@ -487,11 +697,25 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a, int G) {
 // the arcs the source has not reached yet (a bottom-up pass is shared by all
 // pulling sources, and one with a small frontier would make every vertex
 // scan its whole row), top-down again once they fall below to_push of all
-// arcs.
-__global__ void __launch_bounds__(256) k_ms_finalize(MsCtl* ctl, u64* stats, u64* active, u64* slot_ef,
-                                                     u64* ring) {
+// arcs.  Sources that would each push go bottom-up together once the arcs
+// they would push along, source by source, exceed kMsTogether times to_pull
+// of all arcs: the second pass then looks all of them up at once, where the
+// first would read and update masks arc by arc (per call at 10, 3 and 0.5:
+// R-MAT scale 20, 1024 sources 4.9, 4.8 and 4.3 ms; 64 sources on a random
+// graph of 700001 vertices 1.04, 0.76 and 0.74 ms).
+constexpr double kMsTogether = 0.5;
+// With one mask word per vertex, masks are zero outside the frontier, and a
+// lookup reads them at once when at least one vertex in kMsDirect is in the
+// frontier: the bit saves an 8-byte gather only where it is clear, and costs
+// one of its own (random graph of 700001 vertices, 64 sources: 103 us against
+// 86 at a level with 33% of the vertices in the frontier, 106 against 136 at
+// 63%).
+constexpr u64 kMsDirect = 2;
+
+__global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats, u64* active, u64* slot_ef,
+                                                          u64* ring, int64_t n) {
   __shared__ u64 s_act[kMaxWords], s_p[kMaxWords], s_q[kMaxWords];
-  __shared__ u64 s_v, s_e;
+  __shared__ u64 s_v, s_e, s_pushed;
   const int t = threadIdx.x;
   const int W = ctl->W, nslots = ctl->nslots;
   const long long d = ctl->d;
@@ -522,13 +746,14 @@ __global__ void __launch_bounds__(256) k_ms_finalize(MsCtl* ctl, u64* stats, u64
     if (t == 0) {
       s_v = v;
       s_e = e;
+      s_pushed = 0ull;
     }
   }
   __syncthreads();
   const double to_pull = ctl->to_pull, to_push = ctl->to_push;
   const u64 arcs = ctl->arcs;
   const bool pull_ok = ctl->pull_ok != 0;
-  for (int k = t; k < nslots; k += 256) {
+  for (int k = t; k < nslots; k += kMsFinal) {
     u64 ef = 0ull;
     for (int r = 0; r < kMsStats; ++r) {
       ef += slot_ef[r * kMaxSlots + k];
@@ -544,9 +769,20 @@ __global__ void __launch_bounds__(256) k_ms_finalize(MsCtl* ctl, u64* stats, u64
       else if (p && (double)ef < to_push * (double)arcs) p = 0;
       ctl->pull[k] = p;
       atomicOr(p ? &s_q[k >> 6] : &s_p[k >> 6], 1ull << (k & 63));
+      if (!p) atomicAdd(&s_pushed, ef);
     }
   }
   __syncthreads();
+  if (pull_ok && (double)s_pushed > kMsTogether * to_pull * (double)arcs) {
+    for (int k = t; k < nslots; k += kMsFinal)
+      if ((s_p[k >> 6] >> (k & 63)) & 1ull) ctl->pull[k] = 1;
+    __syncthreads();
+    if (t < kMaxWords) {
+      s_q[t] |= s_p[t];
+      s_p[t] = 0ull;
+    }
+    __syncthreads();
+  }
   u64* rec = ring + (size_t)(d % kRing) * kRecWords;
   if (t < kMaxWords) {
     ctl->pmask[t] = s_p[t];
@@ -561,13 +797,16 @@ __global__ void __launch_bounds__(256) k_ms_finalize(MsCtl* ctl, u64* stats, u64
     }
     ctl->any_push = p != 0ull;
     ctl->any_pull = q != 0ull;
+    ctl->direct = W == 1 && s_v * kMsDirect > (u64)n;
     ctl->d = d + 1;
     __hip_atomic_store(rec + 1, s_v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(rec + 2, s_e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  __threadfence_system();
+  // the record's words, written through to host memory, have landed before
+  // its first one is (a release fence would write back the whole L2 for them)
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (t == 0) __hip_atomic_store(rec, (u64)d + 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (t == 0) __hip_atomic_store(rec, (u64)d + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Level planes -> [nsrc][n] bytes.  A thread takes four consecutive vertices
@@ -685,15 +924,19 @@ __global__ void __launch_bounds__(out_block(G)) k_ms_levels_out(const u64* __res
 
 // ------------------------------------------------------------- sessions
 // vis = (vis & ~clr) | set on every vertex: slots being admitted start
-// unvisited everywhere, freed slots become inert (visited everywhere).
-__global__ void __launch_bounds__(kMsBlock) k_ss_masks(u64* vis, int64_t n, int W,
+// unvisited everywhere (so no vertex is known to be full any more), freed
+// slots become inert (visited everywhere).
+__global__ void __launch_bounds__(kMsBlock) k_ss_masks(u64* vis, u64* full, int64_t n, int W, int admits,
                                                        const u64* __restrict__ clr,
                                                        const u64* __restrict__ set) {
   const int64_t stride = (int64_t)gridDim.x * kMsBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kMsBlock + threadIdx.x; i < n * W; i += stride) {
+  const int64_t gid = (int64_t)blockIdx.x * kMsBlock + threadIdx.x;
+  for (int64_t i = gid; i < n * W; i += stride) {
     const int j = (int)(i % W);
     vis[i] = (vis[i] & ~clr[j]) | set[j];
   }
+  if (admits)
+    for (int64_t i = gid; i < (n + 63) / 64; i += stride) full[i] = 0ull;
 }
 
 // Admitted slots, by one workgroup: a source that is in no slot's frontier has
@@ -905,7 +1148,7 @@ gsw_status launch_ms_level(MsArgs a, const LevelStats& st, int G, int bs, hipStr
   a.ctl = st.ctl;
   // every buffer the kernels touch must be there: a missing one would be a
   // device fault, so it is an error here
-  const void* need[] = {a.offs, a.cols, a.vis, a.fr, a.frn, a.nx, a.fbm, a.fbm_n, a.tbm,
+  const void* need[] = {a.offs, a.cols, a.vis, a.fr, a.frn, a.nx, a.fbm, a.fbm_n, a.tbm, a.full,
                         a.stats, a.active, a.slot_ef, a.ctl, st.d_ring};
   for (const void* p : need)
     if (!p) return fail(GSW_EINVAL, "batched level launched with a missing buffer");
@@ -914,10 +1157,19 @@ gsw_status launch_ms_level(MsArgs a, const LevelStats& st, int G, int bs, hipStr
       (bs != 128 && bs != 256 && bs != 512))
     return fail(GSW_EINVAL, "batched level launched with inconsistent arguments");
   const unsigned grid = ms_grid(a.n, bs);
-  hipLaunchKernelGGL(k_ms_push, dim3(grid), dim3(bs), 0, s, a, G);
-  hipLaunchKernelGGL(k_ms_level, dim3(grid), dim3(bs), 0, s, a, G);
-  hipLaunchKernelGGL(k_ms_finalize, dim3(1), dim3(256), 0, s, st.ctl, st.stats, st.active, st.slot_ef,
-                     st.d_ring);
+  auto passes = [&](auto push, auto level) {
+    hipLaunchKernelGGL(push, dim3(grid), dim3(bs), 0, s, a);
+    hipLaunchKernelGGL(level, dim3(grid), dim3(bs), 0, s, a);
+  };
+  switch (G) {
+    case 1: passes(k_ms_push<1>, k_ms_level<1>); break;
+    case 2: passes(k_ms_push<2>, k_ms_level<2>); break;
+    case 4: passes(k_ms_push<4>, k_ms_level<4>); break;
+    case 8: passes(k_ms_push<8>, k_ms_level<8>); break;
+    default: passes(k_ms_push<16>, k_ms_level<16>); break;
+  }
+  hipLaunchKernelGGL(k_ms_finalize, dim3(1), dim3(kMsFinal), 0, s, st.ctl, st.stats, st.active, st.slot_ef,
+                     st.d_ring, a.n);
   return GSW_OK;
 }
 
@@ -928,7 +1180,7 @@ struct MsWorkspace {
   int W = 0;
   int bs = 0;  // block size the captured graph was made with
   u64 *vis = nullptr, *fr = nullptr, *frn = nullptr, *nx = nullptr;
-  u64* bms = nullptr;  // 3 bitmaps of ceil(n/64) words: frontier (two) and touched
+  u64* bms = nullptr;  // kMsBitmaps bitmaps of ceil(n/64) words
   u64* plane = nullptr;  // kMsPlanes level planes in the masks' layout
   int32_t* src = nullptr;
   LevelStats st;
@@ -970,7 +1222,7 @@ gsw_status ms_ensure(gsw_graph* g, int W, hipStream_t s) {
                {(void**)&m->fr, mb},
                {(void**)&m->frn, mb},
                {(void**)&m->nx, mb},
-               {(void**)&m->bms, 3 * (size_t)cdiv(g->n, 64) * sizeof(u64)},
+               {(void**)&m->bms, kMsBitmaps * (size_t)cdiv(g->n, 64) * sizeof(u64)},
                {(void**)&m->plane, kMsPlanes * mb},
                {(void**)&m->src, (size_t)W * 64 * sizeof(int32_t)}};
   gsw_status st = GSW_OK;
@@ -1006,6 +1258,7 @@ MsArgs ms_args(const gsw_graph* g, const MsWorkspace* m, bool odd) {
   a.fbm = m->bms + (odd ? nw : 0);
   a.fbm_n = m->bms + (odd ? 0 : nw);
   a.tbm = m->bms + 2 * nw;
+  a.full = m->bms + 3 * nw;
   a.heavy = g->heavy;
   a.n_heavy = g->n_heavy;
   a.plane = m->plane;
@@ -1120,8 +1373,8 @@ gsw_status gsw_msbfs(const gsw_graph* cg, const int32_t* sources, int32_t n_sour
   GSW_HIP(hipMemcpyAsync(m->src, sources, (size_t)n_sources * sizeof(int32_t), hipMemcpyHostToDevice, s));
   {
     const unsigned grid = (unsigned)std::min<int64_t>(cdiv(g->n * W, kMsBlock), 65536);
-    hipLaunchKernelGGL(k_ms_init, dim3(grid), dim3(kMsBlock), 0, s, m->vis, m->nx, m->plane, m->bms, g->n, W,
-                       n_sources);
+    hipLaunchKernelGGL(k_ms_init, dim3(grid), dim3(kMsBlock), 0, s, m->vis, m->fr, m->frn, m->nx, m->plane, m->bms,
+                       g->n, W, n_sources);
     hipLaunchKernelGGL(k_ms_sources, dim3(1), dim3(kMsSeedBlock), 0, s, m->vis, m->fr, m->bms, W,
                        (const int32_t*)m->src, n_sources);
     GSW_HIP(hipGetLastError());
@@ -1248,7 +1501,7 @@ struct gsw_session {
   gsw_graph* g = nullptr;
   int W = 0, slots = 0;
   u64 *vis = nullptr, *fr = nullptr, *frn = nullptr, *nx = nullptr;
-  u64* bms = nullptr;     // frontier bitmaps (depth d, d+1) and the touched bitmap
+  u64* bms = nullptr;     // kMsBitmaps bitmaps
   u64* fbm[2] = {};       // fbm[0] pairs with fr, fbm[1] with frn (swapped together)
   u64* masks = nullptr;   // clr[kMaxWords] then set[kMaxWords]
   int32_t *dist = nullptr, *seed = nullptr;  // seed: src[slots] then slot[slots]
@@ -1304,7 +1557,7 @@ size_t gsw_session_bytes(const gsw_graph* g, int32_t max_slots) {
   const int64_t n = g->n;
   const size_t W = (size_t)(max_slots + 63) / 64;
   const size_t words = (size_t)cdiv(n, 64);
-  return 4 * (size_t)n * W * sizeof(u64) + 3 * words * sizeof(u64) + 2 * (size_t)kMaxWords * sizeof(u64) +
+  return 4 * (size_t)n * W * sizeof(u64) + kMsBitmaps * words * sizeof(u64) + 2 * (size_t)kMaxWords * sizeof(u64) +
          (size_t)max_slots * n * sizeof(int32_t) + (size_t)max_slots * sizeof(long long) +
          2 * (size_t)max_slots * sizeof(int32_t) + (size_t)n * sizeof(int32_t) + stats_bytes();
 }
@@ -1330,7 +1583,7 @@ gsw_status gsw_session_create(const gsw_graph* cg, int32_t max_slots, gsw_sessio
   const int64_t n = g->n;
   const int64_t nw = cdiv(n, 64);
   const size_t mb = (size_t)n * ss->W * sizeof(u64);
-  const size_t bb = 3 * (size_t)nw * sizeof(u64);
+  const size_t bb = kMsBitmaps * (size_t)nw * sizeof(u64);
   struct Item {
     void** p;
     size_t bytes;
@@ -1458,7 +1711,8 @@ gsw_status ss_queue_level(gsw_session* ss, bool* queued_one) {
   if (any_mask) {
     GSW_HIP(hipMemcpyAsync(ss->masks, h_masks, 2 * (size_t)kMaxWords * sizeof(u64), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_ss_masks, dim3((unsigned)std::min<int64_t>(cdiv(n * W, kMsBlock), 65536)),
-                       dim3(kMsBlock), 0, s, ss->vis, n, W, (const u64*)ss->masks,
+                       dim3(kMsBlock), 0, s, ss->vis, ss->bms + 3 * cdiv(n, 64), n, W, c > 0 ? 1 : 0,
+                       (const u64*)ss->masks,
                        (const u64*)(ss->masks + kMaxWords));
   }
   if (c > 0) {
@@ -1486,6 +1740,7 @@ gsw_status ss_queue_level(gsw_session* ss, bool* queued_one) {
   a.fbm = ss->fbm[0];
   a.fbm_n = ss->fbm[1];
   a.tbm = ss->bms + 2 * cdiv(n, 64);
+  a.full = ss->bms + 3 * cdiv(n, 64);
   a.heavy = g->heavy;
   a.n_heavy = g->n_heavy;
   a.dist = ss->dist;
