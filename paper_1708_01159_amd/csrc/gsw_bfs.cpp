@@ -25,6 +25,13 @@ constexpr int kAhead = 3;
 // Single-workgroup launches queued beyond the latest record's: one runs
 // many levels, so one more is enough to follow it without a gap.
 constexpr int kSoloAhead = 2;
+// Levels of one such launch: few at first; many, with the visited bitmap in
+// LDS where it fits, once the search has turned out to be long (loading and
+// storing 128 KiB costs as much as two levels).  A bitmap of at most
+// kSoloVisSmall words costs next to nothing and always goes there.
+constexpr int32_t kSoloLevels = 32;
+constexpr int64_t kSoloDeep = 32;
+constexpr int64_t kSoloVisSmall = 2048;
 
 // Launch size for queued levels: the full grid, or kSmallLaunch workgroups
 // while the search is in a quiet phase -- the latest frontier the host knows
@@ -252,6 +259,7 @@ BfsBase make_base(const gsw_graph* g, const Workspace& w, int32_t* lv, int32_t* 
   const double dm = g->deg_stats[4];
   b.deg_max = dm >= 2147483647.0 ? 2147483647 : (int32_t)dm;
   b.head_ranked = w.head_ranked ? 1 : 0;
+  b.head_rows = g->symmetric && !w.head_ranked ? 1 : 0;
   b.solo = 0;
   return b;
 }
@@ -335,7 +343,7 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   BfsBase b = make_base(g, w, lv, canonical ? nullptr : pa, timed, o->count_arcs != 0);
   // single-workgroup multi-level launches: not with per-launch events (their
   // levels would share one launch's time), and with a tree its workgroup holds
-  b.solo = !o->no_solo && !events && (o->policy != GSW_POLICY_TREE || w.tree_nodes <= kSoloTree) ? kSoloMaxLevels : 0;
+  b.solo = !o->no_solo && !events && (o->policy != GSW_POLICY_TREE || w.tree_nodes <= kSoloTree) ? kSoloLevels : 0;
   GSW_TRY(launch_init(g, b, g->iso, src, k0, flags0, s));
   if (events) GSW_HIP(hipEventRecord(ev_after(-1), s));
   int64_t launched = 0;  // launches of the level kernels so far
@@ -345,6 +353,9 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   // always a full-grid one, which runs whatever level it finds.
   bool solo = b.solo && solo_eligible(k0, 1, 1, 1, g->n, b.deg_max);
   bool last_solo = false;
+  // such a launch hands a level back only for its arcs: not where the largest
+  // degree bounds them, so there one may follow another
+  const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs;
   int want = solo ? kSoloAhead : kAhead + level_launches(k0, 1) - 1;
   const int32_t cap = o->max_workgroups > 0 && o->max_workgroups < b.grid_max ? o->max_workgroups : b.grid_max;
   int32_t size = cap;
@@ -352,10 +363,12 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   int64_t d = 0;
   for (;; ++d) {
     while (launched - consumed < want) {
-      last_solo = solo && !last_solo;
-      if (last_solo)
-        GSW_TRY(launch_level_solo(g, b, dp, (int32_t)launched, s));
-      else
+      last_solo = solo && (solo_always || !last_solo);
+      if (last_solo) {
+        const bool deep = d >= kSoloDeep;
+        b.solo = deep ? kSoloMaxLevels : kSoloLevels;
+        GSW_TRY(launch_level_solo(g, b, dp, (int32_t)launched, deep || w.nw <= kSoloVisSmall, s));
+      } else
         GSW_TRY(launch_level_auto(g, b, dp, (int32_t)launched, size, s));
       if (events) GSW_HIP(hipEventRecord(ev_after(launched), s));
       ++launched;
@@ -627,7 +640,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
       const int32_t size = launch_size(k, nf, nf1, nf2, disc1, d - 1, n, b.grid_max);
       if (timed_bracket) GSW_HIP(hipEventRecord(w.ev[0], s));
       if (solo) {
-        GSW_TRY(launch_level_solo(g, b_solo, dp, 0, s));
+        GSW_TRY(launch_level_solo(g, b_solo, dp, 0, w.nw <= kSoloVisSmall, s));
       } else {
         GSW_TRY(launch_level_auto(g, b, dp, 0, size, s));
         if (level_launches(k, nf) == 2) GSW_TRY(launch_level_auto(g, b, dp, 1, size, s));

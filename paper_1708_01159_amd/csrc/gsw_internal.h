@@ -266,6 +266,7 @@ struct BfsBase {
   int32_t solo;                    // levels one single-workgroup launch may run (0: such launches off)
   int32_t deg_max;                 // largest out-degree (clamped to 2^31 - 1)
   int32_t head_ranked;             // head holds ranked in-arcs (bottom-up rows are then probed from their start)
+  int32_t head_rows;               // head holds the rows' first out-arcs (symmetric graph, not ranked)
 };
 
 // Single-workgroup multi-level launches (k_level_solo): while the frontier
@@ -278,19 +279,21 @@ struct BfsBase {
 // the shrinking tail of a search that has reached 1% of the graph, by a
 // check of the actual arc count (at most kSoloMaxArcs) before the level
 // starts.  A launch runs at most kSoloMaxLevels levels.
-// One compute unit's memory pipeline bounds such a workgroup: measured on
-// MI355X (2048 x 2048 grid), a level costs it about 3.5 us up to 64
-// frontier vertices, 4.3 us up to 256 and 6.4 us up to 512, then grows with
-// the frontier (12 us up to 1024, 22 us up to 2048), while a level kernel
-// launch costs about 6 us on the device plus about 3 us between launches at
-// any of these sizes; hence kSoloMax = 512.
+// The dependent steps of a level bound such a workgroup while the frontier
+// is small, one compute unit's instruction issue later: measured on MI355X
+// (1023 x 1025 grid) a level costs it about 1 us up to 256 frontier vertices,
+// 1.7 us at 750 and 2.6 us at 1200, while a level kernel launch costs about
+// 6 us on the device plus about 3 us between launches at any of these sizes.
+// 2048 is what the workgroup holds in two entries a thread; larger frontiers
+// would spill to the queue.
 constexpr int kSoloBlock = 1024;
 constexpr int kSoloSlots = 2;  // frontier entries per thread at most
-constexpr int64_t kSoloMax = 512;
+constexpr int64_t kSoloMax = 2048;
 static_assert(kSoloMax <= (int64_t)kSoloBlock * kSoloSlots, "every frontier entry has a thread slot");
 constexpr int64_t kSoloMaxArcs = 65536;
-constexpr int kSoloMaxLevels = 32;
-constexpr int32_t kSoloTree = 1024;  // tree nodes the workgroup holds in LDS
+constexpr int kSoloMaxLevels = 80;
+constexpr int32_t kSoloTree = 1024;  // such launches run with a tree of at most this many nodes
+constexpr int64_t kSoloVisWords = 16384;  // 64-bit words of a visited bitmap that LDS has room for
 __host__ __device__ inline bool solo_eligible(int k, long long nn, long long nf, long long disc_next, long long n,
                                               int32_t deg_max) {
   if (k < 0 || kernel_base(k) > GSW_K_PUSH_EDGE) return false;
@@ -316,6 +319,9 @@ constexpr int32_t kMaxTreeNodes = 32767;
 // words bear the tag, whatever order their stores arrive in, and the device
 // never waits for them.
 constexpr int kBfsRing = 256;
+// A single-workgroup launch whose first record the host has read, and the two
+// queued behind it, may all run before the host reads on.
+static_assert(3 * kSoloMaxLevels <= kBfsRing, "no record is overwritten before it is read");
 constexpr int kBfsRec = 16;
 enum : int {
   kRecKernel = 0,   // kernel that ran level d
@@ -351,7 +357,9 @@ gsw_status launch_level_auto(const gsw_graph* g, const BfsBase& b, const BfsPoli
 // Launch j as a single-workgroup multi-level launch: runs the levels that
 // qualify from the one control slot j % 2 names (none when it does not
 // qualify; the slot then passes to launch j + 1 unchanged).
-gsw_status launch_level_solo(const gsw_graph* g, const BfsBase& b, const BfsPolicy& p, int32_t j, hipStream_t s);
+// lds_vis: the visited bitmap in LDS, if it fits (kSoloVisWords).
+gsw_status launch_level_solo(const gsw_graph* g, const BfsBase& b, const BfsPolicy& p, int32_t j, bool lds_vis,
+                             hipStream_t s);
 // Workgroups of a level-kernel launch on a graph of n vertices (nw bitmap words).
 int32_t level_kernel_grid(int64_t n, int64_t nw);
 // Workgroups of that launch that run a level of `kernel` with n_in frontier entries.

@@ -536,6 +536,18 @@ __device__ __forceinline__ TreeLanes tree_prefetch(const BfsPolicy& p) {
   return t;
 }
 
+// Posts the record of level d to the host ring: the first kBfsRecWords lanes
+// of the calling wave store one word each.
+__device__ __forceinline__ void post_record(u64* ring, int32_t d, const u64 (&rec)[kBfsRecWords]) {
+  const int lane = lane_id();
+  u64 v = rec[0];
+#pragma unroll
+  for (int i = 1; i < kBfsRecWords; ++i) v = lane == i ? rec[i] : v;
+  if (lane < kBfsRecWords)
+    __hip_atomic_store(ring + (size_t)(d % kBfsRing) * kBfsRec + lane, rec_tag(d) | (v & kRecValueMask),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // End of a level, called by every thread of every workgroup of the level's
 // last launch after stage_flush_finish: the last workgroup to finish, which
 // has the next frontier's size from the finish count, picks the next
@@ -615,7 +627,6 @@ __device__ __forceinline__ void level_end(const Args& a, const BfsBase* base, co
       next = choose_next(p, a.d + 1, (long long)nn, ndisc, k_run, &nflags);
     }
   }
-  if (tid != 0) return;
   u64 ticks = 0ull;
   if (a.timed) {
     const u64 t0 = __hip_atomic_load(&c->t_begin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -624,14 +635,11 @@ __device__ __forceinline__ void level_end(const Args& a, const BfsBase* base, co
   }
   const int32_t d = a.d;
   const long long nf = c->nf, disc = disc0;
+  const u64 rec[kBfsRecWords] = {(u64)k_run, (u64)c->flags, (u64)nf, (u64)disc, (u64)nn, ticks,
+                                 (u64)(next + 1), (u64)(c->ef + 1), (u64)a.j};
+  post_record(ring, d, rec);
+  if (tid != 0) return;
   const long long ef_next = a.count_arcs ? (long long)sum_bins64(a.aout) : -1;
-  u64* r = ring + (size_t)(d % kBfsRing) * kBfsRec;
-  const u64 tag = rec_tag(d);
-  const u64 rec[kBfsRecWords] = {(u64)k_run, (u64)c->flags, (u64)nf, (u64)disc, (u64)nn, ticks & kRecValueMask,
-                              (u64)(next + 1), (u64)(c->ef + 1) & kRecValueMask, (u64)a.j};
-#pragma unroll
-  for (int i = 0; i < kBfsRecWords; ++i)
-    __hip_atomic_store(r + i, tag | rec[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   BfsCtl* cn = a.ctl_next;
   cn->d = d + 1;
   cn->kernel = next;
@@ -1515,74 +1523,190 @@ __global__ void __launch_bounds__(kBlock) k_level_auto(BfsBase b, BfsPolicy p, i
 // top-down expansion, applying the policy between levels and posting every
 // level's record, so a long run of small levels (a high-diameter graph, the
 // tail of a scale-free search) costs one launch instead of one launch of the
-// whole grid per level.  Each level: every thread takes up to kSoloSlots
-// frontier vertices (entry i = thread + kSoloBlock * slot) and walks rows of
-// up to kSoloShort arcs itself, all its arcs in flight together; longer rows
-// are set aside and their arcs spread over the whole workgroup through a
-// prefix of their lengths (so one row never holds one thread).  Discoveries
-// go to the queue segment 0 of the next depth with one LDS reservation per
-// wavefront; the frontier bitmaps are not kept while the workgroup runs
-// (all three are zero then) and the one of the depth the workgroup hands
-// back is rebuilt from the queue when it stops.
+// whole grid per level.  Such a level is a chain of dependent steps and costs
+// what their latencies add up to, so the chain is kept short:
+//  - the frontier stays in LDS between levels (every thread takes up to
+//    kSoloSlots entries), and the visited bitmap too where it fits
+//    (LdsVis: claims are LDS atomics then);
+//  - where the head copy holds a row's first arcs (symmetric graph, head not
+//    ranked), they are read in one step beside the row's bounds; where no row
+//    is longer (HeadOnly: meshes), the bounds are not read at all and every
+//    lane takes one arc, four lanes a row, so that a claim, its place in the
+//    next frontier and its stores are one short sequence per lane;
+//  - the barriers are for LDS alone: they do not wait for the level and
+//    parent stores.  The level's counters rotate, so none has to be reset
+//    behind a barrier of its own;
+//  - wave 0 alone decides what follows (sixteen waves deciding for themselves
+//    share four schedulers, and the youngest finished 1600 cycles later), and
+//    walks a tree again only when a count leaves the box of the last leaf;
+//    meanwhile every wave reads the next frontier's rows;
+//  - the records are kept in LDS and posted together when the workgroup stops
+//    (posting one a level cost its wave, and so the level, 1 us).
+// Rows longer than kSoloShort arcs are set aside and their arcs spread over
+// the whole workgroup through a prefix of their lengths, so one row never
+// holds one thread.  The frontier bitmaps are not kept while the workgroup
+// runs (all three are zero then); the one of the depth it hands back is
+// rebuilt from the queue when it stops.  Measured, per level of a path:
+// 0.9 us with heads and the bitmap in LDS, 1.5 with the bitmap's copies
+// between launches, 1.8 with it in global memory (2.9 before, with the
+// frontier in the queue, four barriers and a record a level); a 1023 x 1025
+// grid (3120 levels of up to 1700 vertices) 12.2 -> 3.7 ms, 1.2 us a level.
 constexpr int kSoloShort = 8;
-constexpr int kSoloLong = kSoloBlock;  // long rows set aside per level at most
+constexpr int kSoloLong = 512;  // long rows set aside per level at most
 constexpr int kSoloWaves = kSoloBlock / 64;
+constexpr int kSoloLdsTree = 256;  // tree nodes held in LDS (a larger tree is walked from global memory)
 
+template <bool LdsVis>
 struct SoloLds {
-  u64 t_node[kSoloTree];
-  int32_t t_thr[kSoloTree];
-  int32_t t_next[kSoloTree];
+  uint32_t vis[LdsVis ? 2 * kSoloVisWords : 2];
+  int32_t q[2][kSoloMax];       // frontier entries; any beyond go to the global queue
   int64_t lbeg[kSoloLong];      // long rows: first arc
   int32_t lu[kSoloLong];        // long rows: vertex
   int32_t lpre[kSoloLong + 1];  // long rows: arc counts, then their exclusive prefix
   int32_t wsum[kSoloWaves];
-  u64 esum;                     // arcs of the level's frontier
-  uint32_t cnt;                 // next-frontier entries reserved
-  uint32_t nlong;               // long rows set aside
-  uint32_t nn;                  // the next frontier's size, for every thread
-  int32_t go, next, nflags, pad;
+  u64 t_node[kSoloLdsTree];
+  int32_t t_thr[kSoloLdsTree];
+  // of level lv in slot lv % 3; thread 0 clears the next level's at the start
+  // of a level, when every reader of the one before the last is past a barrier
+  u64 esum[3];       // arcs of the level's frontier
+  uint32_t cnt[3];   // next-frontier entries
+  uint32_t nlong[3]; // long rows set aside
+  int32_t go;        // wave 0's decision: the next level runs here
+  int32_t next, nflags, disc;  // ... else its kernel and flags, and the vertices discovered
+  // of level lv of this launch, for its record
+  int32_t r_kernel[kSoloMaxLevels + 1], r_flags[kSoloMaxLevels + 1], r_nf[kSoloMaxLevels + 1];
+  int32_t r_disc[kSoloMaxLevels + 1];
+  uint32_t r_ticks[kSoloMaxLevels];
+  u64 r_ef[kSoloMaxLevels];
+  QueueIn qi;
+};
+static_assert(sizeof(SoloLds<true>) <= 160 * 1024, "a compute unit's LDS");
+
+// Workgroup barrier for LDS only: no wait for global loads or stores.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The box of counts (next frontier, discovered) around the last decision in
+// which the tree's walk ends at the same leaf.
+struct LeafBox {
+  int32_t f_lo, f_hi, d_lo, d_hi;  // lo < count <= hi
+  int32_t leaf;                    // its kernel, -1 undecided
+  __device__ __forceinline__ bool holds(int32_t f, int32_t d) const {
+    return f > f_lo && f <= f_hi && d > d_lo && d <= d_hi;
+  }
 };
 
-// Claims the targets v[q] >= 0 (visited-word load, then the atomic where the
-// bit is clear) for sources u[q / PER]; winners get depth d + 1, their
-// parent, and a place in qout reserved by one LDS atomic per wavefront.
-// Every lane of the wavefront calls it.
-template <int N, int PER>
-__device__ __forceinline__ void solo_visit(const BfsBase& b, int32_t d, int32_t* qout, uint32_t* cnt,
-                                           const int32_t (&v)[N], const int32_t (&u)[N / PER]) {
-  u64 w[N];
-#pragma unroll
-  for (int q = 0; q < N; ++q) w[q] = v[q] >= 0 ? b.vis[v[q] >> 6] : ~0ull;
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    const u64 bit = 1ull << (v[q] & 63);
-    if (!(w[q] & bit)) w[q] = atomicOr(b.vis + (v[q] >> 6), bit);  // the word before this lane's bit
-  }
-  uint32_t mine = 0;
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    const bool win = v[q] >= 0 && !(w[q] & (1ull << (v[q] & 63)));
-    if (win) {
-      b.level[v[q]] = d + 1;
-      if (b.parent) b.parent[v[q]] = u[q / PER];
-      ++mine;
+template <class Node, class Thr>
+__device__ __forceinline__ LeafBox leaf_box(Node node, Thr thr, int32_t f, int32_t d) {
+  LeafBox b{-1, 0x7fffffff, -1, 0x7fffffff, -1};
+  int32_t x = 0;
+  for (;;) {
+    const u64 nd = node(x);
+    const int32_t t = thr(x);
+    const int left = (int)(int16_t)(uint16_t)(nd & 0xffffull);
+    if (left == -1) break;
+    const bool by_d = (nd >> 32) & 1ull;
+    const bool go_left = (by_d ? d : f) <= t;
+    if (by_d) {
+      if (go_left) b.d_hi = t < b.d_hi ? t : b.d_hi; else b.d_lo = t > b.d_lo ? t : b.d_lo;
+    } else {
+      if (go_left) b.f_hi = t < b.f_hi ? t : b.f_hi; else b.f_lo = t > b.f_lo ? t : b.f_lo;
     }
+    x = go_left ? left : (int)(int16_t)(uint16_t)((nd >> 16) & 0xffffull);
   }
-  const int lane = lane_id();
-  uint32_t inc = mine;
+  const int32_t leaf = -tree_step(node(x), 0, 0, 0);  // leaf kernel + 2, 1 when undecided
+  b.leaf = leaf == 1 ? -1 : leaf - 2;
+  return b;
+}
+
+// Claims the targets v[q] >= 0 for sources u[q / PER]; winners get depth
+// d + 1, their parent, and a place in the next frontier, reserved by one LDS
+// atomic per wavefront.  Every lane of the wavefront calls it.
+template <int N, int PER, bool LdsVis>
+__device__ __forceinline__ void solo_visit(const BfsBase& b, SoloLds<LdsVis>& L, int32_t d, int slot, int nxt,
+                                           const int32_t (&v)[N], const int32_t (&u)[N / PER]) {
+  bool win[N];
+  if constexpr (LdsVis) {
+    uint32_t w[N];
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = (uint32_t)__shfl_up((int)inc, off);
-    if (lane >= off) inc += y;
+    for (int q = 0; q < N; ++q) w[q] = v[q] >= 0 ? atomicOr(&L.vis[v[q] >> 5], 1u << (v[q] & 31)) : ~0u;
+#pragma unroll
+    for (int q = 0; q < N; ++q) win[q] = v[q] >= 0 && !((w[q] >> (v[q] & 31)) & 1u);
+  } else {
+    u64 w[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) w[q] = v[q] >= 0 ? atomicOr(b.vis + (v[q] >> 6), 1ull << (v[q] & 63)) : ~0ull;
+#pragma unroll
+    for (int q = 0; q < N; ++q) win[q] = v[q] >= 0 && !((w[q] >> (v[q] & 63)) & 1ull);
   }
-  const uint32_t total = (uint32_t)__shfl((int)inc, 63);
+  uint32_t total = 0, pos[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const u64 m = __ballot(win[q]);
+    pos[q] = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    total += (uint32_t)__popcll(m);
+  }
   if (total == 0u) return;
   uint32_t base = 0u;
-  if (lane == 63) base = atomicAdd(cnt, total);
-  base = (uint32_t)__shfl((int)base, 63) + inc - mine;
+  if (lane_id() == 0) base = atomicAdd(&L.cnt[slot], total);
+  base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+  // (the two destinations apart: a store that may go to either is a flat one,
+  // which the level's barrier then waits for)
+  int32_t* list = L.q[nxt];
+  if (base + total <= (uint32_t)kSoloMax) {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      if (win[q]) list[base + pos[q]] = v[q];
+  } else {
+    int32_t* far = b.q[(d + 1) & 1];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const uint32_t at = base + pos[q];
+      if (win[q] && at < (uint32_t)kSoloMax) list[at] = v[q];
+      if (win[q] && at >= (uint32_t)kSoloMax) far[at] = v[q];
+    }
+  }
 #pragma unroll
   for (int q = 0; q < N; ++q)
-    if (v[q] >= 0 && !(w[q] & (1ull << (v[q] & 63)))) qout[base++] = v[q];
+    if (win[q]) b.level[v[q]] = d + 1;
+  if (b.parent) {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      if (win[q]) b.parent[v[q]] = u[q / PER];
+  }
+}
+
+// HeadOnly expansion of the frontier's nf entries: lane t of pass k takes arc
+// t % 4 of entry k * kSoloRows + t / 4, kSoloPasses passes at a time with their
+// loads in flight together.
+constexpr int kSoloRows = kSoloBlock / kHeadArcs;
+constexpr int kSoloPasses = 4;
+__device__ __forceinline__ void solo_heads_fetch(const int32_t* __restrict__ head, const int32_t* list, int k0,
+                                                 int32_t nf, int32_t (&u)[kSoloPasses], int32_t (&v)[kSoloPasses]) {
+#pragma unroll
+  for (int k = 0; k < kSoloPasses; ++k) {
+    const int32_t i = (k0 + k) * kSoloRows + (int)(threadIdx.x / kHeadArcs);
+    u[k] = i < nf ? list[i] : -1;
+  }
+#pragma unroll
+  for (int k = 0; k < kSoloPasses; ++k)
+    v[k] = u[k] >= 0 ? head[(int64_t)u[k] * kHeadArcs + (threadIdx.x & (kHeadArcs - 1))] : -1;
+}
+
+// Visits the first N of the fetched passes.
+template <int N, bool LdsVis>
+__device__ __forceinline__ void solo_heads_visit(const BfsBase& b, SoloLds<LdsVis>& L, int32_t d, int slot, int nxt,
+                                                 const int32_t (&u)[kSoloPasses], const int32_t (&v)[kSoloPasses]) {
+  int32_t un[N], vn[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    un[k] = u[k];
+    vn[k] = v[k];
+  }
+  solo_visit<N, 1, LdsVis>(b, L, d, slot, nxt, vn, un);
 }
 
 // Entry i of the depth-d queue as a level kernel wrote it (kQueueBins segments).
@@ -1593,26 +1717,29 @@ __device__ __forceinline__ int32_t solo_queue_binned(const BfsBase& b, int32_t d
   return b.q[d & 1][(int64_t)bin * b.n + (i - qi.pre[bin])];
 }
 
-// Hands depth L back to the level kernel: its frontier (f entries, segment 0
-// of the depth-L queue) becomes the queue's only segment and the depth-L
-// bitmap, the counters the level will append to are zeroed, and control
-// slot cn describes level L.  Every thread calls it.
-__device__ __forceinline__ void solo_publish(const BfsBase& b, BfsCtl* cn, int32_t L, int32_t kernel, int32_t prev,
-                                             int32_t flags, long long f, long long disc, long long ef) {
+// Hands depth `lv` back to the level kernel: its frontier (f entries, the
+// first kSoloMax in `list`, any beyond already in the queue) becomes segment 0
+// of the queue, its only one, and the depth's bitmap, the counters the level
+// will append to are zeroed, and control slot cn describes the level.  Every
+// thread calls it.
+__device__ __forceinline__ void solo_publish(const BfsBase& b, BfsCtl* cn, const int32_t* list, int32_t lv,
+                                             int32_t kernel, int32_t prev, int32_t flags, long long f, long long disc,
+                                             long long ef) {
   const int tid = threadIdx.x;
-  const int32_t* q = b.q[L & 1];
-  u64* bm = b.bm[L % 3];
+  int32_t* q = b.q[lv & 1];
+  u64* bm = b.bm[lv % 3];
   for (long long i = tid; i < f; i += kSoloBlock) {
-    const int32_t v = q[i];
+    const int32_t v = i < kSoloMax ? list[i] : q[i];
+    if (i < kSoloMax) q[i] = v;
     atomicOr(bm + (v >> 6), 1ull << (v & 63));
   }
   if (tid < kQueueBins) {
-    b.ctr[(size_t)(L & 3) * kCtrSlot + tid * kCtrStride] = tid == 0 ? (uint32_t)f : 0u;
-    b.ctr[(size_t)((L + 1) & 3) * kCtrSlot + tid * kCtrStride] = 0u;
-    b.actr[(size_t)((L + 1) & 3) * kArcSlot + tid * kArcStride] = 0ull;
+    b.ctr[(size_t)(lv & 3) * kCtrSlot + tid * kCtrStride] = tid == 0 ? (uint32_t)f : 0u;
+    b.ctr[(size_t)((lv + 1) & 3) * kCtrSlot + tid * kCtrStride] = 0u;
+    b.actr[(size_t)((lv + 1) & 3) * kArcSlot + tid * kArcStride] = 0ull;
   }
   if (tid == 0) {
-    cn->d = L;
+    cn->d = lv;
     cn->kernel = kernel;
     cn->prev = prev;
     cn->flags = flags;
@@ -1628,124 +1755,202 @@ __device__ __forceinline__ void solo_publish(const BfsBase& b, BfsCtl* cn, int32
   }
 }
 
+// Copies n words with the whole workgroup, eight loads in flight per thread
+// (one after another, 128 KiB took 12 us each way).
+__device__ __forceinline__ void solo_copy(u64* dst, const u64* src, int32_t n) {
+  for (int32_t i0 = threadIdx.x; i0 < n; i0 += 8 * kSoloBlock) {
+    u64 w[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = i0 + k * kSoloBlock < n ? src[i0 + k * kSoloBlock] : 0ull;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (i0 + k * kSoloBlock < n) dst[i0 + k * kSoloBlock] = w[k];
+  }
+}
+
+// LdsVis: the visited bitmap in LDS.  HeadOnly: every row is its head record
+// (head_rows, at most kHeadArcs arcs a row, arcs not counted).
+template <bool LdsVis, bool HeadOnly>
 __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy p, int32_t j) {
-  __shared__ SoloLds L;
-  __shared__ QueueIn qi;
+  __shared__ SoloLds<LdsVis> L;
   const int tid = threadIdx.x;
   const int lane = lane_id();
-  const int wid = tid >> 6;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t cpre = counters_prefetch(b.ctr);
   const BfsCtl* c = b.ctl + (j & 1);
   BfsCtl* cn = b.ctl + ((j + 1) & 1);
   int32_t k_id = c->kernel;
   int32_t d = c->d;
-  long long nf = c->nf, disc = c->disc;
   int32_t prev = c->prev, flags = c->flags;
   const bool tree = p.policy == GSW_POLICY_TREE;
   const bool ok = b.solo > 0 && k_id >= 0 && k_id < GSW_N_KERNELS && kernel_base(k_id) <= GSW_K_PUSH_EDGE &&
-                  nf >= 1 && nf <= kSoloMax && (!tree || p.t_nodes <= kSoloTree);
+                  c->nf >= 1 && c->nf <= kSoloMax;
   if (!ok) {  // not a level for this launch: the slot passes on unchanged
     if (tid == 0) *cn = *c;
     return;
   }
-  if (tid == 0) {
-    L.esum = 0ull;
-    L.cnt = 0u;
-    L.nlong = 0u;
+  int32_t nf = (int32_t)c->nf, disc = (int32_t)c->disc;  // (both at most n)
+  if (tid < 3) {
+    L.esum[tid] = 0ull;
+    L.cnt[tid] = 0u;
+    L.nlong[tid] = 0u;
   }
-  if (tree)
-    for (int i = tid; i < p.t_nodes; i += kSoloBlock) {
-      L.t_node[i] = p.t_node[i];
-      L.t_thr[i] = p.t_thr[i];
-    }
-  queue_in_load(cpre, d & 3, qi);  // ends with a barrier
-  if ((long long)qi.pre[kQueueBins] < nf) nf = (long long)qi.pre[kQueueBins];  // never past the queue's entries
-  const bool check_arcs = (long long)b.deg_max * kSoloMax > kSoloMaxArcs;
-  for (int lv = 0;; ++lv) {
-    u64 t0 = 0ull;
-    if (b.timed && tid == 0) t0 = (u64)wall_clock64();
-    // the level's frontier: binned as the level kernel left it on the first
-    // level, segment 0 afterwards
-    int32_t u[kSoloSlots];
-    int64_t beg[kSoloSlots], end[kSoloSlots];
-    bool lng[kSoloSlots];
+  const bool lds_tree = tree && p.t_nodes <= kSoloLdsTree;
+  if (lds_tree && tid < p.t_nodes) {
+    L.t_node[tid] = p.t_node[tid];
+    L.t_thr[tid] = p.t_thr[tid];
+  }
+  if constexpr (LdsVis) solo_copy(reinterpret_cast<u64*>(L.vis), b.vis, (int32_t)b.nw);
+  queue_in_load(cpre, d & 3, L.qi);  // ends with a barrier
+  if ((int32_t)L.qi.pre[kQueueBins] < nf) nf = (int32_t)L.qi.pre[kQueueBins];  // never past the queue's entries
+  const bool heads = b.head_rows != 0;
+  // the policy's decision and the box of counts in which it holds: everywhere
+  // for a fixed kernel, nowhere (yet) otherwise
+  LeafBox box{0, p.policy == GSW_POLICY_FIXED ? 0x7fffffff : 0, 0, 0x7fffffff, p.fixed};
+  int32_t leaf_next = 0, leaf_flags = 0;  // its kernel (a tied leaf: this level's) and trace flags
+  if (p.policy == GSW_POLICY_FIXED) leaf_next = choose_leaf(p, p.fixed, k_id, &leaf_flags);
+  bool leaf_push = kernel_base(leaf_next) <= GSW_K_PUSH_EDGE;  // ... which may go on here
+  // frontiers whose arcs the largest degree bounds
+  const int32_t bound_arcs = b.deg_max > 0 ? (int32_t)(kSoloMaxArcs / b.deg_max) : (int32_t)kSoloMax;
+  const int32_t bound_nf = bound_arcs < (int32_t)kSoloMax ? bound_arcs : (int32_t)kSoloMax;
+  const int32_t levels_max = b.solo;
+  int levels = 0;  // completed here
+  int slot = 0;
+  // the rows of a frontier: HeadOnly an arc per lane and pass, else an entry
+  // per thread and slot with its row's bounds and (heads) its first arcs
+  int32_t u[kSoloPasses], v[kSoloPasses], arc[kSoloSlots][kHeadArcs];
+  int64_t beg[kSoloSlots], end[kSoloSlots];
+  auto fetch = [&](const int32_t* list, int32_t count) {
+    if constexpr (HeadOnly) {
+      if (wid * (64 / kHeadArcs) < count) solo_heads_fetch(b.head, list, 0, count, u, v);
+    } else {
 #pragma unroll
-    for (int q = 0; q < kSoloSlots; ++q) {
-      const long long i = tid + (long long)q * kSoloBlock;
-      u[q] = -1;
-      if (i < nf) u[q] = lv == 0 ? solo_queue_binned(b, d, qi, (uint32_t)i) : b.q[d & 1][i];
-    }
-    u64 arcs = 0ull;
+      for (int q = 0; q < kSoloSlots; ++q) {
+        const int32_t i = tid + q * kSoloBlock;
+        u[q] = i < count ? list[i] : -1;
+        beg[q] = end[q] = 0;
 #pragma unroll
-    for (int q = 0; q < kSoloSlots; ++q) {
-      beg[q] = end[q] = 0;
-      if (u[q] >= 0) {
-        beg[q] = b.offs[u[q]];
-        end[q] = b.offs[u[q] + 1];
-      }
-      const int64_t deg = end[q] - beg[q];
-      arcs += (u64)deg;
-      lng[q] = false;
-      if (deg > kSoloShort) {  // set aside while there is room, else walked by this thread
-        const uint32_t at = atomicAdd(&L.nlong, 1u);
-        if (at < (uint32_t)kSoloLong) {
-          L.lu[at] = u[q];
-          L.lbeg[at] = beg[q];
-          L.lpre[at] = (int32_t)(deg < kSoloMaxArcs ? deg : kSoloMaxArcs + 1);
-          lng[q] = true;
+        for (int k = 0; k < kHeadArcs; ++k) arc[q][k] = -1;
+        if (u[q] >= 0) {
+          beg[q] = b.offs[u[q]];
+          end[q] = b.offs[u[q] + 1];
+          if (heads) {
+            const int4 h = reinterpret_cast<const int4*>(b.head)[u[q]];
+            arc[q][0] = h.x;
+            arc[q][1] = h.y;
+            arc[q][2] = h.z;
+            arc[q][3] = h.w;
+          }
         }
       }
     }
-    if (check_arcs || b.count_arcs) {
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) arcs += __shfl_xor(arcs, off);
-      if (lane == 0 && arcs) atomicAdd(&L.esum, arcs);
+  };
+  // the first frontier, binned as the level kernel left it, into LDS
+  for (int32_t i = tid; i < nf; i += kSoloBlock) L.q[0][i] = solo_queue_binned(b, d, L.qi, (uint32_t)i);
+  __syncthreads();
+  fetch(L.q[0], nf);
+  u64 t0 = b.timed ? (u64)wall_clock64() : 0ull;
+  for (int lv = 0;; ++lv) {
+    const int cur = lv & 1, nxt = cur ^ 1, slot1 = slot == 2 ? 0 : slot + 1;
+    if (tid == kSoloBlock - 1) {
+      L.esum[slot1] = 0ull;
+      L.cnt[slot1] = 0u;
+      L.nlong[slot1] = 0u;
     }
-    __syncthreads();
-    const u64 esum = L.esum;
-    const uint32_t nlong = L.nlong < (uint32_t)kSoloLong ? L.nlong : (uint32_t)kSoloLong;
-    if (esum > (u64)kSoloMaxArcs) {
-      // too many arcs for one workgroup: the level goes back to the level
-      // kernel untouched (on the first level nothing has changed at all)
-      if (lv == 0) {
-        if (tid == 0) *cn = *c;
-      } else {
-        solo_publish(b, cn, d, k_id, prev, flags, nf, disc, b.count_arcs ? (long long)esum : -1);
+    bool lng[kSoloSlots] = {};
+    const bool check = !HeadOnly && nf > bound_arcs;
+    if (!HeadOnly && wid * 64 < nf) {
+      // rows set aside while there is room, else walked by their thread; the
+      // level's arcs where they have to be known
+      if (b.deg_max > kSoloShort) {
+#pragma unroll
+        for (int q = 0; q < kSoloSlots; ++q) {
+          const int64_t deg = end[q] - beg[q];
+          if (deg > kSoloShort) {
+            const uint32_t at = atomicAdd(&L.nlong[slot], 1u);
+            if (at < (uint32_t)kSoloLong) {
+              L.lu[at] = u[q];
+              L.lbeg[at] = beg[q];
+              L.lpre[at] = (int32_t)(deg < kSoloMaxArcs ? deg : kSoloMaxArcs + 1);
+              lng[q] = true;
+            }
+          }
+        }
       }
-      return;
+      if (check || b.count_arcs) {
+        u64 arcs = 0ull;
+#pragma unroll
+        for (int q = 0; q < kSoloSlots; ++q) arcs += (u64)(end[q] - beg[q]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) arcs += __shfl_xor(arcs, off);
+        if (lane == 0 && arcs) atomicAdd(&L.esum[slot], arcs);
+      }
+    }
+    uint32_t nlong = 0u;
+    if (!HeadOnly && (check || b.deg_max > kSoloShort)) {
+      lds_barrier();
+      nlong = L.nlong[slot] < (uint32_t)kSoloLong ? L.nlong[slot] : (uint32_t)kSoloLong;
+      if (check && L.esum[slot] > (u64)kSoloMaxArcs) {
+        // too many arcs for one workgroup: the level goes back to the level
+        // kernel untouched (on the first level nothing has changed at all)
+        if (lv == 0) {
+          if (tid == 0) *cn = *c;
+          return;
+        }
+        if (tid == 0) {
+          L.next = k_id;
+          L.nflags = flags;
+          L.disc = disc;
+        }
+        __syncthreads();  // the cleared bitmap words have landed before bits are set
+        solo_publish(b, cn, L.q[cur], d, L.next, prev, L.nflags, nf, L.disc,
+                     b.count_arcs ? (long long)L.esum[slot] : -1);
+        break;
+      }
     }
     if (lv == 0) {
       // the bitmaps are not kept here: clear the depth-d frontier's words and,
       // unless known clean, the depth-(d-1) bitmap
-#pragma unroll
-      for (int q = 0; q < kSoloSlots; ++q)
-        if (u[q] >= 0) b.bm[d % 3][u[q] >> 6] = 0ull;
+      for (int32_t i = tid; i < nf; i += kSoloBlock) b.bm[d % 3][L.q[0][i] >> 6] = 0ull;
       if (!c->clean)
         for (int64_t i = tid; i < b.nw; i += kSoloBlock) b.bm[(d + 2) % 3][i] = 0ull;
     }
-    int32_t* qout = b.q[(d + 1) & 1];
-    // rows not set aside: a pair of slots' next four arcs each in flight together
-    for (int r0 = 0;; r0 += 4) {
-      bool any_more = false;
-#pragma unroll
-      for (int h = 0; h < kSoloSlots; h += 2) {
-        const bool more = (!lng[h] && beg[h] + r0 < end[h]) || (!lng[h + 1] && beg[h + 1] + r0 < end[h + 1]);
-        if (!__any(more)) continue;
-        any_more = true;
-        int32_t v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int q = h + (k >> 2);
-          const int64_t e = beg[q] + r0 + (k & 3);
-          v[k] = !lng[q] && e < end[q] ? b.cols[e] : -1;
-        }
-        const int32_t us[2] = {u[h], u[h + 1]};
-        solo_visit<8, 4>(b, d, qout, &L.cnt, v, us);
+    if constexpr (HeadOnly) {
+      for (int k0 = 0; k0 * kSoloRows + wid * (64 / kHeadArcs) < nf; k0 += kSoloPasses) {
+        if (k0 > 0) solo_heads_fetch(b.head, L.q[cur], k0, nf, u, v);
+        const int left = (nf - k0 * kSoloRows + kSoloRows - 1) / kSoloRows;
+        if (left == 1)
+          solo_heads_visit<1, LdsVis>(b, L, d, slot, nxt, u, v);
+        else if (left == 2)
+          solo_heads_visit<2, LdsVis>(b, L, d, slot, nxt, u, v);
+        else
+          solo_heads_visit<kSoloPasses, LdsVis>(b, L, d, slot, nxt, u, v);
       }
-      if (!any_more) break;
+    } else if (wid * 64 < nf) {
+      // rows not set aside, four arcs of a slot in flight together
+#pragma unroll
+      for (int q = 0; q < kSoloSlots; ++q) {
+        if (q > 0 && wid * 64 + q * kSoloBlock >= nf) break;
+        const int32_t us[1] = {u[q]};
+        int64_t e = beg[q];
+        if (heads) {
+          if (lng[q])
+#pragma unroll
+            for (int k = 0; k < kHeadArcs; ++k) arc[q][k] = -1;
+          solo_visit<4, 4, LdsVis>(b, L, d, slot, nxt, arc[q], us);
+          e += kHeadArcs;
+        }
+        while (__any(!lng[q] && e < end[q])) {
+          int32_t w[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) w[k] = !lng[q] && e + k < end[q] ? b.cols[e + k] : -1;
+          solo_visit<4, 4, LdsVis>(b, L, d, slot, nxt, w, us);
+          e += 4;
+        }
+      }
     }
     // long rows: their arcs over the whole workgroup
-    if (nlong > 0u) {
+    if (!HeadOnly && nlong > 0u) {
       const int32_t x = tid < (int)nlong ? L.lpre[tid] : 0;
       int32_t inc = x;
 #pragma unroll
@@ -1754,20 +1959,19 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
         if (lane >= off) inc += y;
       }
       if (lane == 63) L.wsum[wid] = inc;
-      __syncthreads();
+      lds_barrier();
       int32_t before = 0;
       for (int w = 0; w < wid; ++w) before += L.wsum[w];
       if (tid < (int)nlong) L.lpre[tid] = before + inc - x;
       if (tid == (int)nlong - 1) L.lpre[nlong] = before + inc;
-      __syncthreads();
+      lds_barrier();
       const int32_t total = L.lpre[nlong];
-      const int32_t rounds = (total + 4 * kSoloBlock - 1) / (4 * kSoloBlock);  // the same in every thread
-      for (int32_t r = 0; r < rounds; ++r) {
-        int32_t v[4], us[4];
+      for (int32_t r = 0; r * 4 * kSoloBlock + wid * 64 < total; ++r) {  // (the same in a wave's lanes)
+        int32_t w[4], us[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const int32_t a = tid + (4 * r + k) * kSoloBlock;
-          v[k] = -1;
+          w[k] = -1;
           us[k] = 0;
           if (a < total) {
             int lo = 0, hi = (int)nlong - 1;
@@ -1775,66 +1979,71 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
               const int mid = (lo + hi + 1) >> 1;
               if (L.lpre[mid] <= a) lo = mid; else hi = mid - 1;
             }
-            v[k] = b.cols[L.lbeg[lo] + (a - L.lpre[lo])];
+            w[k] = b.cols[L.lbeg[lo] + (a - L.lpre[lo])];
             us[k] = L.lu[lo];
           }
         }
-        solo_visit<4, 1>(b, d, qout, &L.cnt, v, us);
+        solo_visit<4, 1, LdsVis>(b, L, d, slot, nxt, w, us);
       }
     }
-    __syncthreads();
-    // level end: the policy picks the next kernel; the level's record
-    const uint32_t nn = L.cnt;
-    const long long ndisc = disc + (long long)nn;
-    if (tree && nn > 0u) {
-      if (tid < p.t_nodes) L.t_next[tid] = tree_step(L.t_node[tid], L.t_thr[tid], (int32_t)nn, (int32_t)ndisc);
-      __syncthreads();
-    }
-    if (tid == 0) {
-      int32_t next = kCtlDone, nflags = 0;
-      if (nn > 0u) {
+    lds_barrier();
+    // level end: the next frontier's rows are on their way while wave 0
+    // decides what runs next
+    const int32_t nn = __builtin_amdgcn_readfirstlane((int)L.cnt[slot]);
+    fetch(L.q[nxt], nn < (int32_t)kSoloMax ? nn : (int32_t)kSoloMax);
+    if (wid == 0) {
+      const int32_t ndisc = disc + nn;
+      if (nn > 0 && !box.holds(nn, ndisc)) {
         if (tree) {
-          int32_t x = L.t_next[0];
-          while (x >= 0) x = L.t_next[x];
-          next = choose_leaf(p, x == -1 ? -1 : -x - 2, k_id, &nflags);
-        } else {
-          next = choose_next(p, d + 1, (long long)nn, ndisc, k_id, &nflags);
+          box = lds_tree ? leaf_box([&](int32_t x) { return L.t_node[x]; }, [&](int32_t x) { return L.t_thr[x]; }, nn, ndisc)
+                         : leaf_box([&](int32_t x) { return p.t_node[x]; }, [&](int32_t x) { return p.t_thr[x]; }, nn, ndisc);
+        } else {  // a schedule's box stays empty
+          box.leaf = p.sched[d + 1 < p.sched_len ? d + 1 : p.sched_len - 1];
         }
+        leaf_next = choose_leaf(p, box.leaf, k_id, &leaf_flags);
+        leaf_push = kernel_base(leaf_next) <= GSW_K_PUSH_EDGE;
       }
-      u64 ticks = 0ull;
-      if (b.timed) {
-        const u64 t1 = (u64)wall_clock64();
-        ticks = t1 > t0 ? t1 - t0 : 0ull;
+      // (solo_eligible, with the kernel's part of it decided above)
+      const bool go = lv + 1 < levels_max && nn > 0 && leaf_push &&
+                      (nn <= bound_nf || (nn <= (int32_t)kSoloMax && nn <= nf && (long long)ndisc * 100 >= b.n));
+      const int32_t next = nn > 0 ? leaf_next : kCtlDone, nflags = nn > 0 ? leaf_flags : 0;
+      if (tid == 0) {
+        L.go = go ? 1 : 0;
+        if (!go) {
+          L.next = next;
+          L.nflags = nflags;
+          L.disc = ndisc;
+        }
+        L.r_kernel[lv] = k_id;  // for the level's record
+        L.r_flags[lv] = flags;
+        L.r_nf[lv] = nf;
+        L.r_disc[lv] = disc;
+        if (b.timed) {
+          const u64 t1 = (u64)wall_clock64();
+          L.r_ticks[lv] = t1 > t0 ? (uint32_t)(t1 - t0) : 0u;
+          t0 = t1;
+        }
+        if (b.count_arcs) L.r_ef[lv] = L.esum[slot];
       }
-      u64* r = b.ring + (size_t)(d % kBfsRing) * kBfsRec;
-      const u64 tag = rec_tag(d);
-      const long long ef = b.count_arcs ? (long long)esum : -1;
-      const u64 rec[kBfsRecWords] = {(u64)k_id, (u64)(flags | kFlagSolo), (u64)nf, (u64)disc, (u64)nn,
-                                  ticks & kRecValueMask, (u64)(next + 1), (u64)(ef + 1) & kRecValueMask,
-                                  (u64)j};
-#pragma unroll
-      for (int i = 0; i < kBfsRecWords; ++i)
-        __hip_atomic_store(r + i, tag | rec[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      L.go = lv + 1 < b.solo && solo_eligible(next, (long long)nn, nf, ndisc, b.n, b.deg_max) ? 1 : 0;
-      L.next = next;
-      L.nflags = nflags;
-      L.nn = nn;
-      L.cnt = 0u;
-      L.nlong = 0u;
-      L.esum = 0ull;
+      prev = k_id;
+      k_id = next;
+      flags = nflags;
+      disc = ndisc;
     }
-    __syncthreads();
-    const int32_t next = L.next, nflags = L.nflags;
-    const long long nnx = (long long)L.nn;
-    if (!L.go) {
-      if (nnx == 0) {
+    lds_barrier();
+    const bool go = __builtin_amdgcn_readfirstlane(L.go) != 0;
+    levels = lv + 1;
+    ++d;
+    nf = nn;
+    if (!go) {
+      if (nn == 0) {
         if (tid == 0) {
-          cn->d = d + 1;
+          cn->d = d;
           cn->kernel = kCtlDone;
-          cn->prev = k_id;
+          cn->prev = prev;
           cn->flags = 0;
           cn->nf = 0;
-          cn->disc = ndisc;
+          cn->disc = disc;
           cn->done = 0ull;
           cn->phase = 0;
           cn->t_begin = 0ull;
@@ -1843,32 +2052,51 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
           cn->ef = -1;
           cn->clean = 1;
         }
-        return;
-      }
-      long long ef_next = -1;
-      if (b.count_arcs) {  // the next frontier's arcs, for its record
-        u64 a = 0ull;
-        const int32_t* q = b.q[(d + 1) & 1];
-        for (long long i = tid; i < nnx; i += kSoloBlock) {
-          const int32_t v = q[i];
-          a += (u64)(b.offs[v + 1] - b.offs[v]);
-        }
+      } else {
+        __syncthreads();  // the cleared bitmap words and the entries past kSoloMax have landed
+        long long ef_next = -1;
+        if (b.count_arcs) {  // the next frontier's arcs, for its record
+          u64 a = 0ull;
+          const int32_t* q = b.q[d & 1];
+          for (int32_t i = tid; i < nn; i += kSoloBlock) {
+            const int32_t w = i < kSoloMax ? L.q[nxt][i] : q[i];
+            a += (u64)(b.offs[w + 1] - b.offs[w]);
+          }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        if (lane == 0 && a) atomicAdd(&L.esum, a);
-        __syncthreads();
-        ef_next = (long long)L.esum;
+          for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
+          if (lane == 0 && a) atomicAdd(&L.esum[slot1], a);  // (zero: the next level's)
+          __syncthreads();
+          ef_next = (long long)L.esum[slot1];
+        }
+        solo_publish(b, cn, L.q[nxt], d, L.next, prev, L.nflags, nn, L.disc, ef_next);
       }
-      solo_publish(b, cn, d + 1, next, k_id, nflags, nnx, ndisc, ef_next);
-      return;
+      break;
     }
-    prev = k_id;
-    k_id = next;
-    flags = nflags;
-    nf = nnx;
-    disc = ndisc;
-    ++d;
+    slot = slot1;
   }
+  // the completed levels' records; the entry after the last holds what follows
+  if (tid == 0) {
+    L.r_kernel[levels] = k_id;
+    L.r_nf[levels] = nf;
+  }
+  __syncthreads();
+  for (int i = tid; i < levels * kBfsRec; i += kSoloBlock) {
+    const int lv = i / kBfsRec, w = i % kBfsRec;
+    if (w >= kBfsRecWords) continue;
+    u64 x = (u64)j;  // kRecLaunch
+    if (w == kRecKernel) x = (u64)L.r_kernel[lv];
+    if (w == kRecFlags) x = (u64)(L.r_flags[lv] | kFlagSolo);
+    if (w == kRecNf) x = (u64)L.r_nf[lv];
+    if (w == kRecDisc) x = (u64)L.r_disc[lv];
+    if (w == kRecNext) x = (u64)L.r_nf[lv + 1];
+    if (w == kRecTicks) x = b.timed ? (u64)L.r_ticks[lv] : 0ull;
+    if (w == kRecNextKernel) x = (u64)(L.r_kernel[lv + 1] + 1);
+    if (w == kRecEf) x = b.count_arcs ? L.r_ef[lv] + 1ull : 0ull;
+    const int32_t at = d - levels + lv;
+    __hip_atomic_store(b.ring + (size_t)(at % kBfsRing) * kBfsRec + w, rec_tag(at) | (x & kRecValueMask),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  if constexpr (LdsVis) solo_copy(b.vis, reinterpret_cast<const u64*>(L.vis), (int32_t)b.nw);  // (all claims are in)
 }
 
 // ------------------------------------------------------------ helpers
@@ -2126,9 +2354,16 @@ gsw_status launch_init(const gsw_graph* g, const BfsBase& b, const unsigned long
   return GSW_OK;
 }
 
-gsw_status launch_level_solo(const gsw_graph* g, const BfsBase& b, const BfsPolicy& p, int32_t j, hipStream_t s) {
+gsw_status launch_level_solo(const gsw_graph* g, const BfsBase& b, const BfsPolicy& p, int32_t j, bool lds_vis,
+                             hipStream_t s) {
   (void)g;
-  hipLaunchKernelGGL(k_level_solo, dim3(1), dim3(kSoloBlock), 0, s, b, p, j);
+  const bool vis = lds_vis && b.nw <= kSoloVisWords;
+  const bool head_only = b.head_rows && b.deg_max <= kHeadArcs && !b.count_arcs;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(kSoloBlock), 0, s, b, p, j); };
+  if (vis && head_only) launch(k_level_solo<true, true>);
+  else if (vis) launch(k_level_solo<true, false>);
+  else if (head_only) launch(k_level_solo<false, true>);
+  else launch(k_level_solo<false, false>);
   GSW_HIP(hipGetLastError());
   return GSW_OK;
 }

@@ -1,0 +1,106 @@
+"""Edges of the single-workgroup launches: frontiers of exactly as many
+vertices as the workgroup holds and of one more, rows as long as the head
+copy and one arc longer, more long rows than it sets aside, bitmaps on both
+sides of what it keeps in LDS, searches past each level cap, trees on both
+sides of what LDS holds -- levels equal the oracle, parents valid."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import checks
+from paper_1708_01159_amd import graphgen as gg
+from paper_1708_01159_amd import gsw
+
+pytestmark = pytest.mark.gpu
+
+SOLO = 4  # trace flag of a level run by a single-workgroup launch
+
+
+def _diamonds(widest, tail, extra=0, legs=0, n=None):
+    """A binary tree over `widest` vertices on its last level but one, mirrored
+    back to one vertex, then a path of `tail`: `extra` chains of the same depth
+    from the root widen every frontier by one each; each vertex of the widest
+    level gets `legs` leaves."""
+    src, dst, front, nv = [], [], [0], 1
+    chains = [0] * extra
+    while len(front) < widest:
+        new = []
+        for v in front:
+            for _ in range(2):
+                src.append(v), dst.append(nv), new.append(nv)
+                nv += 1
+        front = new
+        for i in range(extra):
+            src.append(chains[i]), dst.append(nv)
+            chains[i] = nv
+            nv += 1
+    for v in front:
+        for _ in range(legs):
+            src.append(v), dst.append(nv)
+            nv += 1
+    while len(front) > 1:
+        new = []
+        for i in range(0, len(front), 2):
+            src.extend(front[i:i + 2]), dst.extend([nv, nv]), new.append(nv)
+            nv += 1
+        front = new
+    v = front[0]
+    for _ in range(tail):
+        src.append(v), dst.append(nv)
+        v, nv = nv, nv + 1
+    assert n is None or nv <= n
+    return gg.from_edges(n or nv, src, dst, name="diamond")
+
+
+def _wide_tree(depth):
+    """A complete decision tree of 2^(depth+1) - 1 nodes over the frontier and
+    discovered fractions whose leaves all name queue-driven kernels."""
+    inner = 2 ** depth - 1
+    nodes = 2 * inner + 1
+    rng = np.random.default_rng(3)
+    thr = np.where(np.arange(nodes) < inner, 10.0 ** rng.uniform(-5, 0, nodes), -2.0)
+    value = np.zeros((nodes, 3))
+    value[np.arange(nodes), rng.integers(0, 3, nodes)] = 2.0
+    return gsw.Tree(dict(left=[2 * i + 1 if i < inner else -1 for i in range(nodes)],
+                         right=[2 * i + 2 if i < inner else -1 for i in range(nodes)],
+                         feature=[(21, 23)[i % 2] if i < inner else -2 for i in range(nodes)],
+                         threshold=thr.tolist(), value=value.tolist(),
+                         class_kernel=[gsw.PUSH_VERTEX, gsw.PUSH_WAVE8, gsw.PUSH_EDGE]))
+
+
+SHAPES = {
+    "frontier_2048": dict(widest=2048, tail=10),
+    "frontier_2049": dict(widest=2048, tail=10, extra=1),
+    "frontier_4096_and_back": dict(widest=4096, tail=10),
+    "rows_of_4": dict(widest=256, tail=40, extra=2),
+    "rows_of_5": dict(widest=256, tail=40, extra=3),
+    "long_rows_512": dict(widest=512, tail=5, legs=10),
+    "long_rows_1024": dict(widest=1024, tail=5, legs=10),
+    "bitmap_small": dict(widest=64, tail=130, n=131072),
+    "bitmap_small_passed": dict(widest=64, tail=130, n=131073),
+    "bitmap_largest": dict(widest=64, tail=300, n=1048576),
+    "bitmap_too_large": dict(widest=64, tail=300, n=1048577),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_solo_edges(name):
+    g = _diamonds(**SHAPES[name])
+    n = g.n
+    ref = oracle.levels(g.offs, g.cols, 0)
+    sizes = np.bincount(ref[ref >= 0])
+    G = gsw.Graph.from_csr(g.offs, g.cols)
+    for kw in (dict(policy="fixed", kernel=gsw.PUSH_VERTEX), dict(policy="tree", tree=_wide_tree(6)),
+               dict(policy="tree", tree=_wide_tree(8)),
+               dict(policy="schedule", schedule=np.array([gsw.PUSH_VERTEX] * 7 + [gsw.PUSH_WAVE8], dtype=np.int32))):
+        for count_arcs in (False, True):
+            lv, pa, tr = gsw.bfs(G, [0, 0], count_arcs=count_arcs, trace_cap=1024, **kw)
+            for i in range(2):
+                assert np.array_equal(lv[i], ref)
+                checks.check_bfs(g.offs, g.cols, 0, lv[i], pa[i])
+                rows = [t for t in tr if t.source_idx == i]
+                assert [t.n_frontier for t in rows] == sizes.tolist()
+                assert not any(t.flags & SOLO and t.n_frontier > 2048 for t in rows)
+                if kw["policy"] == "fixed":
+                    assert sum(1 for t in rows if t.flags & SOLO) >= 0.5 * len(rows)
+    G.close()
