@@ -53,7 +53,11 @@ constexpr int kScanItems = 4;                    // push_edge: entries per threa
 constexpr int kScanTile = kBlock * kScanItems;   // entries per scan block
 constexpr int kEdgeChunk = 1024;                 // push_edge: arcs per chunk (4 per lane)
 constexpr int kEdgeWin = 512;                    // push_edge: queue entries a chunk stages in LDS
-constexpr int kPullEager = 8;                    // pull: neighbours probed per lane up front
+constexpr int kPullEager = 4;                    // pull: arcs of a row in flight per lane
+constexpr int kPullGroup = 4;                    // pull: lanes per row past its head arcs
+constexpr int kPullRows = 64 / kPullGroup;       // ... and rows of a wave at a time
+constexpr int kPullMany = 24;                    // pull: with more rows than this to go on, lanes walk their own
+constexpr int32_t kPullMid = 256;                // pull: longer rows are finished by the whole wave
 constexpr int kPullChunk = 8;                    // pull: visited words (512 vertices) per wave step
 constexpr int kTreeLaneNodes = 4;                // level end: tree nodes per lane of one wave (256)
 
@@ -537,12 +541,20 @@ __device__ __forceinline__ TreeLanes tree_prefetch(const BfsPolicy& p) {
 }
 
 // Posts the record of level d to the host ring: the first kBfsRecWords lanes
-// of the calling wave store one word each.
-__device__ __forceinline__ void post_record(u64* ring, int32_t d, const u64 (&rec)[kBfsRecWords]) {
+// of the calling wave store one word each, in the order of the kRec indices.
+// (Values, not an array: a lane-indexed array would go to scratch memory.)
+__device__ __forceinline__ void post_record(u64* ring, int32_t d, u64 r0, u64 r1, u64 r2, u64 r3, u64 r4, u64 r5,
+                                            u64 r6, u64 r7, u64 r8) {
+  static_assert(kBfsRecWords == 9, "one value per word");
   const int lane = lane_id();
-  u64 v = rec[0];
-#pragma unroll
-  for (int i = 1; i < kBfsRecWords; ++i) v = lane == i ? rec[i] : v;
+  u64 v = lane == 1 ? r1 : r0;
+  v = lane == 2 ? r2 : v;
+  v = lane == 3 ? r3 : v;
+  v = lane == 4 ? r4 : v;
+  v = lane == 5 ? r5 : v;
+  v = lane == 6 ? r6 : v;
+  v = lane == 7 ? r7 : v;
+  v = lane == 8 ? r8 : v;
   if (lane < kBfsRecWords)
     __hip_atomic_store(ring + (size_t)(d % kBfsRing) * kBfsRec + lane, rec_tag(d) | (v & kRecValueMask),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -635,9 +647,8 @@ __device__ __forceinline__ void level_end(const Args& a, const BfsBase* base, co
   }
   const int32_t d = a.d;
   const long long nf = c->nf, disc = disc0;
-  const u64 rec[kBfsRecWords] = {(u64)k_run, (u64)c->flags, (u64)nf, (u64)disc, (u64)nn, ticks,
-                                 (u64)(next + 1), (u64)(c->ef + 1), (u64)a.j};
-  post_record(ring, d, rec);
+  post_record(ring, d, (u64)k_run, (u64)c->flags, (u64)nf, (u64)disc, (u64)nn, ticks, (u64)(next + 1),
+              (u64)(c->ef + 1), (u64)a.j);
   if (tid != 0) return;
   const long long ef_next = a.count_arcs ? (long long)sum_bins64(a.aout) : -1;
   BfsCtl* cn = a.ctl_next;
@@ -1159,23 +1170,30 @@ __device__ __forceinline__ bool body_edge_fused(Args& a, Stage& st, const QueueI
 }
 
 // ------------------------------------------ pull_bitmap (wave / 512 vertices)
-// A wave takes kPullChunk visited words (512 vertices) at a time and puts
-// their unvisited vertices on its lanes, 64 per round, in vertex order: a
-// level with few unvisited vertices costs one short round per 512 vertices
-// instead of one dependent load chain per 64.  Each lane looks for an
-// in-neighbour of its vertex (a u with an arc u -> v; on a symmetric graph
-// any neighbour) in the frontier bitmap, in row order, and stops at the
-// first one (Section III-A, vertex pull).  Phase 1: every lane probes the
-// first kHeadArcs neighbours of its row from the dense head copy (the lanes'
-// records are consecutive, so most vertices, which find a frontier
-// neighbour among their first few, never touch their CSR row), then, if
-// still unresolved, the next kPullEager with independent loads (many misses
-// in flight instead of one dependent chain).  Phase 2: rows that are longer
-// and still unresolved are scanned by the whole wavefront, 64 neighbours per
-// step, one row at a time -- a high-degree row does not stall its wave for
-// deg(v) dependent steps.  Discoveries are ORed into the wave's own LDS copy
-// of its words' next-frontier bits; every word of the depth-(d+1) bitmap is
-// written.
+// A wave takes kPullChunk visited words (512 vertices; fewer where the graph
+// would leave waves idle) at a time and puts their unvisited vertices on its
+// lanes, two per lane and round, in vertex order: a level with few unvisited
+// vertices costs one short round per chunk instead of one dependent load
+// chain per 64.  Each lane looks for an in-neighbour of its vertex (a u with
+// an arc u -> v; on a symmetric graph any neighbour) in the frontier bitmap,
+// in row order, and stops at the first one (Section III-A, vertex pull).
+// Phase 1: every lane probes the first kHeadArcs neighbours of its row from
+// the dense head copy (the lanes' records are consecutive, so most vertices,
+// which find a frontier neighbour among their first few, never touch their
+// CSR row).  Phase 2: rows that go on unresolved.  While many do, each lane
+// walks its own row; fewer rows are dealt out to groups of kPullGroup lanes,
+// since the lanes that are done would otherwise wait for the longest row of
+// the wave, and what is left of rows beyond kPullMid arcs is scanned by the
+// whole wavefront, one row at a time.  Discoveries are ORed into the wave's
+// own LDS copy of its words' next-frontier bits; every word of the
+// depth-(d+1) bitmap is written.
+// Bound by the gathers into the bitmap and the chain of dependent loads per
+// round; the kernel stays at 80 VGPRs, since at 82 a compute unit holds five
+// workgroups instead of six and the levels below took 10% longer.  Measured
+// (us, before: four probes at once, own-lane rows, 512 vertices a wave):
+// R-MAT scale 22, 4145 -> 1.28 M vertices 78 -> 59, 1.28 M -> 1.10 M 24 -> 20;
+// 3 M vertices with power-law degrees, 70706 -> 2.55 M 62 -> 39, 1930 -> 0.96 M
+// 172 -> 148; 100003 vertices, 5111 -> 31526 24.5 -> 9.2.
 __device__ __forceinline__ u64 readlane64(u64 x, int i) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, i);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), i);
@@ -1212,78 +1230,137 @@ __device__ __forceinline__ PullV pull_vertex(int k, int total, int64_t w0, const
   return p;
 }
 
-// First in-neighbour of p.v among its head arcs that is in the frontier
-// (-1: none); *more: the row goes on past them.
-__device__ __forceinline__ int32_t pull_head_hit(const Args& a, const PullV& p, const int4 (&h)[kHeadArcs / 4],
-                                                 bool* more) {
-  int32_t hu[kHeadArcs];
+// First in-neighbour among head arcs h that is in the frontier (-1: none).
+// Of a ranked head (a power-law graph) the first arc is probed alone and the
+// others only where it missed: the first one decides for most vertices that
+// are found, and the probes are gathers that the L2 serves at some 150 G/s
+// (8% of the searches of an R-MAT scale 22).  Of any other head, or with at
+// most one vertex per lane, all four go out together: latency counts there.
+__device__ __forceinline__ int32_t pull_probe_first(const Args& a, const int4& h) {
+  const u64 w = h.x >= 0 ? a.fr[h.x >> 6] : 0ull;
+  return (w >> (h.x & 63)) & 1ull ? h.x : -1;
+}
+__device__ __forceinline__ void pull_probe_others(const Args& a, const int4& h, int32_t& par) {
+  const int32_t u[3] = {h.y, h.z, h.w};
+  u64 w[3];
 #pragma unroll
-  for (int r = 0; r < kHeadArcs / 4; ++r) {
-    hu[4 * r] = h[r].x;
-    hu[4 * r + 1] = h[r].y;
-    hu[4 * r + 2] = h[r].z;
-    hu[4 * r + 3] = h[r].w;
-  }
-  u64 hw[kHeadArcs];
+  for (int q = 0; q < 3; ++q) w[q] = par < 0 && u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
 #pragma unroll
-  for (int q = 0; q < kHeadArcs; ++q) hw[q] = hu[q] >= 0 ? a.fr[hu[q] >> 6] : 0ull;
+  for (int q = 2; q >= 0; --q)
+    if ((w[q] >> (u[q] & 63)) & 1ull) par = u[q];
+}
+__device__ __forceinline__ int32_t pull_probe_all(const Args& a, const int4& h) {
+  const u64 w = h.x >= 0 ? a.fr[h.x >> 6] : 0ull;
+  int32_t par = -1;
+  pull_probe_others(a, h, par);
+  return (w >> (h.x & 63)) & 1ull ? h.x : par;
+}
+
+// The rows of two vertices per lane that their head arcs left unresolved
+// (want: bounds [beg, end) in the lane of the vertex), kPullRows rows at a
+// time: kPullGroup lanes take a row kPullEager arcs each at a time, with
+// their column loads and then their bitmap loads in flight together, up to
+// kPullMid arcs into the row; rows longer still are scanned by the whole
+// wave.  Every lane calls it (uniform control flow); par becomes the first
+// in-neighbour in row order in the frontier.
+__device__ __forceinline__ int32_t pull_first(const int32_t (&u)[kPullEager], const bool (&hit)[kPullEager], int lo,
+                                              u64 lanes) {
+  // in row order: arc q of every lane of the group before arc q + 1 of any
   int32_t par = -1;
 #pragma unroll
-  for (int q = kHeadArcs - 1; q >= 0; --q)
-    if (hu[q] >= 0 && ((hw[q] >> (hu[q] & 63)) & 1ull)) par = hu[q];
-  *more = p.mine && hu[kHeadArcs - 1] >= 0;
+  for (int q = kPullEager - 1; q >= 0; --q) {
+    const u64 m = (__ballot(hit[q]) >> lo) & lanes;
+    const int32_t x = __shfl(u[q], m != 0ull ? lo + __ffsll((long long)m) - 1 : 0);
+    if (m != 0ull) par = x;
+  }
   return par;
 }
 
-// The rest of an unresolved row [beg, end) past its head arcs: its own lane
-// goes on kPullEager arcs at a time with independent loads up to kPullLane
-// arcs into the row (the lanes of a wavefront in step, each on its own
-// row), then rows longer still are scanned by the whole wavefront 64 arcs
-// at a time, one row after another.  Every lane calls it (uniform control
-// flow); returns the lane's parent, the first in-neighbour in row order in
-// the frontier.
-constexpr int64_t kPullLane = 64;
-__device__ __forceinline__ int32_t pull_row_rest(const Args& a, bool mine, int32_t par, int64_t beg, int64_t end) {
+__device__ __forceinline__ void pull_rows_rest(const Args& a, bool wantA, int32_t vA, int64_t begA, int32_t degA,
+                                               int32_t& parA, bool wantB, int32_t vB, int64_t begB, int32_t degB,
+                                               int32_t& parB) {
   const int lane = lane_id();
-  const int64_t lim = end - beg < kPullLane ? end - beg : kPullLane;
-  for (int64_t off = a.head_ranked ? 0 : kHeadArcs; __any(mine && par < 0 && off < lim); off += kPullEager) {
-    if (mine && par < 0 && off < lim) {
+  int32_t off0 = a.head_ranked ? 0 : kHeadArcs;
+  while (__popcll(__ballot(wantA)) + __popcll(__ballot(wantB)) > kPullMany) {
+    auto walk = [&](bool want, int64_t beg, int32_t deg, int32_t& par) {
       int32_t u[kPullEager];
       u64 fw[kPullEager];
 #pragma unroll
-      for (int q = 0; q < kPullEager; ++q) u[q] = off + q < lim ? a.rcols[beg + off + q] : -1;
+      for (int q = 0; q < kPullEager; ++q) u[q] = want && off0 + q < deg ? a.rcols[beg + off0 + q] : -1;
 #pragma unroll
       for (int q = 0; q < kPullEager; ++q) fw[q] = u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
 #pragma unroll
       for (int q = kPullEager - 1; q >= 0; --q)
-        if (u[q] >= 0 && ((fw[q] >> (u[q] & 63)) & 1ull)) par = u[q];
-    }
+        if ((fw[q] >> (u[q] & 63)) & 1ull) par = u[q];
+    };
+    walk(wantA, begA, degA, parA);
+    walk(wantB, begB, degB, parB);
+    off0 += kPullEager;
+    wantA = wantA && parA < 0 && off0 < degA;
+    wantB = wantB && parB < 0 && off0 < degB;
   }
-  constexpr int64_t kProbed = kPullLane;
-  u64 rest = __ballot(mine && par < 0 && end - beg > kProbed);
-  while (rest != 0ull) {
-    const int owner = __ffsll((long long)rest) - 1;
-    rest &= rest - 1ull;
-    const int64_t lo = __shfl(beg, owner) + kProbed;
-    const int64_t hi = __shfl(end, owner);
-    int32_t hit = -1;
-    for (int64_t cc = lo; cc < hi; cc += 64) {
-      const int64_t e = cc + lane;
-      int32_t x = -1;
-      bool h = false;
-      if (e < hi) {
-        x = a.rcols[e];
-        h = (a.fr[x >> 6] >> (x & 63)) & 1ull;
+  const u64 mA = __ballot(wantA), mB = __ballot(wantB);
+  const int nA = __popcll(mA), nR = nA + __popcll(mB);
+  u64 longA = 0ull, longB = 0ull;  // owners of rows left to the whole wave
+  const int grp = lane / kPullGroup, sub = lane & (kPullGroup - 1), lo = lane & ~(kPullGroup - 1);
+  for (int r = 0; r < nR; r += kPullRows) {
+    const int k = r + grp;
+    const bool inA = k < nA, on = k < nR;
+    const int own = on ? nth_set_bit(inA ? mA : mB, inA ? k : k - nA) : 0;
+    const int64_t bA = __shfl(begA, own), bB = __shfl(begB, own);
+    const int32_t dA = __shfl(degA, own), dB = __shfl(degB, own);
+    const int64_t beg = inA ? bA : bB;
+    const int32_t deg = on ? (inA ? dA : dB) : 0;
+    const int32_t lim = deg < kPullMid ? deg : kPullMid;
+    int32_t par = -1;
+    for (int32_t off = off0; __any(par < 0 && off < lim); off += kPullGroup * kPullEager) {
+      int32_t u[kPullEager];
+      u64 fw[kPullEager];
+      bool hit[kPullEager];
+#pragma unroll
+      for (int q = 0; q < kPullEager; ++q) {
+        const int32_t e = off + q * kPullGroup + sub;
+        u[q] = par < 0 && e < lim ? a.rcols[beg + e] : -1;
       }
-      const u64 hm = __ballot(h);
-      if (hm != 0ull) {
-        hit = __shfl(x, __ffsll((long long)hm) - 1);
-        break;
-      }
+#pragma unroll
+      for (int q = 0; q < kPullEager; ++q) fw[q] = u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
+#pragma unroll
+      for (int q = 0; q < kPullEager; ++q) hit[q] = (fw[q] >> (u[q] & 63)) & 1ull;
+      const int32_t x = pull_first(u, hit, lo, (1ull << kPullGroup) - 1ull);
+      if (par < 0) par = x;
     }
-    if (lane == owner) par = hit;
+    // back to the owners (each row has one, each owner one row per set)
+    const u64 more = __ballot(sub == 0 && on && par < 0 && deg > kPullMid);
+    const int myA = __popcll(mA & ((1ull << lane) - 1ull)) - r, myB = nA + __popcll(mB & ((1ull << lane) - 1ull)) - r;
+    const bool hereA = wantA && myA >= 0 && myA < kPullRows, hereB = wantB && myB >= 0 && myB < kPullRows;
+    const int32_t xA = __shfl(par, hereA ? myA * kPullGroup : 0), xB = __shfl(par, hereB ? myB * kPullGroup : 0);
+    if (hereA) parA = xA;
+    if (hereB) parB = xB;
+    longA |= __ballot(hereA && ((more >> (hereA ? myA * kPullGroup : 0)) & 1ull));
+    longB |= __ballot(hereB && ((more >> (hereB ? myB * kPullGroup : 0)) & 1ull));
   }
-  return par;
+  while ((longA | longB) != 0ull) {
+    const bool inA = longA != 0ull;
+    const int owner = __ffsll((long long)(inA ? longA : longB)) - 1;
+    if (inA) longA &= longA - 1ull; else longB &= longB - 1ull;
+    const int32_t v = __shfl(inA ? vA : vB, owner);
+    const int64_t beg = a.roffs[v], end = a.roffs[v + 1];
+    int32_t par = -1;
+    for (int64_t c = beg + (off0 > kPullMid ? off0 : kPullMid); par < 0 && c < end; c += 64 * kPullEager) {
+      int32_t u[kPullEager];
+      u64 fw[kPullEager];
+      bool hit[kPullEager];
+#pragma unroll
+      for (int q = 0; q < kPullEager; ++q) u[q] = c + q * 64 + lane < end ? a.rcols[c + q * 64 + lane] : -1;
+#pragma unroll
+      for (int q = 0; q < kPullEager; ++q) fw[q] = u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
+#pragma unroll
+      for (int q = 0; q < kPullEager; ++q) hit[q] = (fw[q] >> (u[q] & 63)) & 1ull;
+      par = pull_first(u, hit, 0, ~0ull);
+    }
+    if (lane == owner && inA) parA = par;
+    if (lane == owner && !inA) parB = par;
+  }
 }
 
 __device__ __forceinline__ void pull_settle(const Args& a, Stage& st, u64* found_w, const PullV& p, int32_t par) {
@@ -1299,11 +1376,17 @@ __device__ __forceinline__ void pull_settle(const Args& a, Stage& st, u64* found
 __device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_found)[kPullChunk]) {
   const int lane = lane_id();
   u64* found_w = s_found[threadIdx.x >> 6];
+  // words per wave and step: a line of them (8; 6, which spreads scale 22
+  // evenly over the waves, has two waves write to one line and made its late
+  // levels 12 us instead of 10), or a smaller power of two where 8 would leave
+  // waves idle (100003 vertices: 24 us at 8 words, 9 at one)
   const int64_t nwaves = (int64_t)a.grid * kWaves;
-  const int64_t nchunks = (a.nw + kPullChunk - 1) / kPullChunk;
+  int chunk = kPullChunk;
+  while (chunk > 1 && a.nw <= nwaves * (chunk / 2)) chunk /= 2;
+  const int64_t nchunks = div_up(a.nw, chunk);
   for (int64_t c = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6; c < nchunks; c += nwaves) {
-    const int64_t w0 = c * kPullChunk;
-    const bool word_lane = lane < kPullChunk && w0 + lane < a.nw;
+    const int64_t w0 = c * chunk;
+    const bool word_lane = lane < chunk && w0 + lane < a.nw;
     const u64 seen = word_lane ? a.vis[w0 + lane] : ~0ull;
     // inclusive prefix of the unvisited counts of the chunk's words (lanes 0..7)
     int inc = __popcll(~seen);
@@ -1329,36 +1412,42 @@ __device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_foun
     // positions r0 + lane and r0 + 64 + lane): their head records and
     // frontier-word probes are in flight together
     for (int r0 = 0; r0 < total; r0 += 128) {
+      const bool two = r0 + 64 < total;  // (the same in every lane)
       const PullV A = pull_vertex(r0 + lane, total, w0, todo, first);
-      const PullV B = pull_vertex(r0 + 64 + lane, total, w0, todo, first);
-      int4 hA[kHeadArcs / 4], hB[kHeadArcs / 4];
-#pragma unroll
-      for (int r = 0; r < kHeadArcs / 4; ++r) {
-        hA[r] = make_int4(-1, -1, -1, -1);
-        hB[r] = hA[r];
+      PullV B = {0, 0, 0, false};
+      int4 hA = make_int4(-1, -1, -1, -1), hB = hA;
+      if (A.mine) hA = reinterpret_cast<const int4*>(a.head)[A.v];
+      if (two) {
+        B = pull_vertex(r0 + 64 + lane, total, w0, todo, first);
+        if (B.mine) hB = reinterpret_cast<const int4*>(a.head)[B.v];
       }
-#pragma unroll
-      for (int r = 0; r < kHeadArcs / 4; ++r) {
-        if (A.mine) hA[r] = reinterpret_cast<const int4*>(a.head)[(int64_t)A.v * (kHeadArcs / 4) + r];
-        if (B.mine) hB[r] = reinterpret_cast<const int4*>(a.head)[(int64_t)B.v * (kHeadArcs / 4) + r];
+      int32_t parA, parB;
+      if (a.head_ranked && two) {
+        parA = pull_probe_first(a, hA);
+        parB = pull_probe_first(a, hB);
+        pull_probe_others(a, hA, parA);
+        pull_probe_others(a, hB, parB);
+      } else {
+        parA = pull_probe_all(a, hA);
+        parB = pull_probe_all(a, hB);
       }
-      bool moreA = false, moreB = false;
-      int32_t parA = pull_head_hit(a, A, hA, &moreA);
-      int32_t parB = pull_head_hit(a, B, hB, &moreB);
+      const bool moreA = A.mine && hA.w >= 0, moreB = B.mine && hB.w >= 0;
       // the row's bounds only when it may go on past the head and that found nothing
-      int64_t begA = 0, endA = 0, begB = 0, endB = 0;
+      int64_t begA = 0, begB = 0;
+      int32_t degA = 0, degB = 0;  // (of a longer row: as many arcs as fit)
       if (moreA && parA < 0) {
         begA = a.roffs[A.v];
-        endA = a.roffs[A.v + 1];
+        const int64_t deg = a.roffs[A.v + 1] - begA;
+        degA = deg < 0x7fffff00 ? (int32_t)deg : 0x7fffff00;
       }
       if (moreB && parB < 0) {
         begB = a.roffs[B.v];
-        endB = a.roffs[B.v + 1];
+        const int64_t deg = a.roffs[B.v + 1] - begB;
+        degB = deg < 0x7fffff00 ? (int32_t)deg : 0x7fffff00;
       }
-      parA = pull_row_rest(a, A.mine, parA, begA, endA);
-      parB = pull_row_rest(a, B.mine, parB, begB, endB);
+      pull_rows_rest(a, moreA && parA < 0, A.v, begA, degA, parA, moreB && parB < 0, B.v, begB, degB, parB);
       pull_settle(a, st, found_w, A, parA);
-      pull_settle(a, st, found_w, B, parB);
+      if (two) pull_settle(a, st, found_w, B, parB);
     }
     // the LDS words are this wave's alone and its LDS operations complete in
     // order; the barrier only keeps the compiler from moving the reads up
