@@ -260,7 +260,9 @@ BfsBase make_base(const gsw_graph* g, const Workspace& w, int32_t* lv, int32_t* 
   b.deg_max = dm >= 2147483647.0 ? 2147483647 : (int32_t)dm;
   b.head_ranked = w.head_ranked ? 1 : 0;
   b.head_rows = g->symmetric && !w.head_ranked ? 1 : 0;
+  b.solo_nf = solo_frontier(g->n, g->nnz, b.deg_max);
   b.solo = 0;
+  b.solo_bits = 0;
   return b;
 }
 
@@ -348,23 +350,28 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   if (events) GSW_HIP(hipEventRecord(ev_after(-1), s));
   int64_t launched = 0;  // launches of the level kernels so far
   int64_t consumed = 0;  // of those, launches that completed a level whose record was read
-  // A single-workgroup launch may hand its first level back untouched (too
-  // many arcs for one workgroup); the launch queued after one is therefore
-  // always a full-grid one, which runs whatever level it finds.
-  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, g->n, b.deg_max);
-  bool last_solo = false;
-  // such a launch hands a level back only for its arcs: not where the largest
-  // degree bounds them, so there one may follow another
+  // A single-workgroup launch may hand a level back (too many arcs for one
+  // workgroup); the next one is therefore not queued before the record of a
+  // full-grid launch behind it, which runs whatever level it finds.  But where
+  // the largest degree bounds the arcs, none is ever handed back, and there
+  // such launches follow one another.
+  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, g->n, b.solo_nf);
   const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs;
-  int want = solo ? kSoloAhead : kAhead + level_launches(k0, 1) - 1;
+  int64_t solo_j = -2;  // the latest such launch
+  // The latest record is of a single-workgroup launch that went on: its other
+  // records came with it, and only the last one says what to launch (a second
+  // such launch behind it found nothing to do, 4-5 us).  Until then no more is
+  // queued than the next level takes if it is the one handed back.
+  bool in_solo = false;
+  int want = solo ? kSoloAhead + 1 : kAhead + level_launches(k0, 1) - 1;
   const int32_t cap = o->max_workgroups > 0 && o->max_workgroups < b.grid_max ? o->max_workgroups : b.grid_max;
   int32_t size = cap;
   int64_t nf_prev = 0;  // frontier of the level before the latest record's
   int64_t d = 0;
   for (;; ++d) {
     while (launched - consumed < want) {
-      last_solo = solo && (solo_always || !last_solo);
-      if (last_solo) {
+      if (solo && (solo_always || solo_j + 1 < consumed)) {
+        solo_j = launched;
         const bool deep = d >= kSoloDeep;
         b.solo = deep ? kSoloMaxLevels : kSoloLevels;
         GSW_TRY(launch_level_solo(g, b, dp, (int32_t)launched, deep || w.nw <= kSoloVisSmall, s));
@@ -390,8 +397,9 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
     if (r.launch + 1 > consumed) consumed = r.launch + 1;
     ++*rows;
     if (nn == 0) break;
-    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, g->n, b.deg_max);
-    want = solo ? kSoloAhead : kAhead + level_launches(nk, nn) - 1;
+    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, g->n, b.solo_nf);
+    in_solo = solo && (r.flags & kFlagSolo) != 0;
+    want = in_solo ? level_launches(nk, nn) : solo ? kSoloAhead : kAhead + level_launches(nk, nn) - 1;
     size = launch_size(nk, nn, r.nf, nf_prev, r.disc, d, g->n, cap);
     nf_prev = r.nf;
   }
@@ -577,6 +585,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
   const BfsBase b = make_base(g, w, lv, pa, false, false);
   BfsBase b_solo = b;  // one level per single-workgroup launch
   b_solo.solo = 1;
+  b_solo.solo_bits = 1;  // every kernel is timed on the frontier it leaves
   std::memset(w.ring, 0, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long));
   w.ring_used = -1;  // every level reposts its record here: the next search clears the whole ring
   GSW_TRY(launch_init(g, b, g->iso, source, GSW_DEFAULT_KERNEL, 0, s));

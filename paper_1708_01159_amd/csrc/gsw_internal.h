@@ -264,6 +264,8 @@ struct BfsBase {
   int32_t grid_max;                // workgroups of a level-kernel launch
   int32_t count_arcs;              // accumulate the next frontier's out-degrees
   int32_t solo;                    // levels one single-workgroup launch may run (0: such launches off)
+  int32_t solo_bits;               // ... which then sets the frontier's bitmap whatever kernel comes next
+  int32_t solo_nf;                 // frontiers that qualify for one at any time (solo_frontier)
   int32_t deg_max;                 // largest out-degree (clamped to 2^31 - 1)
   int32_t head_ranked;             // head holds ranked in-arcs (bottom-up rows are then probed from their start)
   int32_t head_rows;               // head holds the rows' first out-arcs (symmetric graph, not ranked)
@@ -275,31 +277,44 @@ struct BfsBase {
 // level's record, instead of one launch of the whole grid per level.  A
 // level qualifies when its kernel is a queue-driven top-down one
 // (push_vertex, push_wave, push_edge), its frontier has at most kSoloMax
-// vertices and its arcs are bounded: by the graph's largest degree, or, in
-// the shrinking tail of a search that has reached 1% of the graph, by a
-// check of the actual arc count (at most kSoloMaxArcs) before the level
-// starts.  A launch runs at most kSoloMaxLevels levels.
+// vertices and its arcs are few: at most kSoloMaxArcs by the graph's largest
+// degree; or at most kSoloArcs by a count before the level starts, in the
+// shrinking tail of a search that has reached 1% of the graph and at its
+// beginning (where four times the average degree, as hubs come early, stays
+// below the limit).  A launch runs at most kSoloMaxLevels levels.
 // The dependent steps of a level bound such a workgroup while the frontier
 // is small, one compute unit's instruction issue later: measured on MI355X
 // (1023 x 1025 grid) a level costs it about 1 us up to 256 frontier vertices,
 // 1.7 us at 750 and 2.6 us at 1200, while a level kernel launch costs about
 // 6 us on the device plus about 3 us between launches at any of these sizes.
 // 2048 is what the workgroup holds in two entries a thread; larger frontiers
-// would spill to the queue.
+// would spill to the queue.  The arcs: one compute unit's claims leave it at
+// one in 2-3 ns, and a frontier it hands to a bottom-up level costs as many
+// again for the bitmap: 5 vertices with 4260 arcs took 16 us and 10 more at
+// the end (a level kernel: 10), 21 with 21 or 84 with 746 4-5 us (16 and 9).
+// (Where rows are that short the largest degree decides, and there are few
+// claims per arc.)
 constexpr int kSoloBlock = 1024;
 constexpr int kSoloSlots = 2;  // frontier entries per thread at most
 constexpr int64_t kSoloMax = 2048;
 static_assert(kSoloMax <= (int64_t)kSoloBlock * kSoloSlots, "every frontier entry has a thread slot");
-constexpr int64_t kSoloMaxArcs = 65536;
+constexpr int64_t kSoloMaxArcs = 8192;
+constexpr int64_t kSoloArcs = 2048;
 constexpr int kSoloMaxLevels = 80;
 constexpr int32_t kSoloTree = 1024;  // such launches run with a tree of at most this many nodes
 constexpr int64_t kSoloVisWords = 16384;  // 64-bit words of a visited bitmap that LDS has room for
+// Frontiers of at most this many vertices qualify whatever the search's state.
+__host__ __device__ inline int32_t solo_frontier(long long n, long long nnz, int32_t deg_max) {
+  const long long by_max = deg_max > 0 ? kSoloMaxArcs / deg_max : kSoloMax;
+  const long long by_avg = nnz > 0 ? (long long)((double)kSoloArcs * (double)n / (4.0 * (double)nnz)) : kSoloMax;
+  const long long f = by_max > by_avg ? by_max : by_avg;
+  return (int32_t)(f < kSoloMax ? (f > 1 ? f : 1) : kSoloMax);
+}
 __host__ __device__ inline bool solo_eligible(int k, long long nn, long long nf, long long disc_next, long long n,
-                                              int32_t deg_max) {
+                                              int32_t solo_nf) {
   if (k < 0 || kernel_base(k) > GSW_K_PUSH_EDGE) return false;
   if (nn < 1 || nn > kSoloMax) return false;
-  if ((long long)deg_max * nn <= kSoloMaxArcs) return true;
-  return nn <= nf && disc_next * 100 >= n;
+  return nn <= solo_nf || (nn <= nf && disc_next * 100 >= n);
 }
 
 // A tree node in 8 bytes for the device walk: left and right child (int16,

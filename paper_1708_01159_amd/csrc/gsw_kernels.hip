@@ -1817,10 +1817,11 @@ __device__ __forceinline__ void solo_publish(const BfsBase& b, BfsCtl* cn, const
   const int tid = threadIdx.x;
   int32_t* q = b.q[lv & 1];
   u64* bm = b.bm[lv % 3];
+  const bool bits = b.solo_bits || kernel_base(kernel) > GSW_K_PUSH_EDGE;  // (only these levels read the bitmap)
   for (long long i = tid; i < f; i += kSoloBlock) {
     const int32_t v = i < kSoloMax ? list[i] : q[i];
     if (i < kSoloMax) q[i] = v;
-    atomicOr(bm + (v >> 6), 1ull << (v & 63));
+    if (bits) atomicOr(bm + (v >> 6), 1ull << (v & 63));
   }
   if (tid < kQueueBins) {
     b.ctr[(size_t)(lv & 3) * kCtrSlot + tid * kCtrStride] = tid == 0 ? (uint32_t)f : 0u;
@@ -1901,7 +1902,6 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   bool leaf_push = kernel_base(leaf_next) <= GSW_K_PUSH_EDGE;  // ... which may go on here
   // frontiers whose arcs the largest degree bounds
   const int32_t bound_arcs = b.deg_max > 0 ? (int32_t)(kSoloMaxArcs / b.deg_max) : (int32_t)kSoloMax;
-  const int32_t bound_nf = bound_arcs < (int32_t)kSoloMax ? bound_arcs : (int32_t)kSoloMax;
   const int32_t levels_max = b.solo;
   int levels = 0;  // completed here
   int slot = 0;
@@ -1979,7 +1979,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     if (!HeadOnly && (check || b.deg_max > kSoloShort)) {
       lds_barrier();
       nlong = L.nlong[slot] < (uint32_t)kSoloLong ? L.nlong[slot] : (uint32_t)kSoloLong;
-      if (check && L.esum[slot] > (u64)kSoloMaxArcs) {
+      if (check && L.esum[slot] > (u64)kSoloArcs) {
         // too many arcs for one workgroup: the level goes back to the level
         // kernel untouched (on the first level nothing has changed at all)
         if (lv == 0) {
@@ -2094,7 +2094,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       }
       // (solo_eligible, with the kernel's part of it decided above)
       const bool go = lv + 1 < levels_max && nn > 0 && leaf_push &&
-                      (nn <= bound_nf || (nn <= (int32_t)kSoloMax && nn <= nf && (long long)ndisc * 100 >= b.n));
+                      (nn <= b.solo_nf || (nn <= (int32_t)kSoloMax && nn <= nf && (long long)ndisc * 100 >= b.n));
       const int32_t next = nn > 0 ? leaf_next : kCtlDone, nflags = nn > 0 ? leaf_flags : 0;
       if (tid == 0) {
         L.go = go ? 1 : 0;

@@ -104,3 +104,28 @@ def test_solo_edges(name):
                 if kw["policy"] == "fixed":
                     assert sum(1 for t in rows if t.flags & SOLO) >= 0.5 * len(rows)
     G.close()
+
+
+@pytest.mark.parametrize("children,leaves", [(15, 127), (16, 127), (16, 128), (63, 129), (511, 2), (513, 2), (186, 10),
+                                             (187, 10), (750, 10), (2047, 0), (2048, 0), (2049, 0), (4600, 0)])
+def test_solo_start_of_a_search_at_its_arc_limit(children, leaves):
+    """A hub's level and its children's, with arcs on both sides of what one
+    workgroup takes uncounted by degree (2048)."""
+    src, dst, nv = [], [], 1 + children
+    for c in range(1, children + 1):
+        src.append(0), dst.append(c)
+        src.extend([c] * leaves), dst.extend(range(nv, nv + leaves))
+        nv += leaves
+    g = gg.from_edges(nv, src, dst, name="hub")
+    G = gsw.Graph.from_csr(g.offs, g.cols)
+    for s in (0, nv - 1):
+        ref = oracle.levels(g.offs, g.cols, s)
+        sizes = np.bincount(ref[ref >= 0])
+        for kernel in (gsw.PUSH_VERTEX, gsw.PUSH_EDGE):
+            for count_arcs in (False, True):
+                lv, pa, tr = gsw.bfs(G, [s], policy="fixed", kernel=kernel, count_arcs=count_arcs)
+                assert np.array_equal(lv[0], ref)
+                checks.check_bfs(g.offs, g.cols, s, lv[0], pa[0])
+                assert [t.n_frontier for t in tr] == sizes.tolist()
+                assert not any(t.flags & SOLO and t.e_frontier > 8192 for t in tr)
+    G.close()
