@@ -51,6 +51,7 @@ struct Policy {
   const gsw_bfs_opts* o;
   bool has_origin;
   bool has_rorigin;
+  bool hubs = false;  // sources of largest degree: no single-workgroup launch to begin with
 };
 
 gsw_status check_kernel(const gsw_graph* g, int k) {
@@ -355,7 +356,7 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   // full-grid launch behind it, which runs whatever level it finds.  But where
   // the largest degree bounds the arcs, none is ever handed back, and there
   // such launches follow one another.
-  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, g->n, b.solo_nf);
+  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, g->n, b.solo_nf) && !(pol.hubs && b.deg_max > kSoloArcs);
   const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs;
   int64_t solo_j = -2;  // the latest such launch
   // The latest record is of a single-workgroup launch that went on: its other
@@ -445,7 +446,7 @@ bool may_pick(const gsw_bfs_opts* o, int base) {
 // The per-source loop of gsw_bfs (the graph's lock held, options checked).
 gsw_status bfs_sources(gsw_graph* g, const gsw_bfs_opts* o, const int32_t* sources, int32_t n_sources,
                        int32_t* levels, int32_t* parents, gsw_level_trace* trace, int32_t trace_cap,
-                       int32_t* rows) {
+                       int32_t* rows, bool wait = true, bool hubs = false) {
   GSW_HIP(hipSetDevice(g->device));
   GSW_TRY(ensure_workspace(g));
   if (may_pick(o, GSW_K_EDGE_SCAN)) GSW_TRY(ensure_origin(g));
@@ -455,7 +456,7 @@ gsw_status bfs_sources(gsw_graph* g, const gsw_bfs_opts* o, const int32_t* sourc
   if (o->policy == GSW_POLICY_SCHEDULE) GSW_TRY(ensure_schedule(g, o->schedule, o->schedule_len, s));
   const bool has_origin = g->origin != nullptr || g->nnz == 0;
   const bool has_rorigin = g->rorigin != nullptr || g->nnz == 0;
-  const Policy pol{o, has_origin, has_rorigin};
+  const Policy pol{o, has_origin, has_rorigin, hubs};
   const BfsPolicy dp = device_policy(g, g->ws, o, has_origin, has_rorigin);
   const int64_t n = g->n;
   for (int32_t i = 0; i < n_sources; ++i) {
@@ -474,14 +475,14 @@ gsw_status bfs_sources(gsw_graph* g, const gsw_bfs_opts* o, const int32_t* sourc
                                hipMemcpyDeviceToHost, s));
     }
   }
-  GSW_HIP(hipStreamSynchronize(s));
+  if (wait) GSW_HIP(hipStreamSynchronize(s));
   return GSW_OK;
 }
 
 }  // namespace
 
 gsw_status bfs_rows_locked(gsw_graph* g, const int32_t* sources, int32_t count, int32_t* d_levels,
-                           const gsw_tree* tree, hipStream_t s) {
+                           const gsw_tree* tree, hipStream_t s, bool wait, bool hubs) {
   gsw_bfs_opts o;
   gsw_bfs_opts_default(&o);
   if (tree) {
@@ -494,7 +495,7 @@ gsw_status bfs_rows_locked(gsw_graph* g, const int32_t* sources, int32_t count, 
   o.device_ptrs = 1;
   o.stream = s;
   int32_t rows = 0;
-  return bfs_sources(g, &o, sources, count, d_levels, nullptr, nullptr, 0, &rows);
+  return bfs_sources(g, &o, sources, count, d_levels, nullptr, nullptr, 0, &rows, wait, hubs);
 }
 
 }  // namespace gsw

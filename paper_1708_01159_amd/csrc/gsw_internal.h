@@ -429,9 +429,11 @@ gsw_status ensure_origin(gsw_graph* g);
 gsw_status ensure_rorigin(gsw_graph* g);
 // Single-source BFS rows [count][n] int32 into device memory, with the graph's
 // lock already held (the batched path's fallback); policy from tree (NULL:
-// the default kernel at every level).
+// the default kernel at every level).  Without `wait` the rows are complete
+// in stream order only.  hubs: the sources are vertices of largest degree.
 gsw_status bfs_rows_locked(gsw_graph* g, const int32_t* sources, int32_t count, int32_t* d_levels,
-                           const gsw_tree* tree, hipStream_t s);
+                           const gsw_tree* tree, hipStream_t s, bool wait = true,
+                           bool hubs = false);
 hipStream_t pick_stream(gsw_graph* g, void* user_stream);
 
 bool kernel_is_pull(int k);
