@@ -926,9 +926,17 @@ __global__ void __launch_bounds__(out_block(G)) k_ms_levels_out(const u64* __res
 // vis = (vis & ~clr) | set on every vertex: slots being admitted start
 // unvisited everywhere (so no vertex is known to be full any more), freed
 // slots become inert (visited everywhere).
+struct SsMasks {
+  u64 clr[kMaxWords], set[kMaxWords];
+};
 __global__ void __launch_bounds__(kMsBlock) k_ss_masks(u64* vis, u64* full, int64_t n, int W, int admits,
-                                                       const u64* __restrict__ clr,
-                                                       const u64* __restrict__ set) {
+                                                       SsMasks m) {
+  __shared__ u64 clr[kMaxWords], set[kMaxWords];
+  if (threadIdx.x < kMaxWords) {
+    clr[threadIdx.x] = m.clr[threadIdx.x];
+    set[threadIdx.x] = m.set[threadIdx.x];
+  }
+  __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * kMsBlock;
   const int64_t gid = (int64_t)blockIdx.x * kMsBlock + threadIdx.x;
   for (int64_t i = gid; i < n * W; i += stride) {
@@ -942,10 +950,24 @@ __global__ void __launch_bounds__(kMsBlock) k_ss_masks(u64* vis, u64* full, int6
 // Admitted slots, by one workgroup: a source that is in no slot's frontier has
 // its frontier row cleared whole; then the source's bit in vis, in the current
 // frontier and its bitmap, level 0 (stored as 1), and the slot joins the next
-// level top-down.
+// level top-down.  The sources, their slots and every slot's start level are
+// read from host memory, each once (a copy to the device before it cost 8 us
+// of stream time each).
 __global__ void __launch_bounds__(kMsSeedBlock) k_ss_seed(u64* vis, u64* fr, u64* fbm, int32_t* dist, MsCtl* ctl,
-                                                          int64_t n, int W, const int32_t* __restrict__ src,
-                                                          const int32_t* __restrict__ slot, int count) {
+                                                          int64_t n, int W, const int32_t* __restrict__ h_src,
+                                                          const int32_t* __restrict__ h_slot, int count,
+                                                          const long long* __restrict__ h_start, long long* start,
+                                                          int slots) {
+  __shared__ int32_t src[GSW_MSBFS_MAX_SOURCES], slot[GSW_MSBFS_MAX_SOURCES];
+  for (int i = threadIdx.x; i < slots; i += kMsSeedBlock) {
+    const long long st = h_start[i];
+    if (i < count) {
+      src[i] = h_src[i];
+      slot[i] = h_slot[i];
+    }
+    start[i] = st;
+  }
+  __syncthreads();
   for (int i = threadIdx.x; i < count * W; i += kMsSeedBlock) {
     const int64_t s = src[i / W];
     if (!((fbm[s >> 6] >> (s & 63)) & 1ull)) fr[s * W + i % W] = 0ull;
@@ -981,12 +1003,39 @@ __global__ void k_ss_thresholds(MsCtl* ctl, double to_pull, double to_push) {
 }
 
 // A finished slot's levels: out[v] = row[v] - 1 (-1 = not reached), and the
-// row is cleared for the slot's next query.
-__global__ void __launch_bounds__(kMsBlock) k_ss_take(int32_t* row, int32_t* __restrict__ out, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * kMsBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kMsBlock + threadIdx.x; i < n; i += stride) {
-    out[i] = row[i] - 1;
-    row[i] = 0;
+// row is cleared for the slot's next query.  With a flag the host waits for
+// that and not for the stream, whose end it sees 8 us later: every level is
+// then stored through to memory, so that it is in place for any reader, the
+// workgroups count themselves once their stores have been acknowledged, and
+// the last one posts seq.  64 rows of 262144 levels, taken one by one: 17 ->
+// 10 us each.  (At most kSsTakeGrid workgroups: the counts serialise.)
+constexpr int kSsTakeBlock = 1024;
+constexpr int kSsTakeGrid = 256;
+constexpr size_t kSsTakeCtr = 128;  // bytes of its counter
+__global__ void __launch_bounds__(kSsTakeBlock) k_ss_take(int32_t* row, int32_t* __restrict__ out, int64_t n,
+                                                          uint32_t* ctr, u64* flag, u64 seq) {
+  const int64_t stride = (int64_t)gridDim.x * kSsTakeBlock;
+  for (int64_t i0 = (int64_t)blockIdx.x * kSsTakeBlock + threadIdx.x; i0 < n; i0 += 4 * stride) {
+    int32_t x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = i0 + k * stride < n ? row[i0 + k * stride] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = i0 + k * stride;
+      if (i >= n) continue;
+      if (flag)
+        __hip_atomic_store(out + i, x[k] - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      else
+        out[i] = x[k] - 1;
+      row[i] = 0;
+    }
+  }
+  if (!flag) return;
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicAdd(ctr, 1u) == gridDim.x - 1u) {
+    __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1503,20 +1552,21 @@ struct gsw_session {
   u64 *vis = nullptr, *fr = nullptr, *frn = nullptr, *nx = nullptr;
   u64* bms = nullptr;     // kMsBitmaps bitmaps
   u64* fbm[2] = {};       // fbm[0] pairs with fr, fbm[1] with frn (swapped together)
-  u64* masks = nullptr;   // clr[kMaxWords] then set[kMaxWords]
-  int32_t *dist = nullptr, *seed = nullptr;  // seed: src[slots] then slot[slots]
+  int32_t* dist = nullptr;
+  uint32_t* take_ctr = nullptr;             // workgroups of the running k_ss_take that have finished
+  u64 *flag = nullptr, *d_flag = nullptr;   // mapped host memory: the latest fetch that is in place
+  u64 fetches = 0;
   long long* start_d = nullptr;             // start level of every slot (device)
   int32_t* take = nullptr;  // device staging for fetches into host memory
   LevelStats st;
-  // pinned staging for the per-boundary uploads (masks; seed src/slot; start
-  // of every slot), kStage sets used in turn: an async copy reads its set
-  // when it runs on the stream, and with up to two levels queued beyond the
+  // mapped host memory for the per-boundary uploads (seed src/slot; start of
+  // every slot), kStage sets used in turn: the seed kernel reads its set when
+  // it runs on the stream, and with up to two levels queued beyond the
   // one the host waits for, a set is rewritten only after the level it fed
   // has finished
   static constexpr int kStage = 4;
-  u64* h_masks = nullptr;    // [kStage][2 kMaxWords]
-  int32_t* h_seed = nullptr;   // [kStage][2 slots]
-  long long* h_start = nullptr;  // [kStage][slots]
+  int32_t *h_seed = nullptr, *d_seed = nullptr;      // [kStage][2 slots]; as seen by the device
+  long long *h_start = nullptr, *d_start = nullptr;  // [kStage][slots]
   std::vector<long long> start_up;  // start level of every slot, as uploaded
   std::vector<int32_t> source;
   std::vector<int64_t> start;  // level at which a running slot was seeded
@@ -1537,11 +1587,11 @@ namespace {
 void ss_free(gsw_session* ss) {
   if (!ss) return;
   if (ss->stream) (void)hipStreamSynchronize(ss->stream);  // a level may still be queued
-  void* p[] = {ss->vis, ss->fr, ss->frn, ss->nx, ss->bms, ss->masks, ss->dist, ss->start_d, ss->seed, ss->take};
+  void* p[] = {ss->vis, ss->fr, ss->frn, ss->nx, ss->bms, ss->dist, ss->start_d, ss->take_ctr, ss->take};
   for (void* x : p)
     if (x) (void)hipFree(x);
   stats_free(&ss->st);
-  void* hp[] = {ss->h_masks, ss->h_seed, ss->h_start};
+  void* hp[] = {ss->flag, ss->h_seed, ss->h_start};
   for (void* x : hp)
     if (x) (void)hipHostFree(x);
   if (ss->stream) (void)hipStreamDestroy(ss->stream);
@@ -1557,9 +1607,9 @@ size_t gsw_session_bytes(const gsw_graph* g, int32_t max_slots) {
   const int64_t n = g->n;
   const size_t W = (size_t)(max_slots + 63) / 64;
   const size_t words = (size_t)cdiv(n, 64);
-  return 4 * (size_t)n * W * sizeof(u64) + kMsBitmaps * words * sizeof(u64) + 2 * (size_t)kMaxWords * sizeof(u64) +
+  return 4 * (size_t)n * W * sizeof(u64) + kMsBitmaps * words * sizeof(u64) + kSsTakeCtr +
          (size_t)max_slots * n * sizeof(int32_t) + (size_t)max_slots * sizeof(long long) +
-         2 * (size_t)max_slots * sizeof(int32_t) + (size_t)n * sizeof(int32_t) + stats_bytes();
+         (size_t)n * sizeof(int32_t) + stats_bytes();
 }
 
 gsw_status gsw_session_create(const gsw_graph* cg, int32_t max_slots, gsw_session** out) {
@@ -1592,10 +1642,9 @@ gsw_status gsw_session_create(const gsw_graph* cg, int32_t max_slots, gsw_sessio
                {(void**)&ss->frn, mb},
                {(void**)&ss->nx, mb},
                {(void**)&ss->bms, bb},
-               {(void**)&ss->masks, 2 * (size_t)kMaxWords * sizeof(u64)},
                {(void**)&ss->dist, (size_t)max_slots * n * sizeof(int32_t)},
                {(void**)&ss->start_d, (size_t)max_slots * sizeof(long long)},
-               {(void**)&ss->seed, 2 * (size_t)max_slots * sizeof(int32_t)},
+               {(void**)&ss->take_ctr, kSsTakeCtr},
                {(void**)&ss->take, (size_t)n * sizeof(int32_t)}};
   for (auto& it : items) {
     hipError_t e = hipMalloc(it.p, it.bytes);
@@ -1616,13 +1665,18 @@ gsw_status gsw_session_create(const gsw_graph* cg, int32_t max_slots, gsw_sessio
   if (st == GSW_OK) st = stats_alloc(&ss->st, ss->stream);
   if (st == GSW_OK) {
     ss->bytes += ss->st.bytes;
-    if (hipHostMalloc((void**)&ss->h_masks, gsw_session::kStage * 2 * (size_t)kMaxWords * sizeof(u64),
-                      hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&ss->h_seed, gsw_session::kStage * 2 * (size_t)max_slots * sizeof(int32_t),
-                      hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&ss->h_start, gsw_session::kStage * (size_t)max_slots * sizeof(long long),
-                      hipHostMallocDefault) != hipSuccess)
+    const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
+    if (hipHostMalloc((void**)&ss->flag, sizeof(u64), mapped) != hipSuccess ||
+        hipHostMalloc((void**)&ss->h_seed, gsw_session::kStage * 2 * (size_t)max_slots * sizeof(int32_t), mapped) !=
+            hipSuccess ||
+        hipHostMalloc((void**)&ss->h_start, gsw_session::kStage * (size_t)max_slots * sizeof(long long), mapped) !=
+            hipSuccess ||
+        hipHostGetDevicePointer((void**)&ss->d_flag, ss->flag, 0) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&ss->d_seed, ss->h_seed, 0) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&ss->d_start, ss->h_start, 0) != hipSuccess)
       st = fail(GSW_EHIP, "session pinned staging memory");
+    else
+      *ss->flag = 0ull;
   }
   if (st == GSW_OK) {
     const hipStream_t s = ss->stream;
@@ -1632,6 +1686,7 @@ gsw_status gsw_session_create(const gsw_graph* cg, int32_t max_slots, gsw_sessio
     if (hipMemsetAsync(ss->vis, 0xff, mb, s) != hipSuccess || hipMemsetAsync(ss->fr, 0, mb, s) != hipSuccess ||
         hipMemsetAsync(ss->frn, 0, mb, s) != hipSuccess || hipMemsetAsync(ss->nx, 0, mb, s) != hipSuccess ||
         hipMemsetAsync(ss->bms, 0, bb, s) != hipSuccess ||
+        hipMemsetAsync(ss->take_ctr, 0, kSsTakeCtr, s) != hipSuccess ||
         hipMemsetAsync(ss->dist, 0, (size_t)max_slots * n * sizeof(int32_t), s) != hipSuccess ||
         hipMemcpyAsync(ss->st.ctl, ss->st.h_ctl, sizeof(MsCtl), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -1682,13 +1737,13 @@ gsw_status ss_queue_level(gsw_session* ss, bool* queued_one) {
   int c = 0;
   bool any_mask = false, running = false;
   const int si = (int)(ss->queued % gsw_session::kStage);
-  u64* h_masks = ss->h_masks + (size_t)si * 2 * kMaxWords;
+  SsMasks m;
   int32_t* h_seed = ss->h_seed + (size_t)si * 2 * ss->slots;
   long long* h_start = ss->h_start + (size_t)si * ss->slots;
   {
     std::lock_guard<std::mutex> lock(ss->mu);
-    u64* clr = h_masks;
-    u64* set = h_masks + kMaxWords;
+    u64* clr = m.clr;
+    u64* set = m.set;
     for (int j = 0; j < kMaxWords; ++j) clr[j] = set[j] = 0ull;
     for (int k = 0; k < ss->slots; ++k) {
       if (ss->state[(size_t)k] == 1) {
@@ -1709,26 +1764,18 @@ gsw_status ss_queue_level(gsw_session* ss, bool* queued_one) {
     }
   }
   if (any_mask) {
-    GSW_HIP(hipMemcpyAsync(ss->masks, h_masks, 2 * (size_t)kMaxWords * sizeof(u64), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_ss_masks, dim3((unsigned)std::min<int64_t>(cdiv(n * W, kMsBlock), 65536)),
-                       dim3(kMsBlock), 0, s, ss->vis, ss->bms + 3 * cdiv(n, 64), n, W, c > 0 ? 1 : 0,
-                       (const u64*)ss->masks,
-                       (const u64*)(ss->masks + kMaxWords));
+                       dim3(kMsBlock), 0, s, ss->vis, ss->bms + 3 * cdiv(n, 64), n, W, c > 0 ? 1 : 0, m);
   }
   if (c > 0) {
     std::memcpy(h_start, ss->start_up.data(), (size_t)ss->slots * sizeof(long long));
-    GSW_HIP(hipMemcpyAsync(ss->seed, h_seed, 2 * (size_t)ss->slots * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    GSW_HIP(hipMemcpyAsync(ss->start_d, h_start, ss->slots * sizeof(long long), hipMemcpyHostToDevice, s));
+    const int32_t* d_seed = ss->d_seed + (size_t)si * 2 * ss->slots;
     hipLaunchKernelGGL(k_ss_seed, dim3(1), dim3(kMsSeedBlock), 0, s, ss->vis, ss->fr, ss->fbm[0], ss->dist,
-                       ss->st.ctl, n, W, (const int32_t*)ss->seed, (const int32_t*)(ss->seed + ss->slots), c);
+                       ss->st.ctl, n, W, d_seed, d_seed + ss->slots, c,
+                       (const long long*)(ss->d_start + (size_t)si * ss->slots), ss->start_d, ss->slots);
   }
   GSW_HIP(hipGetLastError());
-  if (!running) {
-    // nothing to run: no level will be queued after these copies, so wait
-    // for them before the staging set can come round again
-    if (any_mask) GSW_HIP(hipStreamSynchronize(s));
-    return GSW_OK;
-  }
+  if (!running) return GSW_OK;  // (then nothing was seeded: no staging set is in use)
   MsArgs a;
   std::memset(&a, 0, sizeof a);
   a.offs = g->offs;
@@ -1824,12 +1871,19 @@ gsw_status gsw_session_fetch(gsw_session* ss, int32_t slot, int32_t* levels, int
   const int64_t n = ss->g->n;
   int32_t* row = ss->dist + (int64_t)slot * n;
   int32_t* dst = device_ptr ? levels : ss->take;
-  hipLaunchKernelGGL(k_ss_take, dim3((unsigned)std::min<int64_t>(cdiv(n, kMsBlock), 65536)), dim3(kMsBlock), 0, s,
-                     row, dst, n);
+  u64* flag = device_ptr ? ss->d_flag : nullptr;
+  const u64 seq = ++ss->fetches;
+  hipLaunchKernelGGL(k_ss_take, dim3((unsigned)std::min<int64_t>(cdiv(n, 4 * kSsTakeBlock), kSsTakeGrid)),
+                     dim3(kSsTakeBlock), 0, s, row, dst, n, ss->take_ctr, flag, seq);
   GSW_HIP(hipGetLastError());
-  if (!device_ptr)
+  if (device_ptr) {
+    bool missing = false;
+    GSW_HIP(await_record([&]() -> bool { return *(const volatile u64*)ss->flag == seq; }, s, &missing));
+    if (missing) return fail(GSW_EHIP, "slot %d: the copy finished without posting its flag", slot);
+  } else {
     GSW_HIP(hipMemcpyAsync(levels, ss->take, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  GSW_HIP(hipStreamSynchronize(s));
+    GSW_HIP(hipStreamSynchronize(s));
+  }
   std::lock_guard<std::mutex> lock(ss->mu);
   ss->state[(size_t)slot] = 0;
   ss->source[(size_t)slot] = -1;
