@@ -47,13 +47,6 @@ constexpr int64_t kSoloVisSmall = 2048;
 constexpr int32_t kSmallLaunch = 16;
 constexpr int64_t kSmallFrontier = 4096;
 
-struct Policy {
-  const gsw_bfs_opts* o;
-  bool has_origin;
-  bool has_rorigin;
-  bool hubs = false;  // sources of largest degree: no single-workgroup launch to begin with
-};
-
 gsw_status check_kernel(const gsw_graph* g, int k) {
   (void)g;
   if (k < 0 || k >= GSW_N_KERNELS) return fail(GSW_EINVAL, "unknown kernel id %d", k);
@@ -314,18 +307,19 @@ int32_t launch_size(int next_kernel, int64_t nn, int64_t nf, int64_t nf_prev, in
 namespace {
 
 // Waits until level d's record is in the ring.
-gsw_status wait_record(const gsw_graph* g, int64_t d, hipStream_t s, Record* rec) {
+gsw_status wait_record(const Workspace& w, int64_t d, hipStream_t s, Record* rec) {
   bool missing = false;
-  const hipError_t e = await_record([&]() -> bool { return take_record(g->ws.ring, d, rec); }, s, &missing);
+  const hipError_t e = await_record([&]() -> bool { return take_record(w.ring, d, rec); }, s, &missing);
   if (e != hipSuccess) return fail(GSW_EHIP, "level %lld: %s", (long long)d, hipGetErrorString(e));
   if (missing) return fail(GSW_EHIP, "level %lld finished without posting its record", (long long)d);
   return GSW_OK;
 }
 
-gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int32_t src_idx, int32_t src,
-                      int32_t* lv, int32_t* pa, gsw_level_trace* trace, int32_t trace_cap, int32_t* rows,
-                      hipStream_t s) {
-  Workspace& w = g->ws;
+}  // namespace
+
+gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso, const SearchPolicy& pol,
+                      const BfsPolicy& dp, int32_t src_idx, int32_t src, int32_t* lv, int32_t* pa,
+                      gsw_level_trace* trace, int32_t trace_cap, int32_t* rows, hipStream_t s) {
   const gsw_bfs_opts* o = pol.o;
   const bool events = o->time_levels == 2;  // per-launch HIP events
   const bool timed = o->time_levels == 1;   // device wall-clock stamps
@@ -347,7 +341,7 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   // single-workgroup multi-level launches: not with per-launch events (their
   // levels would share one launch's time), and with a tree its workgroup holds
   b.solo = !o->no_solo && !events && (o->policy != GSW_POLICY_TREE || w.tree_nodes <= kSoloTree) ? kSoloLevels : 0;
-  GSW_TRY(launch_init(g, b, g->iso, src, k0, flags0, s));
+  GSW_TRY(launch_init(g, b, iso, src, k0, flags0, s));
   if (events) GSW_HIP(hipEventRecord(ev_after(-1), s));
   int64_t launched = 0;  // launches of the level kernels so far
   int64_t consumed = 0;  // of those, launches that completed a level whose record was read
@@ -382,7 +376,7 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
       ++launched;
     }
     Record r;
-    GSW_TRY(wait_record(g, d, s, &r));
+    GSW_TRY(wait_record(w, d, s, &r));
     const int64_t nn = r.next;
     const int nk = r.next_kernel;
     const int64_t first_j = consumed;  // launches of this level: first_j .. r.launch
@@ -408,6 +402,8 @@ gsw_status run_levels(gsw_graph* g, const Policy& pol, const BfsPolicy& dp, int3
   if (canonical) GSW_TRY(launch_canonical_parents(g, w, lv, pa, s));
   return GSW_OK;
 }
+
+namespace {
 
 struct DevBuf {
   void* p = nullptr;
@@ -456,13 +452,13 @@ gsw_status bfs_sources(gsw_graph* g, const gsw_bfs_opts* o, const int32_t* sourc
   if (o->policy == GSW_POLICY_SCHEDULE) GSW_TRY(ensure_schedule(g, o->schedule, o->schedule_len, s));
   const bool has_origin = g->origin != nullptr || g->nnz == 0;
   const bool has_rorigin = g->rorigin != nullptr || g->nnz == 0;
-  const Policy pol{o, has_origin, has_rorigin, hubs};
+  const SearchPolicy pol{o, has_origin, has_rorigin, hubs};
   const BfsPolicy dp = device_policy(g, g->ws, o, has_origin, has_rorigin);
   const int64_t n = g->n;
   for (int32_t i = 0; i < n_sources; ++i) {
     int32_t* lv = o->device_ptrs ? levels + (size_t)i * n : g->ws.lvl_tmp;
     int32_t* pa = parents ? (o->device_ptrs ? parents + (size_t)i * n : g->ws.par_tmp) : nullptr;
-    const gsw_status st = run_levels(g, pol, dp, i, sources[i], lv, pa, trace, trace_cap, rows, s);
+    const gsw_status st = run_levels(g, g->ws, g->iso, pol, dp, i, sources[i], lv, pa, trace, trace_cap, rows, s);
     if (st != GSW_OK) {
       (void)hipStreamSynchronize(s);
       return st;
@@ -689,7 +685,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
     cur = adv_solo ? 1 : level_launches(adv, nf) & 1;  // slot written by the last launch
     GSW_HIP(hipStreamSynchronize(s));
     Record r;
-    GSW_TRY(wait_record(g, d, s, &r));
+    GSW_TRY(wait_record(w, d, s, &r));
     const int64_t nn = r.next;
     GSW_HIP(hipMemcpy(w.h_ctr, w.ctr + (size_t)((d + 1) & 3) * kCtrSlot, kCtrSlot * sizeof(uint32_t),
                       hipMemcpyDeviceToHost));

@@ -378,6 +378,18 @@ using namespace gsw;
 
 namespace {
 
+// The record ring of searches that may not allocate, so made with the graph.
+gsw_status make_noalloc_ring(gsw_graph* g) {
+  if (g->n > GSW_NOALLOC_MAX_VERTICES) return GSW_OK;
+  const size_t rb = (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long);
+  if (hipHostMalloc((void**)&g->na_ring, rb, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&g->d_na_ring, g->na_ring, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(GSW_ENOMEM, "mapped host memory for the level records");
+  }
+  return GSW_OK;
+}
+
 void free_graph(gsw_graph* g) {
   if (!g) return;
   Workspace& w = g->ws;
@@ -391,6 +403,7 @@ void free_graph(gsw_graph* g) {
   if (w.h_ctr) (void)hipHostFree(w.h_ctr);
   if (w.h_ctl) (void)hipHostFree(w.h_ctl);
   if (w.ring) (void)hipHostFree(w.ring);
+  if (g->na_ring) (void)hipHostFree(g->na_ring);
   if (g->iso) (void)hipFree(g->iso);
   for (hipEvent_t ev : w.ev)
     if (ev) (void)hipEventDestroy(ev);
@@ -490,6 +503,7 @@ gsw_status gsw_graph_create_host(int64_t n, int64_t nnz, const int64_t* offs, co
   if (st == GSW_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(GSW_EHIP, "CSR upload");
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_origin(g);
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_rorigin(g);
+  if (st == GSW_OK) st = make_noalloc_ring(g);
   if (st != GSW_OK) {
     free_graph(g);
     return st;
@@ -534,6 +548,7 @@ gsw_status gsw_graph_create_device(int64_t n, int64_t nnz, const int64_t* d_offs
   if (st == GSW_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(GSW_EHIP, "transpose upload");
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_origin(g);
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_rorigin(g);
+  if (st == GSW_OK) st = make_noalloc_ring(g);
   if (st != GSW_OK) {
     free_graph(g);
     return st;

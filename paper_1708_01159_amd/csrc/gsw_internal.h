@@ -173,6 +173,9 @@ struct gsw_graph {
   unsigned long long* heavy = nullptr;
   int64_t n_heavy = -1;
   gsw::CcWorkspace* cc = nullptr; // connected components, allocated on first use
+  // gsw_bfs_noalloc's level records: mapped host memory, host and device view
+  // (graphs of up to GSW_NOALLOC_MAX_VERTICES)
+  unsigned long long *na_ring = nullptr, *d_na_ring = nullptr;
   hipStream_t stream = nullptr;   // library stream for this graph
   std::mutex mu;
 };
@@ -421,6 +424,18 @@ struct TreeBuf {
 int32_t specialise_tree(const gsw_graph* g, const gsw_tree* t, const TreeBuf& buf);
 BfsPolicy device_policy(const gsw_graph* g, const Workspace& w, const gsw_bfs_opts* o, bool has_origin,
                         bool has_rorigin);
+// One source: queues levels on s ahead of the records that the device posts to
+// w's ring, up to the search's last record.  Its outputs (and canonical
+// parents) are complete in stream order.
+struct SearchPolicy {
+  const gsw_bfs_opts* o;
+  bool has_origin;
+  bool has_rorigin;
+  bool hubs = false;  // sources of largest degree: no single-workgroup launch to begin with
+};
+gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso, const SearchPolicy& pol,
+                      const BfsPolicy& dp, int32_t src_idx, int32_t src, int32_t* lv, int32_t* pa,
+                      gsw_level_trace* trace, int32_t trace_cap, int32_t* rows, hipStream_t s);
 BfsBase make_base(const gsw_graph* g, const Workspace& w, int32_t* lv, int32_t* pa, bool timed, bool count_arcs);
 
 gsw_status ensure_workspace(gsw_graph* g);

@@ -2,14 +2,12 @@
 // allocate memory.  Every buffer its kernels need beyond the caller's graph,
 // levels and parents -- bitmaps, frontier queues, counters, level control,
 // push_edge scan arrays, the head copy of the in-arcs, the vertices without
-// in-arcs, the per-level records, the device copies of a tree or schedule --
-// lives in one file-scope device array of fixed size, laid out for graphs of
-// up to GSW_NOALLOC_MAX_VERTICES vertices.  The level kernels are the same as
-// gsw_bfs's; only the buffers and the host's reading of the level records
-// differ: the records go to device memory, and the host queues kBatch
-// launches at a time (single-workgroup multi-level launches are not used
-// here, so each launch completes at most one level), then copies those
-// levels' records back and waits.
+// in-arcs, the device copies of a tree or schedule -- lives in one file-scope
+// device array of fixed size, laid out for graphs of up to
+// GSW_NOALLOC_MAX_VERTICES vertices; the level records go to mapped host memory
+// that the graph was created with.  The search itself is gsw_bfs's, level
+// kernels and host loop: eight launches at a time with a copy of their records
+// and a wait in between cost a source 40 us more.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -30,7 +28,7 @@ constexpr size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Byte offsets of the regions inside the array, each 256-byte aligned.
 struct Layout {
-  size_t vis, bm[3], iso, ctl, done, q[2], ctr, actr, scan, ebeg, bsum, head, ring, tree, thr, sched, total;
+  size_t vis, bm[3], iso, ctl, done, q[2], ctr, actr, scan, ebeg, bsum, head, tree, sched, total;
 };
 
 constexpr Layout make_layout() {
@@ -57,9 +55,7 @@ constexpr Layout make_layout() {
   L.ebeg = take((size_t)kMaxN * sizeof(int64_t));
   L.bsum = take((size_t)((kMaxN + 1023) / 1024 + 1) * sizeof(int64_t));
   L.head = take((size_t)kMaxN * kHeadArcs * sizeof(int32_t));
-  L.ring = take((size_t)kBfsRing * kBfsRec * sizeof(unsigned long long));
-  L.tree = take((size_t)kMaxTree * sizeof(unsigned long long));
-  L.thr = take((size_t)kMaxTree * sizeof(int32_t));
+  L.tree = take((size_t)(kMaxTree + 1) * (sizeof(unsigned long long) + sizeof(int32_t)));
   L.sched = take((size_t)kMaxSched * sizeof(int32_t));
   L.total = at;
   return L;
@@ -84,13 +80,9 @@ DeviceScratch g_dev[kMaxDevices];
 // host-side tree buffers below are one per process.
 std::mutex g_mu;
 
-// Host buffers for specialising a tree (sized for the largest tree accepted)
-// and for the record ring's copy.
+// Host buffers for specialising a tree (sized for the largest tree accepted).
 int32_t h_order[kMaxTree], h_newid[kMaxTree], h_stack[kMaxTree + 1], h_thr[kMaxTree];
-unsigned long long h_nodes[kMaxTree];
-unsigned long long h_ring[(size_t)kBfsRing * kBfsRec];
-
-constexpr int kBatch = 8;  // launches queued before each read of the records
+unsigned long long h_nodes[kMaxTree + kMaxTree / 2 + 2];  // the thresholds follow the nodes for one upload
 
 gsw_status device_scratch(int device, DeviceScratch** out) {
   if (device < 0 || device >= kMaxDevices) return fail(GSW_EINVAL, "device %d out of range", device);
@@ -125,9 +117,7 @@ void scratch_workspace(unsigned char* base, int64_t n, Workspace* w) {
   w->head = reinterpret_cast<int32_t*>(base + kLayout.head);
   w->ctl = reinterpret_cast<BfsCtl*>(base + kLayout.ctl);
   w->done = reinterpret_cast<unsigned long long*>(base + kLayout.done);
-  w->d_ring = reinterpret_cast<unsigned long long*>(base + kLayout.ring);
   w->d_tree = reinterpret_cast<unsigned long long*>(base + kLayout.tree);
-  w->d_thr = reinterpret_cast<int32_t*>(base + kLayout.thr);
   w->d_sched = reinterpret_cast<int32_t*>(base + kLayout.sched);
 }
 
@@ -175,53 +165,6 @@ gsw_status check_options(const gsw_graph* g, const gsw_bfs_opts* o) {
   return GSW_OK;
 }
 
-// Copies the ring slots of levels d .. d + count - 1 into h_ring.
-gsw_status copy_records(const Workspace& w, int64_t d, int count, hipStream_t s) {
-  const size_t rec = (size_t)kBfsRec * sizeof(unsigned long long);
-  const int first = (int)(d % kBfsRing);
-  const int a = count < kBfsRing - first ? count : kBfsRing - first;
-  GSW_HIP(hipMemcpyAsync(h_ring + (size_t)first * kBfsRec, w.d_ring + (size_t)first * kBfsRec, (size_t)a * rec,
-                         hipMemcpyDeviceToHost, s));
-  if (count > a) GSW_HIP(hipMemcpyAsync(h_ring, w.d_ring, (size_t)(count - a) * rec, hipMemcpyDeviceToHost, s));
-  return GSW_OK;
-}
-
-// One source.  The records of the levels run by the launches queued so far
-// are all in the ring once the copy that follows them completes: each level
-// takes at least one launch, so kBatch launches post at most kBatch records.
-gsw_status run_source(gsw_graph* g, const Workspace& w, const gsw_bfs_opts* o, const BfsPolicy& dp,
-                      bool has_origin, bool has_rorigin, double tick_ms, int32_t src_idx, int32_t src,
-                      int32_t* lv, int32_t* pa, const unsigned long long* iso, gsw_level_trace* trace,
-                      int32_t trace_cap, int32_t* rows, hipStream_t s) {
-  const bool timed = o->time_levels == 1;
-  GSW_HIP(hipMemsetAsync(w.d_ring, 0, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long), s));
-  int32_t flags0 = 0;
-  const int k0 = first_kernel(g, o, has_origin, has_rorigin, &flags0);
-  const bool canonical = o->canonical_parents && pa;  // every parent is written afterwards
-  const BfsBase b = make_base(g, w, lv, canonical ? nullptr : pa, timed, o->count_arcs != 0);  // solo launches off
-  GSW_TRY(launch_init(g, b, iso, src, k0, flags0, s));
-  const int32_t cap = o->max_workgroups > 0 && o->max_workgroups < b.grid_max ? o->max_workgroups : b.grid_max;
-  int32_t j = 0;
-  for (int64_t d = 0;;) {
-    for (int i = 0; i < kBatch; ++i) GSW_TRY(launch_level_auto(g, b, dp, j++, cap, s));
-    GSW_TRY(copy_records(w, d, kBatch, s));
-    GSW_HIP(hipStreamSynchronize(s));
-    const int64_t d0 = d;
-    Record r;
-    bool ended = false;
-    while (!ended && d - d0 < kBatch && take_record(h_ring, d, &r)) {
-      if (trace && *rows < trace_cap) trace_row(&trace[*rows], src_idx, d, r, timed, tick_ms);
-      ++*rows;
-      ++d;
-      ended = r.next == 0;
-    }
-    if (ended) break;
-    if (d == d0) return fail(GSW_EHIP, "level %lld posted no record in %d launches", (long long)d, kBatch);
-  }
-  if (canonical) GSW_TRY(launch_canonical_parents(g, w, lv, pa, s));
-  return GSW_OK;
-}
-
 }  // namespace
 }  // namespace gsw
 
@@ -246,6 +189,9 @@ extern "C" gsw_status gsw_bfs_noalloc(const gsw_graph* cg, const int32_t* source
   const hipStream_t s = pick_stream(g, opts->stream);
   Workspace w;
   scratch_workspace(ds->ptr, g->n, &w);
+  w.ring = g->na_ring;
+  w.d_ring = g->d_na_ring;
+  w.tick_ms = ds->tick_ms;
   unsigned long long* iso = reinterpret_cast<unsigned long long*>(ds->ptr + kLayout.iso);
   // graph-derived buffers, rebuilt every call (the array is shared by every graph)
   GSW_TRY(launch_build_head(g, w.head, false, s));
@@ -255,8 +201,11 @@ extern "C" gsw_status gsw_bfs_noalloc(const gsw_graph* cg, const int32_t* source
     const int32_t m = specialise_tree(g, opts->tree, buf);
     if (m < 1) return fail(GSW_EINVAL, "tree could not be specialised to the graph");
     w.tree_nodes = m;
-    GSW_HIP(hipMemcpyAsync(w.d_tree, h_nodes, (size_t)m * sizeof(unsigned long long), hipMemcpyHostToDevice, s));
-    GSW_HIP(hipMemcpyAsync(w.d_thr, h_thr, (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    const size_t at = ((size_t)m + 1) & ~(size_t)1;  // 16-byte aligned
+    std::memcpy(h_nodes + at, h_thr, (size_t)m * sizeof(int32_t));
+    w.d_thr = reinterpret_cast<int32_t*>(w.d_tree + at);
+    GSW_HIP(hipMemcpyAsync(w.d_tree, h_nodes, at * sizeof(unsigned long long) + (size_t)m * sizeof(int32_t),
+                           hipMemcpyHostToDevice, s));
   } else if (opts->policy == GSW_POLICY_SCHEDULE) {
     GSW_HIP(hipMemcpyAsync(w.d_sched, opts->schedule, (size_t)opts->schedule_len * sizeof(int32_t),
                            hipMemcpyHostToDevice, s));
@@ -264,11 +213,11 @@ extern "C" gsw_status gsw_bfs_noalloc(const gsw_graph* cg, const int32_t* source
   const bool has_origin = g->origin != nullptr || g->nnz == 0;
   const bool has_rorigin = g->rorigin != nullptr || g->nnz == 0;
   const BfsPolicy dp = device_policy(g, w, opts, has_origin, has_rorigin);
+  const SearchPolicy pol{opts, has_origin, has_rorigin};
   int32_t rows = 0;
   for (int32_t i = 0; i < n_sources; ++i) {
-    const gsw_status st = run_source(g, w, opts, dp, has_origin, has_rorigin, ds->tick_ms, i, sources[i],
-                                     levels + (size_t)i * g->n, parents ? parents + (size_t)i * g->n : nullptr,
-                                     iso, trace, trace_cap, &rows, s);
+    const gsw_status st = run_levels(g, w, iso, pol, dp, i, sources[i], levels + (size_t)i * g->n,
+                                     parents ? parents + (size_t)i * g->n : nullptr, trace, trace_cap, &rows, s);
     if (st != GSW_OK) {
       (void)hipStreamSynchronize(s);
       return st;
