@@ -350,15 +350,18 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   // full-grid launch behind it, which runs whatever level it finds.  But where
   // the largest degree bounds the arcs, none is ever handed back, and there
   // such launches follow one another.
-  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, g->n, b.solo_nf) && !(pol.hubs && b.deg_max > kSoloArcs);
-  const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs;
+  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, b) &&
+              !(pol.hubs && b.deg_max > kSoloArcs && !solo_whole(b.n, b.nnz));
+  const bool whole = solo_whole(b.n, b.nnz);
+  const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs || whole;
   int64_t solo_j = -2;  // the latest such launch
   // The latest record is of a single-workgroup launch that went on: its other
   // records came with it, and only the last one says what to launch (a second
   // such launch behind it found nothing to do, 4-5 us).  Until then no more is
   // queued than the next level takes if it is the one handed back.
   bool in_solo = false;
-  int want = solo ? kSoloAhead + 1 : kAhead + level_launches(k0, 1) - 1;
+  int64_t first_d = 0, latest = 0;  // the latest record's launch and the first level it ran
+  int want = solo ? (whole ? 1 : kSoloAhead + 1) : kAhead + level_launches(k0, 1) - 1;
   const int32_t cap = o->max_workgroups > 0 && o->max_workgroups < b.grid_max ? o->max_workgroups : b.grid_max;
   int32_t size = cap;
   int64_t nf_prev = 0;  // frontier of the level before the latest record's
@@ -367,7 +370,7 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
     while (launched - consumed < want) {
       if (solo && (solo_always || solo_j + 1 < consumed)) {
         solo_j = launched;
-        const bool deep = d >= kSoloDeep;
+        const bool deep = d >= kSoloDeep || whole;
         b.solo = deep ? kSoloMaxLevels : kSoloLevels;
         GSW_TRY(launch_level_solo(g, b, dp, (int32_t)launched, deep || w.nw <= kSoloVisSmall, s));
       } else
@@ -392,9 +395,13 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
     if (r.launch + 1 > consumed) consumed = r.launch + 1;
     ++*rows;
     if (nn == 0) break;
-    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, g->n, b.solo_nf);
+    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, b);
     in_solo = solo && (r.flags & kFlagSolo) != 0;
-    want = in_solo ? level_launches(nk, nn) : solo ? kSoloAhead : kAhead + level_launches(nk, nn) - 1;
+    if (r.launch != latest) first_d = d;
+    latest = r.launch;
+    // (a whole graph's launch goes on to its level cap, and then nothing waits)
+    if (whole && solo) want = in_solo && d - first_d + 1 < kSoloMaxLevels ? 0 : 1;
+    else want = in_solo ? level_launches(nk, nn) : solo ? kSoloAhead : kAhead + level_launches(nk, nn) - 1;
     size = launch_size(nk, nn, r.nf, nf_prev, r.disc, d, g->n, cap);
     nf_prev = r.nf;
   }

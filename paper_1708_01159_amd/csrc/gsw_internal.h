@@ -306,6 +306,16 @@ constexpr int64_t kSoloArcs = 2048;
 constexpr int kSoloMaxLevels = 80;
 constexpr int32_t kSoloTree = 1024;  // such launches run with a tree of at most this many nodes
 constexpr int64_t kSoloVisWords = 16384;  // 64-bit words of a visited bitmap that LDS has room for
+// A graph so small that one workgroup runs its searches to the end, bottom-up
+// levels too, whatever the frontier and its arcs.  Measured, a search by the
+// tree in one workgroup and by level kernels: R-MAT of 1024 vertices and
+// 20990 arcs 37 and 85 us, 2048 random vertices and 31860 arcs 48 and 80, a
+// clique of 181 (32580 arcs) 29 and 33: more arcs per level than that, and one
+// compute unit loses.
+constexpr int64_t kSoloWholeArcs = 32768;
+__host__ __device__ inline bool solo_whole(long long n, long long nnz) {
+  return n <= kSoloMax && nnz <= kSoloWholeArcs;
+}
 // Frontiers of at most this many vertices qualify whatever the search's state.
 __host__ __device__ inline int32_t solo_frontier(long long n, long long nnz, int32_t deg_max) {
   const long long by_max = deg_max > 0 ? kSoloMaxArcs / deg_max : kSoloMax;
@@ -313,11 +323,11 @@ __host__ __device__ inline int32_t solo_frontier(long long n, long long nnz, int
   const long long f = by_max > by_avg ? by_max : by_avg;
   return (int32_t)(f < kSoloMax ? (f > 1 ? f : 1) : kSoloMax);
 }
-__host__ __device__ inline bool solo_eligible(int k, long long nn, long long nf, long long disc_next, long long n,
-                                              int32_t solo_nf) {
-  if (k < 0 || kernel_base(k) > GSW_K_PUSH_EDGE) return false;
-  if (nn < 1 || nn > kSoloMax) return false;
-  return nn <= solo_nf || (nn <= nf && disc_next * 100 >= n);
+__host__ __device__ inline bool solo_eligible(int k, long long nn, long long nf, long long disc_next, const BfsBase& b) {
+  if (k < 0 || nn < 1 || nn > kSoloMax) return false;
+  if (solo_whole(b.n, b.nnz)) return kernel_base(k) <= GSW_K_PULL_BITMAP;
+  if (kernel_base(k) > GSW_K_PUSH_EDGE) return false;
+  return nn <= b.solo_nf || (nn <= nf && disc_next * 100 >= b.n);
 }
 
 // A tree node in 8 bytes for the device walk: left and right child (int16,

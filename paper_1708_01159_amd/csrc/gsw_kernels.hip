@@ -1662,6 +1662,8 @@ struct SoloLds {
   uint32_t nlong[3]; // long rows set aside
   int32_t go;        // wave 0's decision: the next level runs here
   int32_t next, nflags, disc;  // ... else its kernel and flags, and the vertices discovered
+  int32_t pull;      // (whole graph) the next level is bottom-up
+  uint32_t fr[kSoloMax / 32];  // (whole graph) the frontier's bitmap in such a level
   // of level lv of this launch, for its record
   int32_t r_kernel[kSoloMaxLevels + 1], r_flags[kSoloMaxLevels + 1], r_nf[kSoloMaxLevels + 1];
   int32_t r_disc[kSoloMaxLevels + 1];
@@ -1858,9 +1860,96 @@ __device__ __forceinline__ void solo_copy(u64* dst, const u64* src, int32_t n) {
   }
 }
 
+// The in-arcs of a thread's vertices, for bottom-up levels of a whole graph.
+struct SoloIn {
+  int64_t beg[kSoloSlots];
+  int32_t deg[kSoloSlots];
+  int4 head[kSoloSlots];
+};
+
+// Bottom-up level of a graph of at most kSoloMax vertices: every thread has
+// the same kSoloSlots vertices, with the bounds and first arcs of their rows,
+// in every level, and looks for its unvisited ones' first in-neighbour in the
+// frontier's LDS bitmap, kSoloShort arcs at a time past the head; when only
+// kSoloFew of a wave's rows go on, the wave goes through those together.
+constexpr int kSoloFew = 4;
+__device__ __forceinline__ void solo_pull(const BfsBase& b, SoloLds<true>& L, int32_t d, int slot, int nxt,
+                                          const int32_t* list, int32_t nf, const SoloIn& in) {
+  const int tid = threadIdx.x, lane = lane_id();
+  if (tid < kSoloMax / 32) L.fr[tid] = 0u;
+  lds_barrier();
+  for (int32_t i = tid; i < nf; i += kSoloBlock) atomicOr(&L.fr[list[i] >> 5], 1u << (list[i] & 31));
+  lds_barrier();
+  int32_t par[kSoloSlots];
+  bool want[kSoloSlots];
+  auto hit = [&](int32_t u) { return u >= 0 && ((L.fr[u >> 5] >> (u & 31)) & 1u); };
+  const int32_t from = b.head_ranked ? 0 : kHeadArcs;
+#pragma unroll
+  for (int q = 0; q < kSoloSlots; ++q) {
+    const int32_t v = tid + q * kSoloBlock;
+    par[q] = -1;
+    want[q] = v < (int32_t)b.n && !((L.vis[v >> 5] >> (v & 31)) & 1u);
+    if (want[q]) {
+      const int4 h = in.head[q];
+      par[q] = hit(h.x) ? h.x : hit(h.y) ? h.y : hit(h.z) ? h.z : hit(h.w) ? h.w : -1;
+    }
+    want[q] = want[q] && par[q] < 0 && in.deg[q] > from && in.deg[q] > kHeadArcs;
+  }
+#pragma unroll
+  for (int q = 0; q < kSoloSlots; ++q) {
+    int32_t off = from;
+    u64 rest = __ballot(want[q]);
+    while (__popcll(rest) > kSoloFew) {
+      if (want[q]) {
+        int32_t u[kSoloShort];
+#pragma unroll
+        for (int k = 0; k < kSoloShort; ++k) u[k] = off + k < in.deg[q] ? b.rcols[in.beg[q] + off + k] : -1;
+#pragma unroll
+        for (int k = kSoloShort - 1; k >= 0; --k)
+          if (hit(u[k])) par[q] = u[k];
+      }
+      off += kSoloShort;
+      want[q] = want[q] && par[q] < 0 && off < in.deg[q];
+      rest = __ballot(want[q]);
+    }
+    while (rest != 0ull) {
+      const int owner = __ffsll((long long)rest) - 1;
+      rest &= rest - 1ull;
+      const int64_t beg = __shfl(in.beg[q], owner);
+      const int32_t deg = __shfl(in.deg[q], owner);
+      int32_t found = -1;
+      for (int32_t e = off; found < 0 && e < deg; e += 64) {
+        const int32_t x = e + lane < deg ? b.rcols[beg + e + lane] : -1;
+        const u64 m = __ballot(hit(x));
+        const int32_t y = __shfl(x, m != 0ull ? __ffsll((long long)m) - 1 : 0);
+        if (m != 0ull) found = y;
+      }
+      if (lane == owner) par[q] = found;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kSoloSlots; ++q) {
+    const int32_t v = tid + q * kSoloBlock;
+    const bool win = par[q] >= 0;
+    const u64 m = __ballot(win);
+    if (m == 0ull) continue;
+    uint32_t at = 0u;
+    if (lane == 0) at = atomicAdd(&L.cnt[slot], (uint32_t)__popcll(m));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(m & lanes_below(lane));
+    if (win) {
+      atomicOr(&L.vis[v >> 5], 1u << (v & 31));
+      L.q[nxt][at] = v;
+      b.level[v] = d + 1;
+      if (b.parent) b.parent[v] = par[q];
+    }
+  }
+}
+
 // LdsVis: the visited bitmap in LDS.  HeadOnly: every row is its head record
-// (head_rows, at most kHeadArcs arcs a row, arcs not counted).
-template <bool LdsVis, bool HeadOnly>
+// (head_rows, at most kHeadArcs arcs a row, arcs not counted).  Whole: a graph
+// of at most kSoloMax vertices and kSoloWholeArcs arcs: any frontier and its
+// arcs are taken, and bottom-up levels too.
+template <bool LdsVis, bool HeadOnly, bool Whole = false>
 __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy p, int32_t j) {
   __shared__ SoloLds<LdsVis> L;
   const int tid = threadIdx.x;
@@ -1873,7 +1962,8 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   int32_t d = c->d;
   int32_t prev = c->prev, flags = c->flags;
   const bool tree = p.policy == GSW_POLICY_TREE;
-  const bool ok = b.solo > 0 && k_id >= 0 && k_id < GSW_N_KERNELS && kernel_base(k_id) <= GSW_K_PUSH_EDGE &&
+  constexpr int last_base = Whole ? GSW_K_PULL_BITMAP : GSW_K_PUSH_EDGE;  // (the kernels it runs come first)
+  const bool ok = b.solo > 0 && k_id >= 0 && k_id < GSW_N_KERNELS && kernel_base(k_id) <= last_base &&
                   c->nf >= 1 && c->nf <= kSoloMax;
   if (!ok) {  // not a level for this launch: the slot passes on unchanged
     if (tid == 0) *cn = *c;
@@ -1899,7 +1989,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   LeafBox box{0, p.policy == GSW_POLICY_FIXED ? 0x7fffffff : 0, 0, 0x7fffffff, p.fixed};
   int32_t leaf_next = 0, leaf_flags = 0;  // its kernel (a tied leaf: this level's) and trace flags
   if (p.policy == GSW_POLICY_FIXED) leaf_next = choose_leaf(p, p.fixed, k_id, &leaf_flags);
-  bool leaf_push = kernel_base(leaf_next) <= GSW_K_PUSH_EDGE;  // ... which may go on here
+  bool leaf_push = kernel_base(leaf_next) <= last_base;  // ... which may go on here
   // frontiers whose arcs the largest degree bounds
   const int32_t bound_arcs = b.deg_max > 0 ? (int32_t)(kSoloMaxArcs / b.deg_max) : (int32_t)kSoloMax;
   const int32_t levels_max = b.solo;
@@ -1936,8 +2026,24 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   };
   // the first frontier, binned as the level kernel left it, into LDS
   for (int32_t i = tid; i < nf; i += kSoloBlock) L.q[0][i] = solo_queue_binned(b, d, L.qi, (uint32_t)i);
+  SoloIn in;
+  if constexpr (Whole) {
+#pragma unroll
+    for (int q = 0; q < kSoloSlots; ++q) {
+      const int32_t x = tid + q * kSoloBlock;
+      in.beg[q] = 0;
+      in.deg[q] = 0;
+      in.head[q] = make_int4(-1, -1, -1, -1);
+      if (x < (int32_t)b.n) {
+        in.beg[q] = b.roffs[x];
+        in.deg[q] = (int32_t)(b.roffs[x + 1] - in.beg[q]);
+        in.head[q] = reinterpret_cast<const int4*>(b.head)[x];
+      }
+    }
+  }
   __syncthreads();
   fetch(L.q[0], nf);
+  bool pull = Whole && kernel_base(k_id) == GSW_K_PULL_BITMAP;
   u64 t0 = b.timed ? (u64)wall_clock64() : 0ull;
   for (int lv = 0;; ++lv) {
     const int cur = lv & 1, nxt = cur ^ 1, slot1 = slot == 2 ? 0 : slot + 1;
@@ -1947,11 +2053,11 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       L.nlong[slot1] = 0u;
     }
     bool lng[kSoloSlots] = {};
-    const bool check = !HeadOnly && nf > bound_arcs;
+    const bool check = !HeadOnly && !Whole && nf > bound_arcs;
     if (!HeadOnly && wid * 64 < nf) {
       // rows set aside while there is room, else walked by their thread; the
       // level's arcs where they have to be known
-      if (b.deg_max > kSoloShort) {
+      if (b.deg_max > kSoloShort && !pull) {
 #pragma unroll
         for (int q = 0; q < kSoloSlots; ++q) {
           const int64_t deg = end[q] - beg[q];
@@ -1960,7 +2066,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
             if (at < (uint32_t)kSoloLong) {
               L.lu[at] = u[q];
               L.lbeg[at] = beg[q];
-              L.lpre[at] = (int32_t)(deg < kSoloMaxArcs ? deg : kSoloMaxArcs + 1);
+              L.lpre[at] = (int32_t)(Whole || deg < kSoloMaxArcs ? deg : kSoloMaxArcs + 1);
               lng[q] = true;
             }
           }
@@ -1976,7 +2082,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       }
     }
     uint32_t nlong = 0u;
-    if (!HeadOnly && (check || b.deg_max > kSoloShort)) {
+    if (!HeadOnly && !pull && (check || b.deg_max > kSoloShort)) {
       lds_barrier();
       nlong = L.nlong[slot] < (uint32_t)kSoloLong ? L.nlong[slot] : (uint32_t)kSoloLong;
       if (check && L.esum[slot] > (u64)kSoloArcs) {
@@ -2004,6 +2110,8 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       if (!c->clean)
         for (int64_t i = tid; i < b.nw; i += kSoloBlock) b.bm[(d + 2) % 3][i] = 0ull;
     }
+    if constexpr (Whole)
+      if (pull) solo_pull(b, L, d, slot, nxt, L.q[cur], nf, in);
     if constexpr (HeadOnly) {
       for (int k0 = 0; k0 * kSoloRows + wid * (64 / kHeadArcs) < nf; k0 += kSoloPasses) {
         if (k0 > 0) solo_heads_fetch(b.head, L.q[cur], k0, nf, u, v);
@@ -2015,7 +2123,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
         else
           solo_heads_visit<kSoloPasses, LdsVis>(b, L, d, slot, nxt, u, v);
       }
-    } else if (wid * 64 < nf) {
+    } else if (!pull && wid * 64 < nf) {
       // rows not set aside, four arcs of a slot in flight together
 #pragma unroll
       for (int q = 0; q < kSoloSlots; ++q) {
@@ -2090,14 +2198,15 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
           box.leaf = p.sched[d + 1 < p.sched_len ? d + 1 : p.sched_len - 1];
         }
         leaf_next = choose_leaf(p, box.leaf, k_id, &leaf_flags);
-        leaf_push = kernel_base(leaf_next) <= GSW_K_PUSH_EDGE;
+        leaf_push = kernel_base(leaf_next) <= last_base;
       }
       // (solo_eligible, with the kernel's part of it decided above)
       const bool go = lv + 1 < levels_max && nn > 0 && leaf_push &&
-                      (nn <= b.solo_nf || (nn <= (int32_t)kSoloMax && nn <= nf && (long long)ndisc * 100 >= b.n));
+                      (Whole || nn <= b.solo_nf || (nn <= (int32_t)kSoloMax && nn <= nf && (long long)ndisc * 100 >= b.n));
       const int32_t next = nn > 0 ? leaf_next : kCtlDone, nflags = nn > 0 ? leaf_flags : 0;
       if (tid == 0) {
         L.go = go ? 1 : 0;
+        if (Whole) L.pull = kernel_base(leaf_next) == GSW_K_PULL_BITMAP ? 1 : 0;
         if (!go) {
           L.next = next;
           L.nflags = nflags;
@@ -2121,6 +2230,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     }
     lds_barrier();
     const bool go = __builtin_amdgcn_readfirstlane(L.go) != 0;
+    if (Whole) pull = __builtin_amdgcn_readfirstlane(L.pull) != 0;
     levels = lv + 1;
     ++d;
     nf = nn;
@@ -2449,7 +2559,8 @@ gsw_status launch_level_solo(const gsw_graph* g, const BfsBase& b, const BfsPoli
   const bool vis = lds_vis && b.nw <= kSoloVisWords;
   const bool head_only = b.head_rows && b.deg_max <= kHeadArcs && !b.count_arcs;
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(kSoloBlock), 0, s, b, p, j); };
-  if (vis && head_only) launch(k_level_solo<true, true>);
+  if (solo_whole(b.n, b.nnz)) launch(k_level_solo<true, false, true>);
+  else if (vis && head_only) launch(k_level_solo<true, true>);
   else if (vis) launch(k_level_solo<true, false>);
   else if (head_only) launch(k_level_solo<false, true>);
   else launch(k_level_solo<false, false>);

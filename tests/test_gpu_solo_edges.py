@@ -129,3 +129,48 @@ def test_solo_start_of_a_search_at_its_arc_limit(children, leaves):
                 assert [t.n_frontier for t in tr] == sizes.tolist()
                 assert not any(t.flags & SOLO and t.e_frontier > 8192 for t in tr)
     G.close()
+
+
+def _tiny_graphs():
+    path = gg.from_edges(2048, list(range(2047)), list(range(1, 2048)), name="path2048")
+    hub = gg.from_edges(2048, [0] * 2047 + [1] * 2000, list(range(1, 2048)) + list(range(2, 2002)), name="hubs")
+    ragged = gg.rmat(10, 14, seed=91)
+    a = gg.rmat(10, 8, seed=92)
+    rows = np.repeat(np.arange(a.n), a.degrees())
+    keep = np.random.default_rng(5).random(a.nnz) < 0.6
+    directed = gg.from_edges(a.n, rows[keep], a.cols[keep], symmetrize=False, name="dir")
+    clique = gg.from_edges(181, np.repeat(np.arange(181), 181), np.tile(np.arange(181), 181), name="clique")  # 32580 arcs
+    over = gg.from_edges(182, np.repeat(np.arange(182), 182), np.tile(np.arange(182), 182), name="over")  # 32942
+    wide = gg.from_edges(2049, list(range(2048)), list(range(1, 2049)), name="path2049")
+    lone = gg.from_edges(1, [], [], name="one")
+    return {g.name if g.name != "rmat" else "rmat10": g for g in (path, hub, directed, clique, over, wide, lone)} | {
+        "ragged": ragged}
+
+
+@pytest.mark.parametrize("name", ["path2048", "hubs", "dir", "clique", "over", "path2049", "one", "ragged"])
+def test_whole_graph_in_one_workgroup(name):
+    """Graphs on both sides of what one workgroup searches to the end: every
+    kernel it runs, bottom-up included, schedules that leave and come back."""
+    g = _tiny_graphs()[name]
+    G = gsw.Graph.from_csr(g.offs, g.cols, flags=gsw.WITH_ORIGIN)
+    srcs = sorted({0, g.n // 2, g.n - 1})
+    refs = [oracle.levels(g.offs, g.cols, s) for s in srcs]
+    check = checks.check_bfs if G.symmetric else checks.check_bfs_directed
+    scheds = [[gsw.PULL_BITMAP], [gsw.PUSH_VERTEX, gsw.PULL_BITMAP], [gsw.PULL_BITMAP, gsw.PUSH_EDGE] * 60,
+              [gsw.PUSH_EDGE, gsw.VERTEX_SCAN, gsw.PULL_BITMAP, gsw.PUSH_WAVE8, gsw.REV_EDGE_SCAN] * 20 + [gsw.PULL_BITMAP]]
+    for kw in [dict(policy="fixed", kernel=k) for k in (gsw.PULL_BITMAP, gsw.PUSH_EDGE,
+                                                        gsw.kernel_id(gsw.PULL_BITMAP, gsw.COUNT_WAVE))] + \
+              [dict(policy="schedule", schedule=np.array(s, dtype=np.int32)) for s in scheds] + \
+              [dict(policy="tree", tree=_wide_tree(6))]:
+        for extra in (dict(), dict(count_arcs=True), dict(time_levels=True)):
+            lv, pa, tr = gsw.bfs(G, srcs, trace_cap=8192, **kw, **extra)
+            lv0, _, tr0 = gsw.bfs(G, srcs, trace_cap=8192, solo=False, **kw, **extra)
+            assert [(t.source_idx, t.level, t.kernel, t.flags & ~SOLO, t.n_frontier, t.discovered, t.n_next, t.e_frontier)
+                    for t in tr] == [(t.source_idx, t.level, t.kernel, t.flags, t.n_frontier, t.discovered, t.n_next,
+                                      t.e_frontier) for t in tr0]
+            for i, s in enumerate(srcs):
+                assert np.array_equal(lv[i], refs[i]) and np.array_equal(lv0[i], refs[i])
+                check(g.offs, g.cols, s, lv[i], pa[i])
+            if kw.get("kernel") == gsw.PULL_BITMAP and len(tr):
+                assert all(bool(t.flags & SOLO) == (name not in ("over", "path2049")) for t in tr)
+    G.close()
