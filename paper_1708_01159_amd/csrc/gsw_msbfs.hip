@@ -51,7 +51,10 @@ typedef unsigned long long u64;
 
 constexpr int kMsBlock = 256;     // workgroup size of the helper kernels, default of the level kernels
 constexpr int kMsMaxBlock = 512;  // level kernels: 128, 256 or 512 threads (gsw_msbfs_opts.block_size)
-constexpr int kMsMaxWaves = 16384; // level kernels: wavefronts per launch at most
+// Level kernels: wavefronts per launch at most, two full loads of the chip at
+// six a SIMD (16384 were 2% slower on R-MAT scale 20 and no faster on a
+// random graph of 700001 vertices).
+constexpr int kMsMaxWaves = 12288;
 constexpr int kMsFinal = 1024;    // threads of the level's last kernel: one per source slot
 constexpr int kMsStats = 8;        // stat counters, spread like the queue bins
 constexpr int kMsStatStride = 32;  // u64 words between counters
@@ -586,8 +589,14 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
 // whole.  Also accumulates the level's statistics: vertices with new bits and
 // their degrees, per source the degree sum of its new frontier (each source's
 // direction is steered by it), and the OR of the new frontier masks.
+// What bounds it from four mask words up is latency, a group's arcs one after
+// another, so six waves a SIMD (80 VGPRs, 68 bytes spilled) beat the four that
+// 98 VGPRs allow: 1000 sources on R-MAT scale 20 3.63 -> 3.20 ms, 200 on a
+// random graph of 700001 vertices 1.39 -> 1.23.  With one or two words a lane
+// walks rows itself, eight arcs in flight, and needs the registers (64 sources:
+// 0.58 ms, 0.65 at six).
 template <int G>
-__global__ void __launch_bounds__(kMsMaxBlock) k_ms_level(MsArgs a) {
+__global__ void __launch_bounds__(kMsMaxBlock, G >= 4 ? 6 : 4) k_ms_level(MsArgs a) {
   __shared__ u64 s_ef[kMaxSlots];
   const Wave<G> w;
   const int j = w.j;
