@@ -303,9 +303,16 @@ constexpr int64_t kSoloMax = 2048;
 static_assert(kSoloMax <= (int64_t)kSoloBlock * kSoloSlots, "every frontier entry has a thread slot");
 constexpr int64_t kSoloMaxArcs = 8192;
 constexpr int64_t kSoloArcs = 2048;
+constexpr int32_t kSoloFewRows = 16;
 constexpr int kSoloMaxLevels = 80;
 constexpr int32_t kSoloTree = 1024;  // such launches run with a tree of at most this many nodes
 constexpr int64_t kSoloVisWords = 16384;  // 64-bit words of a visited bitmap that LDS has room for
+// Counted arcs that one workgroup takes: more of a lane-per-row kernel's level
+// of few rows, which the level kernel would leave to one of its workgroups or
+// to a few (a row of 4579 arcs: 26 us there, 11 here; of 2446 arcs 13 and 6).
+__host__ __device__ inline int32_t solo_arc_limit(int k, int32_t nf) {
+  return kernel_base(k) != GSW_K_PUSH_EDGE && nf <= kSoloFewRows ? (int32_t)kSoloMaxArcs : (int32_t)kSoloArcs;
+}
 // A graph so small that one workgroup runs its searches to the end, bottom-up
 // levels too, whatever the frontier and its arcs.  Measured, a search by the
 // tree in one workgroup and by level kernels: R-MAT of 1024 vertices and

@@ -1662,6 +1662,7 @@ struct SoloLds {
   uint32_t nlong[3]; // long rows set aside
   int32_t go;        // wave 0's decision: the next level runs here
   int32_t next, nflags, disc;  // ... else its kernel and flags, and the vertices discovered
+  int32_t limit;     // arcs the next level may have where they are counted
   int32_t pull;      // (whole graph) the next level is bottom-up
   uint32_t fr[kSoloMax / 32];  // (whole graph) the frontier's bitmap in such a level
   // of level lv of this launch, for its record
@@ -1992,6 +1993,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   bool leaf_push = kernel_base(leaf_next) <= last_base;  // ... which may go on here
   // frontiers whose arcs the largest degree bounds
   const int32_t bound_arcs = b.deg_max > 0 ? (int32_t)(kSoloMaxArcs / b.deg_max) : (int32_t)kSoloMax;
+  int32_t limit = solo_arc_limit(k_id, nf);
   const int32_t levels_max = b.solo;
   int levels = 0;  // completed here
   int slot = 0;
@@ -2085,7 +2087,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     if (!HeadOnly && !pull && (check || b.deg_max > kSoloShort)) {
       lds_barrier();
       nlong = L.nlong[slot] < (uint32_t)kSoloLong ? L.nlong[slot] : (uint32_t)kSoloLong;
-      if (check && L.esum[slot] > (u64)kSoloArcs) {
+      if (check && L.esum[slot] > (u64)limit) {
         // too many arcs for one workgroup: the level goes back to the level
         // kernel untouched (on the first level nothing has changed at all)
         if (lv == 0) {
@@ -2206,6 +2208,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       const int32_t next = nn > 0 ? leaf_next : kCtlDone, nflags = nn > 0 ? leaf_flags : 0;
       if (tid == 0) {
         L.go = go ? 1 : 0;
+        if (!HeadOnly && !Whole) L.limit = solo_arc_limit(leaf_next, nn);
         if (Whole) L.pull = kernel_base(leaf_next) == GSW_K_PULL_BITMAP ? 1 : 0;
         if (!go) {
           L.next = next;
@@ -2230,6 +2233,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     }
     lds_barrier();
     const bool go = __builtin_amdgcn_readfirstlane(L.go) != 0;
+    if (!HeadOnly && !Whole) limit = L.limit;
     if (Whole) pull = __builtin_amdgcn_readfirstlane(L.pull) != 0;
     levels = lv + 1;
     ++d;

@@ -174,3 +174,31 @@ def test_whole_graph_in_one_workgroup(name):
             if kw.get("kernel") == gsw.PULL_BITMAP and len(tr):
                 assert all(bool(t.flags & SOLO) == (name not in ("over", "path2049")) for t in tr)
     G.close()
+
+
+@pytest.mark.parametrize("arcs", [2048, 2049, 8192, 8193])
+def test_solo_rows_that_a_level_kernel_leaves_to_one_workgroup(arcs):
+    """A level of few long rows: counted arcs up to 8192 for the lane-per-row
+    kernels, up to 2048 for push_edge; 16 rows and 17 at the next level."""
+    for rows in (16, 17):
+        src, dst = [0] * arcs, list(range(1, arcs + 1))
+        nv = arcs + 1
+        for c in range(1, rows + 1):  # below a second root: rows of 200 arcs
+            src.append(nv), dst.append(nv + c)
+        for c in range(1, rows + 1):
+            src.extend([nv + c] * 200), dst.extend(range(nv + rows + 1 + 200 * c, nv + rows + 201 + 200 * c))
+        n = nv + rows + 201 + 200 * rows + 20000  # (isolated vertices: the average degree stays low)
+        g = gg.from_edges(n, src, dst, name="rows")
+        G = gsw.Graph.from_csr(g.offs, g.cols)
+        for s in (0, nv):
+            ref = oracle.levels(g.offs, g.cols, s)
+            for kernel in (gsw.PUSH_VERTEX, gsw.PUSH_WAVE16, gsw.PUSH_EDGE):
+                lv, pa, tr = gsw.bfs(G, [s], policy="fixed", kernel=kernel, count_arcs=True)
+                assert np.array_equal(lv[0], ref)
+                checks.check_bfs(g.offs, g.cols, s, lv[0], pa[0])
+                few = kernel != gsw.PUSH_EDGE
+                for t in tr[:2]:
+                    if t.n_frontier <= 17 and t.n_frontier * int(g.degrees().max()) > 8192:
+                        limit = 8192 if few and t.n_frontier <= 16 else 2048
+                        assert bool(t.flags & SOLO) == (t.e_frontier <= limit), (s, kernel, t)
+        G.close()
