@@ -298,7 +298,8 @@ gsw_status ensure_workspace(gsw_graph* g) {
   if (!w.head_built) {
     const bool ranked = head_ranking_pays(g);
     if (n > 0) {
-      GSW_TRY(launch_build_head(g, w.head, ranked, g->stream));
+      // (the first queue is free until the first search: it holds the degrees)
+      GSW_TRY(launch_build_head(g, w.head, ranked ? w.q[0] : nullptr, g->stream));
       GSW_HIP(hipStreamSynchronize(g->stream));
     }
     w.head_built = true;

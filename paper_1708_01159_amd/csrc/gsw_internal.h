@@ -407,8 +407,8 @@ gsw_status launch_canonical_parents(const gsw_graph* g, const Workspace& w, cons
 gsw_status launch_build_origin(const int64_t* offs, int64_t n, int32_t* origin, hipStream_t s);
 // Whether the single-source workspace ranks the head (out-degree standard deviation above the mean).
 bool head_ranking_pays(const gsw_graph* g);
-// ranked: the kHeadArcs in-neighbours of largest out-degree (see kHeadArcs), else the first ones.
-gsw_status launch_build_head(const gsw_graph* g, int32_t* head, bool ranked, hipStream_t s);
+// deg (room for n): the kHeadArcs in-neighbours of largest out-degree (see kHeadArcs); null: the first ones.
+gsw_status launch_build_head(const gsw_graph* g, int32_t* head, int32_t* deg, hipStream_t s);
 
 // ----- pieces of the single-source level loop (gsw_bfs.cpp)
 // A level's record, decoded.

@@ -2333,34 +2333,110 @@ __global__ void __launch_bounds__(kBlock) k_build_head(const int64_t* __restrict
   }
 }
 
+// Out-degrees in 4 bytes, for the gathers of the next kernel.
+__global__ void __launch_bounds__(kBlock) k_head_degrees(const int64_t* __restrict__ offs, int32_t* __restrict__ deg,
+                                                         int64_t n) {
+  for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n; v += (int64_t)gridDim.x * kBlock) {
+    const int64_t d = offs[v + 1] - offs[v];
+    deg[v] = d < 0x7fffffff ? (int32_t)d : 0x7fffffff;
+  }
+}
+
 // The ranked head: per vertex (rows of in-arcs), the four in-neighbours of
 // largest out-degree among the row's first kHeadScan arcs, in decreasing
-// degree (an earlier arc first among equal degrees), -1 padded.
+// degree (an earlier arc first among equal degrees), -1 padded.  An arc's key
+// is its neighbour's degree above its position counted down, so the largest
+// keys are the head.  A row of up to four arcs is sorted by its lane; a longer
+// one goes to kHeadGroup lanes of the wave, each of which keeps the four
+// largest keys of its arcs (kBatch in flight), and the group draws the
+// largest of its lanes' first keys four times.  Bound by the gathers of the
+// degrees: R-MAT scale 22, 8 + 630 us (a lane per row, arc after arc: 3.0 ms).
+constexpr int kHeadGroup = 16;
+
+// keys in decreasing order; k joins them, the smallest leaves
+__device__ __forceinline__ void head_insert(u64 (&top)[kHeadArcs], u64 k) {
+#pragma unroll
+  for (int i = 0; i < kHeadArcs; ++i) {
+    const u64 lo = k < top[i] ? k : top[i];
+    top[i] = k < top[i] ? top[i] : k;
+    k = lo;
+  }
+}
+
+__device__ __forceinline__ u64 head_key(int32_t deg, int32_t pos) {
+  return ((u64)(uint32_t)deg << 32) | (u64)(0xffffffffu - (uint32_t)pos);
+}
+
 __global__ void __launch_bounds__(kBlock) k_build_head_ranked(const int64_t* __restrict__ roffs,
                                                               const int32_t* __restrict__ rcols,
-                                                              const int64_t* __restrict__ offs,
-                                                              int4* __restrict__ head, int64_t n) {
-  static_assert(kHeadArcs == 4, "one int4 record per row");
-  for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n; v += (int64_t)gridDim.x * kBlock) {
-    const int64_t beg = roffs[v], deg = roffs[v + 1] - beg;
-    const int64_t lim = deg < kHeadScan ? deg : kHeadScan;
-    int32_t id[4] = {-1, -1, -1, -1};
-    int64_t dg[4] = {-1, -1, -1, -1};
-    for (int64_t e = 0; e < lim; ++e) {
-      const int32_t u = rcols[beg + e];
-      const int64_t du = offs[u + 1] - offs[u];
-      if (du > dg[3]) {  // insertion into the four largest so far
-        int k = 3;
-        while (k > 0 && du > dg[k - 1]) {
-          dg[k] = dg[k - 1];
-          id[k] = id[k - 1];
-          --k;
-        }
-        dg[k] = du;
-        id[k] = u;
-      }
+                                                              const int32_t* __restrict__ deg,
+                                                              int32_t* __restrict__ head, int64_t n) {
+  static_assert(kHeadArcs == 4 && kHeadScan >= kHeadArcs, "one int4 record per row");
+  const int lane = lane_id();
+  const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+  for (int64_t v0 = (((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6) * 64; v0 < n; v0 += nwaves * 64) {
+    const int64_t v = v0 + lane;
+    int64_t beg = 0;
+    int32_t len = 0;
+    if (v < n) {
+      beg = roffs[v];
+      const int64_t d = roffs[v + 1] - beg;
+      len = d < kHeadScan ? (int32_t)d : kHeadScan;
     }
-    head[v] = make_int4(id[0], id[1], id[2], id[3]);
+    const bool longer = len > kHeadArcs;
+    if (v < n && !longer) {
+      int32_t id[kHeadArcs];
+      u64 top[kHeadArcs] = {};
+#pragma unroll
+      for (int q = 0; q < kHeadArcs; ++q) id[q] = q < len ? rcols[beg + q] : -1;
+#pragma unroll
+      for (int q = 0; q < kHeadArcs; ++q) head_insert(top, id[q] >= 0 ? head_key(deg[id[q]], q) : 0ull);
+      int32_t out[kHeadArcs];
+#pragma unroll
+      for (int q = 0; q < kHeadArcs; ++q) {
+        const int32_t pos = (int32_t)(0xffffffffu - (uint32_t)top[q]);
+        out[q] = top[q] == 0ull ? -1 : pos == 0 ? id[0] : pos == 1 ? id[1] : pos == 2 ? id[2] : id[3];
+      }
+      reinterpret_cast<int4*>(head)[v] = make_int4(out[0], out[1], out[2], out[3]);
+    }
+    const u64 rows = __ballot(longer);
+    const int nrows = __popcll(rows);
+    const int sub = lane & (kHeadGroup - 1);
+    for (int r = 0; r < nrows; r += 64 / kHeadGroup) {
+      const int k = r + lane / kHeadGroup;
+      const bool on = k < nrows;
+      const int own = on ? nth_set_bit(rows, k) : 0;
+      const int64_t b0 = __shfl(beg, own);
+      const int32_t len_own = __shfl(len, own), len0 = on ? len_own : 0;
+      u64 top[kHeadArcs] = {};
+      for (int32_t e = sub; __any(e < len0); e += kHeadGroup * kBatch) {
+        int32_t u[kBatch], du[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) u[q] = e + q * kHeadGroup < len0 ? rcols[b0 + e + q * kHeadGroup] : -1;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) du[q] = u[q] >= 0 ? deg[u[q]] : 0;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+          if (__any(u[q] >= 0)) head_insert(top, u[q] >= 0 ? head_key(du[q], e + q * kHeadGroup) : 0ull);
+      }
+      int32_t mine = -1;  // the position that lane `sub` of the group writes
+#pragma unroll
+      for (int i = 0; i < kHeadArcs; ++i) {
+        u64 best = top[0];
+#pragma unroll
+        for (int off = 1; off < kHeadGroup; off <<= 1) {
+          const u64 y = __shfl_xor(best, off);
+          best = y > best ? y : best;
+        }
+        if (top[0] == best) {  // (keys differ: one lane, or all of an empty group)
+#pragma unroll
+          for (int q = 0; q + 1 < kHeadArcs; ++q) top[q] = top[q + 1];
+          top[kHeadArcs - 1] = 0ull;
+        }
+        if (sub == i) mine = (int32_t)(0xffffffffu - (uint32_t)best);
+      }
+      if (on && sub < kHeadArcs) head[(v0 + own) * kHeadArcs + sub] = rcols[b0 + mine];
+    }
   }
 }
 
@@ -2581,10 +2657,13 @@ gsw_status launch_level_auto(const gsw_graph* g, const BfsBase& b, const BfsPoli
   return GSW_OK;
 }
 
-gsw_status launch_build_head(const gsw_graph* g, int32_t* head, bool ranked, hipStream_t s) {
-  if (ranked)
-    hipLaunchKernelGGL(k_build_head_ranked, dim3(persistent_grid(cdiv(g->n, kBlock))), dim3(kBlock), 0, s,
-                       g->roffs, g->rcols, g->offs, reinterpret_cast<int4*>(head), g->n);
+gsw_status launch_build_head(const gsw_graph* g, int32_t* head, int32_t* deg, hipStream_t s) {
+  if (deg) {
+    hipLaunchKernelGGL(k_head_degrees, dim3(persistent_grid(cdiv(g->n, kBlock))), dim3(kBlock), 0, s, g->offs, deg,
+                       g->n);
+    hipLaunchKernelGGL(k_build_head_ranked, dim3((unsigned)cdiv(g->n, kBlock)), dim3(kBlock), 0, s, g->roffs,
+                       g->rcols, (const int32_t*)deg, head, g->n);
+  }
   else
     hipLaunchKernelGGL(k_build_head, dim3(persistent_grid(cdiv(g->n, kBlock))), dim3(kBlock), 0, s, g->roffs,
                        g->rcols, reinterpret_cast<int4*>(head), g->n);
