@@ -58,6 +58,8 @@ constexpr int kPullGroup = 4;                    // pull: lanes per row past its
 constexpr int kPullRows = 64 / kPullGroup;       // ... and rows of a wave at a time
 constexpr int kPullMany = 24;                    // pull: with more rows than this to go on, lanes walk their own
 constexpr int32_t kPullMid = 256;                // pull: longer rows are finished by the whole wave
+constexpr int kPullSum = 65536;                  // pull: bits of the LDS summary of a small frontier
+constexpr int64_t kPullSparse = 8192;            // ... of at most this many vertices
 constexpr int kPullChunk = 8;                    // pull: visited words (512 vertices) per wave step
 constexpr int kTreeLaneNodes = 4;                // level end: tree nodes per lane of one wave (256)
 
@@ -1230,29 +1232,61 @@ __device__ __forceinline__ PullV pull_vertex(int k, int total, int64_t w0, const
   return p;
 }
 
+// Whether a bottom-up level of nf frontier vertices goes by the summary: while
+// three words of four are empty, which saves that share of the gathers, and
+// the queue is short enough for every workgroup to read it.  3 M vertices with
+// power-law degrees, where 2 million look through all their in-arcs: 4578 in
+// the frontier 98 -> 74 us, 1930 146 -> 93; R-MAT scale 22, 4145: 59 and 59
+// (few arcs are looked through there).
+__device__ __forceinline__ bool pull_sparse(long long nf, int64_t nw) { return nf <= kPullSparse && nf * 4 <= nw; }
+__device__ __forceinline__ int pull_shift(int64_t n) {
+  int s = 6;
+  while (((n - 1) >> s) >= kPullSum) ++s;
+  return s;
+}
+
+// The frontier as a bottom-up level reads it: the word of u's bit (0 for
+// u < 0).  A small frontier (kSparse) is also summed up in LDS, a bit per
+// 2^shift vertices, which answers most probes without a gather.
+struct PullFr {
+  const uint32_t* sum;
+  int shift;
+  template <bool kSparse>
+  __device__ __forceinline__ u64 word(const Args& a, int32_t u) const {
+    if constexpr (kSparse) {
+      const uint32_t x = (uint32_t)(u < 0 ? 0 : u) >> shift;
+      if (!((sum[x >> 5] >> (x & 31)) & 1u)) return 0ull;
+    }
+    return u >= 0 ? a.fr[u >> 6] : 0ull;
+  }
+};
+
 // First in-neighbour among head arcs h that is in the frontier (-1: none).
 // Of a ranked head (a power-law graph) the first arc is probed alone and the
 // others only where it missed: the first one decides for most vertices that
 // are found, and the probes are gathers that the L2 serves at some 150 G/s
 // (8% of the searches of an R-MAT scale 22).  Of any other head, or with at
 // most one vertex per lane, all four go out together: latency counts there.
-__device__ __forceinline__ int32_t pull_probe_first(const Args& a, const int4& h) {
-  const u64 w = h.x >= 0 ? a.fr[h.x >> 6] : 0ull;
+template <bool kSparse>
+__device__ __forceinline__ int32_t pull_probe_first(const Args& a, const PullFr& f, const int4& h) {
+  const u64 w = f.word<kSparse>(a, h.x);
   return (w >> (h.x & 63)) & 1ull ? h.x : -1;
 }
-__device__ __forceinline__ void pull_probe_others(const Args& a, const int4& h, int32_t& par) {
+template <bool kSparse>
+__device__ __forceinline__ void pull_probe_others(const Args& a, const PullFr& f, const int4& h, int32_t& par) {
   const int32_t u[3] = {h.y, h.z, h.w};
   u64 w[3];
 #pragma unroll
-  for (int q = 0; q < 3; ++q) w[q] = par < 0 && u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
+  for (int q = 0; q < 3; ++q) w[q] = par < 0 ? f.word<kSparse>(a, u[q]) : 0ull;
 #pragma unroll
   for (int q = 2; q >= 0; --q)
     if ((w[q] >> (u[q] & 63)) & 1ull) par = u[q];
 }
-__device__ __forceinline__ int32_t pull_probe_all(const Args& a, const int4& h) {
-  const u64 w = h.x >= 0 ? a.fr[h.x >> 6] : 0ull;
+template <bool kSparse>
+__device__ __forceinline__ int32_t pull_probe_all(const Args& a, const PullFr& f, const int4& h) {
+  const u64 w = f.word<kSparse>(a, h.x);
   int32_t par = -1;
-  pull_probe_others(a, h, par);
+  pull_probe_others<kSparse>(a, f, h, par);
   return (w >> (h.x & 63)) & 1ull ? h.x : par;
 }
 
@@ -1276,7 +1310,8 @@ __device__ __forceinline__ int32_t pull_first(const int32_t (&u)[kPullEager], co
   return par;
 }
 
-__device__ __forceinline__ void pull_rows_rest(const Args& a, bool wantA, int32_t vA, int64_t begA, int32_t degA,
+template <bool kSparse>
+__device__ __forceinline__ void pull_rows_rest(const Args& a, const PullFr& f, bool wantA, int32_t vA, int64_t begA, int32_t degA,
                                                int32_t& parA, bool wantB, int32_t vB, int64_t begB, int32_t degB,
                                                int32_t& parB) {
   const int lane = lane_id();
@@ -1288,7 +1323,7 @@ __device__ __forceinline__ void pull_rows_rest(const Args& a, bool wantA, int32_
 #pragma unroll
       for (int q = 0; q < kPullEager; ++q) u[q] = want && off0 + q < deg ? a.rcols[beg + off0 + q] : -1;
 #pragma unroll
-      for (int q = 0; q < kPullEager; ++q) fw[q] = u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
+      for (int q = 0; q < kPullEager; ++q) fw[q] = f.word<kSparse>(a, u[q]);
 #pragma unroll
       for (int q = kPullEager - 1; q >= 0; --q)
         if ((fw[q] >> (u[q] & 63)) & 1ull) par = u[q];
@@ -1323,7 +1358,7 @@ __device__ __forceinline__ void pull_rows_rest(const Args& a, bool wantA, int32_
         u[q] = par < 0 && e < lim ? a.rcols[beg + e] : -1;
       }
 #pragma unroll
-      for (int q = 0; q < kPullEager; ++q) fw[q] = u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
+      for (int q = 0; q < kPullEager; ++q) fw[q] = f.word<kSparse>(a, u[q]);
 #pragma unroll
       for (int q = 0; q < kPullEager; ++q) hit[q] = (fw[q] >> (u[q] & 63)) & 1ull;
       const int32_t x = pull_first(u, hit, lo, (1ull << kPullGroup) - 1ull);
@@ -1353,7 +1388,7 @@ __device__ __forceinline__ void pull_rows_rest(const Args& a, bool wantA, int32_
 #pragma unroll
       for (int q = 0; q < kPullEager; ++q) u[q] = c + q * 64 + lane < end ? a.rcols[c + q * 64 + lane] : -1;
 #pragma unroll
-      for (int q = 0; q < kPullEager; ++q) fw[q] = u[q] >= 0 ? a.fr[u[q] >> 6] : 0ull;
+      for (int q = 0; q < kPullEager; ++q) fw[q] = f.word<kSparse>(a, u[q]);
 #pragma unroll
       for (int q = 0; q < kPullEager; ++q) hit[q] = (fw[q] >> (u[q] & 63)) & 1ull;
       par = pull_first(u, hit, 0, ~0ull);
@@ -1373,7 +1408,8 @@ __device__ __forceinline__ void pull_settle(const Args& a, Stage& st, u64* found
   stage_push(st, a, found, p.v);
 }
 
-__device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_found)[kPullChunk]) {
+template <bool kSparse>
+__device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_found)[kPullChunk], const PullFr& f) {
   const int lane = lane_id();
   u64* found_w = s_found[threadIdx.x >> 6];
   // words per wave and step: a line of them (8; 6, which spreads scale 22
@@ -1423,13 +1459,13 @@ __device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_foun
       }
       int32_t parA, parB;
       if (a.head_ranked && two) {
-        parA = pull_probe_first(a, hA);
-        parB = pull_probe_first(a, hB);
-        pull_probe_others(a, hA, parA);
-        pull_probe_others(a, hB, parB);
+        parA = pull_probe_first<kSparse>(a, f, hA);
+        parB = pull_probe_first<kSparse>(a, f, hB);
+        pull_probe_others<kSparse>(a, f, hA, parA);
+        pull_probe_others<kSparse>(a, f, hB, parB);
       } else {
-        parA = pull_probe_all(a, hA);
-        parB = pull_probe_all(a, hB);
+        parA = pull_probe_all<kSparse>(a, f, hA);
+        parB = pull_probe_all<kSparse>(a, f, hB);
       }
       const bool moreA = A.mine && hA.w >= 0, moreB = B.mine && hB.w >= 0;
       // the row's bounds only when it may go on past the head and that found nothing
@@ -1445,7 +1481,7 @@ __device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_foun
         const int64_t deg = a.roffs[B.v + 1] - begB;
         degB = deg < 0x7fffff00 ? (int32_t)deg : 0x7fffff00;
       }
-      pull_rows_rest(a, moreA && parA < 0, A.v, begA, degA, parA, moreB && parB < 0, B.v, begB, degB, parB);
+      pull_rows_rest<kSparse>(a, f, moreA && parA < 0, A.v, begA, degA, parA, moreB && parB < 0, B.v, begB, degB, parB);
       pull_settle(a, st, found_w, A, parA);
       if (two) pull_settle(a, st, found_w, B, parB);
     }
@@ -1455,7 +1491,7 @@ __device__ __forceinline__ void body_pull(const Args& a, Stage& st, u64 (*s_foun
     if (word_lane) {
       const u64 fm = found_w[lane];
       a.nx[w0 + lane] = fm;
-      if (fm) a.vis[w0 + lane] = seen | fm;  // this wave is the word's only writer in a pull level
+      if (fm) a.vis[w0 + lane] |= fm;  // (read again: no register to spare for it) this wave is the word's only writer in a pull level
     }
   }
 }
@@ -1534,12 +1570,15 @@ __device__ __forceinline__ void body_rev_edge_scan(const Args& a, Stage& st) {
 // the search has ended a launch does nothing but pass that on.
 union LevelLds {
   LongRows lr;
-  u64 found[kWaves][kPullChunk];
+  struct {
+    u64 found[kWaves][kPullChunk];
+    uint32_t sum[kPullSum / 32];
+  } pull;
   EdgeLds edge;
   int64_t wsum[kWaves];
 };
 
-__global__ void __launch_bounds__(kBlock) k_level_auto(BfsBase b, BfsPolicy p, int32_t j) {
+__global__ void __launch_bounds__(kBlock, 6) k_level_auto(BfsBase b, BfsPolicy p, int32_t j) {
   __shared__ Stage st;
   __shared__ QueueIn qi;
   __shared__ LevelLds lds;
@@ -1552,6 +1591,7 @@ __global__ void __launch_bounds__(kBlock) k_level_auto(BfsBase b, BfsPolicy p, i
   }
   const int k = kernel_base(k_id);
   const int32_t d = c->d;
+  const long long nf = c->nf;
   // the launch may be smaller than the level asks for: its workgroups then
   // stride over the work
   const int32_t grid = c->grid < (int32_t)gridDim.x ? c->grid : (int32_t)gridDim.x;
@@ -1595,7 +1635,25 @@ __global__ void __launch_bounds__(kBlock) k_level_auto(BfsBase b, BfsPolicy p, i
       body_edge_expand(a, st, qi, es, lds.edge, c->etot);
       break;
     }
-    case GSW_K_PULL_BITMAP: body_pull(a, st, lds.found); break;
+    case GSW_K_PULL_BITMAP: {
+      if (!pull_sparse(nf, a.nw)) {
+        body_pull<false>(a, st, lds.pull.found, PullFr{nullptr, 0});
+      } else {
+        // the frontier's vertices are in the queue too
+        queue_in_load(cpre, d & 3, qi);
+        const int shift = pull_shift(a.n);
+        for (int i = threadIdx.x; i < kPullSum / 32; i += kBlock) lds.pull.sum[i] = 0u;
+        __syncthreads();
+        const uint32_t cnt = qi.pre[kQueueBins];
+        for (uint32_t i = threadIdx.x; i < cnt; i += kBlock) {
+          const uint32_t x = (uint32_t)queue_at(a, qi, i) >> shift;
+          atomicOr(&lds.pull.sum[x >> 5], 1u << (x & 31));
+        }
+        __syncthreads();
+        body_pull<true>(a, st, lds.pull.found, PullFr{lds.pull.sum, shift});
+      }
+      break;
+    }
     case GSW_K_VERTEX_SCAN: body_vertex_scan(a, st, lds.lr); break;
     case GSW_K_REV_EDGE_SCAN: body_rev_edge_scan(a, st); break;
     default: body_edge_scan(a, st); break;

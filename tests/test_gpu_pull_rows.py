@@ -56,3 +56,24 @@ def test_pull_rows(name):
             assert np.array_equal(lv[i], refs[i])
             (checks.check_bfs_directed if directed else checks.check_bfs)(g.offs, g.cols, s, lv[i], pa[i])
     G.close()
+
+
+@pytest.mark.parametrize("n,children", [(262144, 1024), (262144, 1025), (262080, 1023), (70001, 273), (70001, 274),
+                                        (4194304, 5000), (4194305, 5000), (4300007, 8192), (4300007, 8193)])
+def test_pull_small_frontiers(n, children):
+    """Frontiers on both sides of those a bottom-up level sums up in LDS, with
+    one bit per 64 vertices and per 128; ids up to the last one."""
+    rng = np.random.default_rng(n + children)
+    ids = np.concatenate([[n - 1, 0, 63, 64], rng.permutation(np.arange(65, n - 1))])
+    hub, kids, leaves = ids[0], ids[1:1 + children], ids[1 + children:1 + 4 * children]
+    src = np.concatenate([np.full(children, hub), rng.choice(kids, leaves.size), rng.choice(kids, leaves.size)])
+    dst = np.concatenate([kids, leaves, leaves])
+    g = gg.from_edges(n, src, dst, name="two_levels")
+    G = gsw.Graph.from_csr(g.offs, g.cols, flags=gsw.ASSUME_SYMMETRIC | gsw.TRUSTED)
+    for s in (int(hub), int(leaves[0])):
+        ref = oracle.levels(g.offs, g.cols, s)
+        lv, pa, tr = gsw.bfs(G, [s], policy="fixed", kernel=gsw.PULL_BITMAP)
+        assert np.array_equal(lv[0], ref)
+        checks.check_bfs(g.offs, g.cols, s, lv[0], pa[0])
+        assert [t.n_frontier for t in tr] == np.bincount(ref[ref >= 0]).tolist()
+    G.close()
