@@ -179,7 +179,8 @@ typedef struct {
                                 more bytes read per discovered vertex) */
   int32_t no_solo;           /* 1: never run levels in single-workgroup launches.  0 (the
                                 default): while the frontier is small (at most 2048
-                                vertices, with bounded arcs) and the policy names a
+                                vertices, 1024 in searches of large graphs, with
+                                bounded arcs) and the policy names a
                                 queue-driven top-down kernel (push_vertex, push_wave,
                                 push_edge), one workgroup of 1024 threads runs such levels
                                 one after another in a single launch, deciding each next

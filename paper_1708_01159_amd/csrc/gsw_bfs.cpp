@@ -257,6 +257,7 @@ BfsBase make_base(const gsw_graph* g, const Workspace& w, int32_t* lv, int32_t* 
   b.solo_nf = solo_frontier(g->n, g->nnz, b.deg_max);
   b.solo = 0;
   b.solo_bits = 0;
+  b.solo_max = (int32_t)kSoloMaxGlobal;
   return b;
 }
 
@@ -350,11 +351,16 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   // full-grid launch behind it, which runs whatever level it finds.  But where
   // the largest degree bounds the arcs, none is ever handed back, and there
   // such launches follow one another.
-  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, b) &&
+  bool solo = b.solo && solo_eligible(k0, 1, 1, 1, b, kSoloMaxGlobal) &&
               !(pol.hubs && b.deg_max > kSoloArcs && !solo_whole(b.n, b.nnz));
   const bool whole = solo_whole(b.n, b.nnz);
   const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs || whole;
   int64_t solo_j = -2;  // the latest such launch
+  // such launches from lds_from on have the visited bitmap in LDS, and so take
+  // larger frontiers
+  const bool lds_fits = w.nw <= kSoloVisWords;
+  int64_t lds_from = w.nw <= kSoloVisSmall ? 0 : INT64_MAX;
+  auto solo_max_of = [&](int64_t launch) { return launch >= lds_from ? kSoloMax : kSoloMaxGlobal; };
   // The latest record is of a single-workgroup launch that went on: its other
   // records came with it, and only the last one says what to launch (a second
   // such launch behind it found nothing to do, 4-5 us).  Until then no more is
@@ -371,8 +377,10 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
       if (solo && (solo_always || solo_j + 1 < consumed)) {
         solo_j = launched;
         const bool deep = d >= kSoloDeep || whole;
+        if (deep && lds_fits && lds_from > launched) lds_from = launched;
         b.solo = deep ? kSoloMaxLevels : kSoloLevels;
-        GSW_TRY(launch_level_solo(g, b, dp, (int32_t)launched, deep || w.nw <= kSoloVisSmall, s));
+        b.solo_max = (int32_t)solo_max_of(launched);
+        GSW_TRY(launch_level_solo(g, b, dp, (int32_t)launched, launched >= lds_from, s));
       } else
         GSW_TRY(launch_level_auto(g, b, dp, (int32_t)launched, size, s));
       if (events) GSW_HIP(hipEventRecord(ev_after(launched), s));
@@ -395,13 +403,17 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
     if (r.launch + 1 > consumed) consumed = r.launch + 1;
     ++*rows;
     if (nn == 0) break;
-    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, b);
-    in_solo = solo && (r.flags & kFlagSolo) != 0;
+    const int64_t lim = lds_fits && (d + 1 >= kSoloDeep || lds_from == 0) ? kSoloMax : kSoloMaxGlobal;
+    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, b, lim);
+    in_solo = solo && (r.flags & kFlagSolo) != 0 && nn <= solo_max_of(r.launch);
     if (r.launch != latest) first_d = d;
     latest = r.launch;
     // (a whole graph's launch goes on to its level cap, and then nothing waits)
     if (whole && solo) want = in_solo && d - first_d + 1 < kSoloMaxLevels ? 0 : 1;
     else want = in_solo ? level_launches(nk, nn) : solo ? kSoloAhead : kAhead + level_launches(nk, nn) - 1;
+    // (launches queued before the bitmap went to LDS pass a larger frontier on)
+    if (solo && nn > kSoloMaxGlobal && lds_from > consumed)
+      want += (int)((lds_from < launched ? lds_from : launched) - consumed);
     size = launch_size(nk, nn, r.nf, nf_prev, r.disc, d, g->n, cap);
     nf_prev = r.nf;
   }
@@ -589,6 +601,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
   const BfsBase b = make_base(g, w, lv, pa, false, false);
   BfsBase b_solo = b;  // one level per single-workgroup launch
   b_solo.solo = 1;
+  b_solo.solo_max = (int32_t)(w.nw <= kSoloVisSmall ? kSoloMax : kSoloMaxGlobal);
   b_solo.solo_bits = 1;  // every kernel is timed on the frontier it leaves
   std::memset(w.ring, 0, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long));
   w.ring_used = -1;  // every level reposts its record here: the next search clears the whole ring
@@ -648,7 +661,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
     // (never handed back), else the level kernel with the loop's launch size,
     // twice for push_edge on more than kEdgeFuse entries
     auto run = [&](int k, bool timed_bracket) -> gsw_status {
-      const bool solo = kernel_base(k) <= GSW_K_PUSH_EDGE && nf <= kSoloMax &&
+      const bool solo = kernel_base(k) <= GSW_K_PUSH_EDGE && nf <= b_solo.solo_max &&
                         (long long)b.deg_max * nf <= kSoloMaxArcs;
       const int32_t size = launch_size(k, nf, nf1, nf2, disc1, d - 1, n, b.grid_max);
       if (timed_bracket) GSW_HIP(hipEventRecord(w.ev[0], s));
@@ -686,7 +699,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
       }
     }
     GSW_TRY(restore(adv));
-    const bool adv_solo = kernel_base(adv) <= GSW_K_PUSH_EDGE && nf <= kSoloMax &&
+    const bool adv_solo = kernel_base(adv) <= GSW_K_PUSH_EDGE && nf <= b_solo.solo_max &&
                           (long long)b.deg_max * nf <= kSoloMaxArcs;
     GSW_TRY(run(adv, false));
     cur = adv_solo ? 1 : level_launches(adv, nf) & 1;  // slot written by the last launch

@@ -268,6 +268,7 @@ struct BfsBase {
   int32_t count_arcs;              // accumulate the next frontier's out-degrees
   int32_t solo;                    // levels one single-workgroup launch may run (0: such launches off)
   int32_t solo_bits;               // ... which then sets the frontier's bitmap whatever kernel comes next
+  int32_t solo_max;                // ... and the largest frontier it takes (kSoloMax or kSoloMaxGlobal)
   int32_t solo_nf;                 // frontiers that qualify for one at any time (solo_frontier)
   int32_t deg_max;                 // largest out-degree (clamped to 2^31 - 1)
   int32_t head_ranked;             // head holds ranked in-arcs (bottom-up rows are then probed from their start)
@@ -300,6 +301,10 @@ struct BfsBase {
 constexpr int kSoloBlock = 1024;
 constexpr int kSoloSlots = 2;  // frontier entries per thread at most
 constexpr int64_t kSoloMax = 2048;
+// ... but with the visited bitmap in global memory, where one compute unit's
+// atomics bound it (grids of 2048 x 2048 and 900 x 4000 at 512, 1024 and 2048:
+// 22.9, 22.0 and 24.1 ms a search, 35.1, 30.4 and 32.6).
+constexpr int64_t kSoloMaxGlobal = 1024;
 static_assert(kSoloMax <= (int64_t)kSoloBlock * kSoloSlots, "every frontier entry has a thread slot");
 constexpr int64_t kSoloMaxArcs = 8192;
 constexpr int64_t kSoloArcs = 2048;
@@ -330,8 +335,9 @@ __host__ __device__ inline int32_t solo_frontier(long long n, long long nnz, int
   const long long f = by_max > by_avg ? by_max : by_avg;
   return (int32_t)(f < kSoloMax ? (f > 1 ? f : 1) : kSoloMax);
 }
-__host__ __device__ inline bool solo_eligible(int k, long long nn, long long nf, long long disc_next, const BfsBase& b) {
-  if (k < 0 || nn < 1 || nn > kSoloMax) return false;
+__host__ __device__ inline bool solo_eligible(int k, long long nn, long long nf, long long disc_next, const BfsBase& b,
+                                              long long solo_max) {
+  if (k < 0 || nn < 1 || nn > solo_max) return false;
   if (solo_whole(b.n, b.nnz)) return kernel_base(k) <= GSW_K_PULL_BITMAP;
   if (kernel_base(k) > GSW_K_PUSH_EDGE) return false;
   return nn <= b.solo_nf || (nn <= nf && disc_next * 100 >= b.n);

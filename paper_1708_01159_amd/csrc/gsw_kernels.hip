@@ -1699,6 +1699,11 @@ __global__ void __launch_bounds__(kBlock, 6) k_level_auto(BfsBase b, BfsPolicy p
 // frontier in the queue, four barriers and a record a level); a 1023 x 1025
 // grid (3120 levels of up to 1700 vertices) 12.2 -> 3.7 ms, 1.2 us a level.
 constexpr int kSoloShort = 8;
+// Frontiers beyond this many vertices look at the visited word before they
+// claim in it (global memory): a claim takes a compute unit 2-3 ns, and most
+// of a mesh's arcs lead back; a look costs a smaller frontier its latency.
+// Grid of 1030 x 1030: 9.4 -> 7.8 ms with the frontier limit that it allows.
+constexpr int32_t kSoloFilter = 192;
 constexpr int kSoloLong = 512;  // long rows set aside per level at most
 constexpr int kSoloWaves = kSoloBlock / 64;
 constexpr int kSoloLdsTree = 256;  // tree nodes held in LDS (a larger tree is walked from global memory)
@@ -1777,7 +1782,7 @@ __device__ __forceinline__ LeafBox leaf_box(Node node, Thr thr, int32_t f, int32
 // atomic per wavefront.  Every lane of the wavefront calls it.
 template <int N, int PER, bool LdsVis>
 __device__ __forceinline__ void solo_visit(const BfsBase& b, SoloLds<LdsVis>& L, int32_t d, int slot, int nxt,
-                                           const int32_t (&v)[N], const int32_t (&u)[N / PER]) {
+                                           bool filter, const int32_t (&v)[N], const int32_t (&u)[N / PER]) {
   bool win[N];
   if constexpr (LdsVis) {
     uint32_t w[N];
@@ -1787,8 +1792,17 @@ __device__ __forceinline__ void solo_visit(const BfsBase& b, SoloLds<LdsVis>& L,
     for (int q = 0; q < N; ++q) win[q] = v[q] >= 0 && !((w[q] >> (v[q] & 31)) & 1u);
   } else {
     u64 w[N];
+    if (filter) {
 #pragma unroll
-    for (int q = 0; q < N; ++q) w[q] = v[q] >= 0 ? atomicOr(b.vis + (v[q] >> 6), 1ull << (v[q] & 63)) : ~0ull;
+      for (int q = 0; q < N; ++q)
+        w[q] = v[q] >= 0 ? __hip_atomic_load(b.vis + (v[q] >> 6), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0ull;
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        if (!((w[q] >> (v[q] & 63)) & 1ull)) w[q] = atomicOr(b.vis + (v[q] >> 6), 1ull << (v[q] & 63));
+    } else {
+#pragma unroll
+      for (int q = 0; q < N; ++q) w[q] = v[q] >= 0 ? atomicOr(b.vis + (v[q] >> 6), 1ull << (v[q] & 63)) : ~0ull;
+    }
 #pragma unroll
     for (int q = 0; q < N; ++q) win[q] = v[q] >= 0 && !((w[q] >> (v[q] & 63)) & 1ull);
   }
@@ -1848,7 +1862,7 @@ __device__ __forceinline__ void solo_heads_fetch(const int32_t* __restrict__ hea
 
 // Visits the first N of the fetched passes.
 template <int N, bool LdsVis>
-__device__ __forceinline__ void solo_heads_visit(const BfsBase& b, SoloLds<LdsVis>& L, int32_t d, int slot, int nxt,
+__device__ __forceinline__ void solo_heads_visit(const BfsBase& b, SoloLds<LdsVis>& L, int32_t d, int slot, int nxt, bool filter,
                                                  const int32_t (&u)[kSoloPasses], const int32_t (&v)[kSoloPasses]) {
   int32_t un[N], vn[N];
 #pragma unroll
@@ -1856,7 +1870,7 @@ __device__ __forceinline__ void solo_heads_visit(const BfsBase& b, SoloLds<LdsVi
     un[k] = u[k];
     vn[k] = v[k];
   }
-  solo_visit<N, 1, LdsVis>(b, L, d, slot, nxt, vn, un);
+  solo_visit<N, 1, LdsVis>(b, L, d, slot, nxt, filter, vn, un);
 }
 
 // Entry i of the depth-d queue as a level kernel wrote it (kQueueBins segments).
@@ -2023,7 +2037,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   const bool tree = p.policy == GSW_POLICY_TREE;
   constexpr int last_base = Whole ? GSW_K_PULL_BITMAP : GSW_K_PUSH_EDGE;  // (the kernels it runs come first)
   const bool ok = b.solo > 0 && k_id >= 0 && k_id < GSW_N_KERNELS && kernel_base(k_id) <= last_base &&
-                  c->nf >= 1 && c->nf <= kSoloMax;
+                  c->nf >= 1 && c->nf <= b.solo_max;
   if (!ok) {  // not a level for this launch: the slot passes on unchanged
     if (tid == 0) *cn = *c;
     return;
@@ -2113,6 +2127,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       L.nlong[slot1] = 0u;
     }
     bool lng[kSoloSlots] = {};
+    const bool filter = nf > kSoloFilter;
     const bool check = !HeadOnly && !Whole && nf > bound_arcs;
     if (!HeadOnly && wid * 64 < nf) {
       // rows set aside while there is room, else walked by their thread; the
@@ -2177,11 +2192,11 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
         if (k0 > 0) solo_heads_fetch(b.head, L.q[cur], k0, nf, u, v);
         const int left = (nf - k0 * kSoloRows + kSoloRows - 1) / kSoloRows;
         if (left == 1)
-          solo_heads_visit<1, LdsVis>(b, L, d, slot, nxt, u, v);
+          solo_heads_visit<1, LdsVis>(b, L, d, slot, nxt, filter, u, v);
         else if (left == 2)
-          solo_heads_visit<2, LdsVis>(b, L, d, slot, nxt, u, v);
+          solo_heads_visit<2, LdsVis>(b, L, d, slot, nxt, filter, u, v);
         else
-          solo_heads_visit<kSoloPasses, LdsVis>(b, L, d, slot, nxt, u, v);
+          solo_heads_visit<kSoloPasses, LdsVis>(b, L, d, slot, nxt, filter, u, v);
       }
     } else if (!pull && wid * 64 < nf) {
       // rows not set aside, four arcs of a slot in flight together
@@ -2194,14 +2209,14 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
           if (lng[q])
 #pragma unroll
             for (int k = 0; k < kHeadArcs; ++k) arc[q][k] = -1;
-          solo_visit<4, 4, LdsVis>(b, L, d, slot, nxt, arc[q], us);
+          solo_visit<4, 4, LdsVis>(b, L, d, slot, nxt, filter, arc[q], us);
           e += kHeadArcs;
         }
         while (__any(!lng[q] && e < end[q])) {
           int32_t w[4];
 #pragma unroll
           for (int k = 0; k < 4; ++k) w[k] = !lng[q] && e + k < end[q] ? b.cols[e + k] : -1;
-          solo_visit<4, 4, LdsVis>(b, L, d, slot, nxt, w, us);
+          solo_visit<4, 4, LdsVis>(b, L, d, slot, nxt, filter, w, us);
           e += 4;
         }
       }
@@ -2240,7 +2255,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
             us[k] = L.lu[lo];
           }
         }
-        solo_visit<4, 1, LdsVis>(b, L, d, slot, nxt, w, us);
+        solo_visit<4, 1, LdsVis>(b, L, d, slot, nxt, filter, w, us);
       }
     }
     lds_barrier();
@@ -2262,7 +2277,8 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       }
       // (solo_eligible, with the kernel's part of it decided above)
       const bool go = lv + 1 < levels_max && nn > 0 && leaf_push &&
-                      (Whole || nn <= b.solo_nf || (nn <= (int32_t)kSoloMax && nn <= nf && (long long)ndisc * 100 >= b.n));
+                      nn <= b.solo_max &&
+                      (Whole || nn <= b.solo_nf || (nn <= nf && (long long)ndisc * 100 >= b.n));
       const int32_t next = nn > 0 ? leaf_next : kCtlDone, nflags = nn > 0 ? leaf_flags : 0;
       if (tid == 0) {
         L.go = go ? 1 : 0;

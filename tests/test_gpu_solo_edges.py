@@ -202,3 +202,49 @@ def test_solo_rows_that_a_level_kernel_leaves_to_one_workgroup(arcs):
                         limit = 8192 if few and t.n_frontier <= 16 else 2048
                         assert bool(t.flags & SOLO) == (t.e_frontier <= limit), (s, kernel, t)
         G.close()
+
+
+@pytest.mark.parametrize("n", [200003, 1100003])
+@pytest.mark.parametrize("lead", [20, 29, 30, 31, 32, 33, 60, 100])
+def test_solo_frontiers_where_the_bitmap_moves(lead, n):
+    """A path, then frontiers of 1, 2, 4 .. 4096 vertices and back, twice: they
+    pass what a launch takes with the bitmap in global memory (1024) and in LDS
+    (2048) before, while and after later launches hold it in LDS (from depth
+    32, if it fits)."""
+    src, dst, nv, at = [], [], 1, 0
+
+    def path(k):
+        nonlocal nv, at
+        for _ in range(k):
+            src.append(at), dst.append(nv)
+            at, nv = nv, nv + 1
+
+    for _ in range(2):
+        path(lead)
+        front = [at]
+        while len(front) < 4096:
+            new = list(range(nv, nv + 2 * len(front)))
+            nv += 2 * len(front)
+            src.extend(v for v in front for _ in range(2)), dst.extend(new)
+            front = new
+        while len(front) > 1:
+            new = list(range(nv, nv + len(front) // 2))
+            nv += len(new)
+            src.extend(front), dst.extend(v for v in new for _ in range(2))
+            front = new
+        at = front[0]
+    path(5)
+    g = gg.from_edges(n, src, dst, name="bulges")
+    G = gsw.Graph.from_csr(g.offs, g.cols)
+    ref = oracle.levels(g.offs, g.cols, 0)
+    for kw in (dict(policy="fixed", kernel=gsw.PUSH_VERTEX), dict(policy="fixed", kernel=gsw.PUSH_EDGE),
+               dict(policy="tree", tree=_wide_tree(6))):
+        for count_arcs in (False, True):
+            lv, pa, tr = gsw.bfs(G, [0], trace_cap=4096, count_arcs=count_arcs, **kw)
+            assert np.array_equal(lv[0], ref)
+            checks.check_bfs(g.offs, g.cols, 0, lv[0], pa[0])
+            assert [t.n_frontier for t in tr] == np.bincount(ref[ref >= 0]).tolist()
+            limit = 2048 if n <= 1048576 else 1024
+            assert not any(t.flags & SOLO and t.n_frontier > limit for t in tr)
+            assert sum(1 for t in tr if t.flags & SOLO) >= 0.5 * len(tr)
+    G.close()
