@@ -41,7 +41,10 @@ def _csv_rows(path):
 
 def _short(name):
     name = name.replace("gsw::(anonymous namespace)::", "").replace("void ", "")
-    return name.split("(")[0][:48]
+    name = name.split("(")[0]
+    if name.startswith("k_"):  # one name for all forms of a kernel template
+        name = name.split("<")[0]
+    return name[:48]
 
 
 SOLO_FLAG = 4  # trace flag of a level run by a single-workgroup launch
@@ -180,7 +183,7 @@ def summarize(d, root):
 
 
 BATCHED_CMD = "python3 -u bench.py --batched-only 1024 --copy-calib"
-MS_KERNELS = ("k_ms_init", "k_ms_sources", "k_ms_push", "k_ms_level", "k_ms_finalize", "k_ms_transpose")
+MS_KERNELS = ("k_ms_init", "k_ms_sources", "k_ms_push", "k_ms_level", "k_ms_finalize", "k_ms_levels_out")
 
 
 def summarize_batched(d, tuned_batches: int = 6):
@@ -189,8 +192,9 @@ def summarize_batched(d, tuned_batches: int = 6):
     tuned batch, run once untimed and five times timed; the autotuning
     batches before them are left out): rocprofv3 durations, FETCH_SIZE and
     WRITE_SIZE scaled by the 1 GiB copy of the same run, the traffic rate
-    against 8 TB/s, and for the transpose -- a pure stream of B*n bytes in
-    and B*n bytes out -- its algorithmic bytes and roofline fraction.  The
+    against 8 TB/s, and for the kernel that writes the levels from the bit
+    planes -- B*n bytes out, a bit per source and vertex in for the visited
+    mask and for every plane -- its bytes out and their share of the traffic.  The
     level kernels' algorithmic bytes depend on each source's direction and
     on early exits that only the device sees, so their line gives the
     measured traffic."""
@@ -246,13 +250,13 @@ def summarize_batched(d, tuned_batches: int = 6):
         per[k] = (us, fb, wb)
         L.append("| %s | %.1f | %.1f | %.1f | %.1f | %.0f | %.3f |" % (
             k, len(t) / tuned_batches, us, fb / 1e6, wb / 1e6, rate, rate / HBM_PEAK_GBS))
-    if "k_ms_transpose" in per:
-        us, fb, wb = per["k_ms_transpose"]
-        alg = 2.0 * B * n
-        L += ["", "k_ms_transpose: algorithmic bytes %.1f MB per batch (the int8 levels, %d x %d bytes, read "
-              "vertex-major and written source-major); %.1f us -> %.0f GB/s = **%.3f** of 8 TB/s; counter "
-              "traffic / algorithmic = %.2f." % (alg / 1e6, B, n, us, alg / (us * 1e-6) / 1e9,
-                                                 alg / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, (fb + wb) / alg)]
+    if "k_ms_levels_out" in per:
+        us, fb, wb = per["k_ms_levels_out"]
+        out = float(B) * n
+        L += ["", "k_ms_levels_out: %.1f MB of int8 levels per batch (%d x %d bytes) written source-major from bit "
+              "planes; %.1f us, counter traffic %.1f MB -> %.0f GB/s = **%.3f** of 8 TB/s, of which the levels are "
+              "%.2f." % (out / 1e6, B, n, us, (fb + wb) / 1e6, (fb + wb) / (us * 1e-6) / 1e9,
+                         (fb + wb) / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, out / (fb + wb))]
     return "\n".join(L)
 
 

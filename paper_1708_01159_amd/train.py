@@ -144,7 +144,7 @@ def collect(graphs=None, reps: int = 3, kernels=None, log=print, source_seed: in
                 source=np.array(src), level=np.array(lvl), kernels=np.array(ks))
 
 
-# A single-workgroup launch runs up to 32 small top-down levels back to back
+# A single-workgroup launch runs up to 80 small levels back to back
 # (gsw_bfs_opts.no_solo); the profile above times each level as one launch
 # of its own, so on such levels it charges a push kernel a whole launch
 # (about 6-12 us on MI355X) where the search pays a few microseconds.  The
