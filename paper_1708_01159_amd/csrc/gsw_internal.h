@@ -318,6 +318,12 @@ constexpr int64_t kSoloVisWords = 16384;  // 64-bit words of a visited bitmap th
 __host__ __device__ inline int32_t solo_arc_limit(int k, int32_t nf) {
   return kernel_base(k) != GSW_K_PUSH_EDGE && nf <= kSoloFewRows ? (int32_t)kSoloMaxArcs : (int32_t)kSoloArcs;
 }
+// The length that a launch notes for a row it sets aside: the row's own, for
+// whatever limit a level is taken under.  (One that 32 bits do not hold is of
+// a level that is handed back by its counted arcs; no sum is taken of it.)
+__host__ __device__ inline int32_t solo_row_length(int64_t deg) {
+  return deg < 0x7fffffff ? (int32_t)deg : 0x7fffffff;
+}
 // A graph so small that one workgroup runs its searches to the end, bottom-up
 // levels too, whatever the frontier and its arcs.  Measured, a search by the
 // tree in one workgroup and by level kernels: R-MAT of 1024 vertices and

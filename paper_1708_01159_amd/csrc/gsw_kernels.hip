@@ -2141,7 +2141,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
             if (at < (uint32_t)kSoloLong) {
               L.lu[at] = u[q];
               L.lbeg[at] = beg[q];
-              L.lpre[at] = (int32_t)(Whole || deg < kSoloMaxArcs ? deg : kSoloMaxArcs + 1);
+              L.lpre[at] = solo_row_length(deg);
               lng[q] = true;
             }
           }

@@ -1,0 +1,34 @@
+// Rules of the single-workgroup launches that can be checked without a GPU.
+// Prints "ok" and exits 0 when every check holds.
+#include <cstdio>
+
+#include "../../paper_1708_01159_amd/csrc/gsw_internal.h"
+
+using namespace gsw;
+
+#define CHECK(c)                                                          \
+  do {                                                                    \
+    if (!(c)) {                                                           \
+      std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); \
+      return 1;                                                           \
+    }                                                                     \
+  } while (0)
+
+int main() {
+  // A row of a level that a launch takes is walked over exactly its arcs: at
+  // most kSoloMaxArcs in all by the largest degree or by a count, any number
+  // up to kSoloWholeArcs on a graph searched to the end.
+  const int64_t most = kSoloMaxArcs > kSoloWholeArcs ? kSoloMaxArcs : kSoloWholeArcs;
+  for (int64_t deg = 0; deg <= most; ++deg) {
+    if (solo_row_length(deg) != deg) std::fprintf(stderr, "row of %lld arcs\n", (long long)deg);
+    CHECK(solo_row_length(deg) == deg);
+  }
+  for (int k = 0; k < GSW_N_KERNELS; ++k)
+    for (int32_t nf = 1; nf <= kSoloMax; ++nf) CHECK(solo_arc_limit(k, nf) <= kSoloMaxArcs);
+  // a longer row's level is handed back, by its counted arcs and not by this
+  // length, which must still be one that no sum is taken of
+  const int64_t lens[] = {most + 1, 0x7ffffffell, 0x7fffffffll, 0x80000000ll, 0x100000000ll, 0x7fffffffffll};
+  for (int64_t deg : lens) CHECK(solo_row_length(deg) > kSoloMaxArcs);
+  std::puts("ok");
+  return 0;
+}

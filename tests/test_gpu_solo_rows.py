@@ -1,0 +1,61 @@
+"""A row of as many arcs as a single-workgroup launch takes (8192), one fewer
+and one more, with a row of another component behind it in the CSR: nothing
+of that component is reached."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import checks
+from paper_1708_01159_amd import graphgen as gg
+from paper_1708_01159_amd import gsw
+
+pytestmark = pytest.mark.gpu
+
+SOLO = 4  # trace flag of a level run by a single-workgroup launch
+HUB, NEXT, ROOT = 2, 3, 20001  # the row behind the hub's is the first of another component
+
+
+def _graph(arcs, larger, sinks):
+    """Hub of `arcs` arcs; `larger`: another component holds a longer row, so
+    that the hub's arcs are counted; `sinks`: the hub's level has 15 vertices
+    without out-arcs beside it (directed)."""
+    leaves = arcs if sinks else arcs - 1  # (symmetric: the arc back to the root is one of the hub's)
+    src, dst = [HUB] * leaves + [NEXT] * 40, list(range(4, leaves + 4)) + list(range(13000, 13040))
+    if larger:
+        src += [ROOT + 20] * 9000
+        dst += list(range(30000, 39000))
+    src += [ROOT] * (16 if sinks else 1)
+    dst += [HUB] + (list(range(ROOT + 1, ROOT + 16)) if sinks else [])
+    return gg.from_edges(60000, src, dst, symmetrize=not sinks, name="hub")
+
+
+@pytest.mark.parametrize("sinks", [False, True])
+@pytest.mark.parametrize("larger", [False, True])
+@pytest.mark.parametrize("arcs", [8191, 8192, 8193])
+def test_row_of_as_many_arcs_as_one_workgroup_takes(arcs, larger, sinks):
+    import torch
+
+    g = _graph(arcs, larger, sinks)
+    deg = g.degrees()
+    assert deg[HUB] == arcs and deg[NEXT] == 40 and deg.max() == (9000 if larger else arcs)
+    G = gsw.Graph.from_csr(g.offs, g.cols)
+    check = checks.check_bfs_directed if sinks else checks.check_bfs
+    for s in (HUB, ROOT):
+        ref = oracle.levels(g.offs, g.cols, s)
+        sizes = np.bincount(ref[ref >= 0])
+        assert ref[NEXT] < 0
+        hub = int(ref[HUB])
+        for kernel in (gsw.PUSH_VERTEX, gsw.PUSH_WAVE16, gsw.PUSH_EDGE):
+            for count_arcs in (False, True):
+                lv, pa, tr = gsw.bfs(G, [s], policy="fixed", kernel=kernel, count_arcs=count_arcs)
+                assert np.array_equal(lv[0], ref)
+                check(g.offs, g.cols, s, lv[0], pa[0])
+                assert [t.n_frontier for t in tr] == sizes.tolist()
+                # taken by the largest degree, or counted; 8193 arcs never are
+                by_degree = sizes[hub] * int(deg.max()) <= 8192
+                counted = arcs <= (2048 if kernel == gsw.PUSH_EDGE else 8192)
+                assert bool(tr[hub].flags & SOLO) == (by_degree or counted)
+            lv = torch.full((1, g.n), 9, dtype=torch.int32, device="cuda")
+            gsw.bfs_noalloc(G, [s], lv, policy="fixed", kernel=kernel)
+            assert np.array_equal(lv[0].cpu().numpy(), ref)
+    G.close()
