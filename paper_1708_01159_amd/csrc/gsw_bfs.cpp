@@ -22,8 +22,9 @@ namespace {
 // far have used, plus one more when the next level is push_edge (two
 // launches).  Launches queued past the end of the search do nothing.
 constexpr int kAhead = 3;
-// Single-workgroup launches queued beyond the latest record's: one runs
-// many levels, so one more is enough to follow it without a gap.
+// Launches queued beyond the latest record's where the next level may run in
+// a single workgroup: one such launch runs many levels, so one more is enough
+// to follow it without a gap.
 constexpr int kSoloAhead = 2;
 // Levels of one such launch: few at first; many, with the visited bitmap in
 // LDS where it fits, once the search has turned out to be long (loading and
@@ -348,7 +349,8 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   int64_t consumed = 0;  // of those, launches that completed a level whose record was read
   // A single-workgroup launch may hand a level back (too many arcs for one
   // workgroup); the next one is therefore not queued before the record of a
-  // full-grid launch behind it, which runs whatever level it finds.  But where
+  // full-grid launch behind it.  Those run whatever level they find, in two
+  // launches where it is push_edge on more than kEdgeFuse entries.  But where
   // the largest degree bounds the arcs, none is ever handed back, and there
   // such launches follow one another.
   bool solo = b.solo && solo_eligible(k0, 1, 1, 1, b, kSoloMaxGlobal) &&
@@ -356,6 +358,7 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   const bool whole = solo_whole(b.n, b.nnz);
   const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs || whole;
   int64_t solo_j = -2;  // the latest such launch
+  uint64_t solo_bits = 0;  // launch j is one: bit j % 64 (never as many queued)
   // such launches from lds_from on have the visited bitmap in LDS, and so take
   // larger frontiers
   const bool lds_fits = w.nw <= kSoloVisWords;
@@ -368,14 +371,32 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   bool in_solo = false;
   int64_t first_d = 0, latest = 0;  // the latest record's launch and the first level it ran
   int want = solo ? (whole ? 1 : kSoloAhead + 1) : kAhead + level_launches(k0, 1) - 1;
+  // Whatever `want` says, the launches queued behind the latest record must be
+  // able to complete the next level (next_k, next_n), or its record never comes: one
+  // of them a single-workgroup launch that hands no such level back, or as
+  // many level-kernel launches as it takes, since the others may pass it on.
+  int next_k = k0;
+  int64_t next_n = 1;
+  bool running = false;  // the launch of the latest record completes it
+  auto covered = [&]() -> bool {
+    if (running) return true;
+    int autos = 0;
+    for (int64_t j = consumed; j < launched; ++j) {
+      if (!((solo_bits >> (j & 63)) & 1u)) ++autos;
+      else if (solo && solo_always && next_n <= solo_max_of(j)) return true;
+    }
+    return autos >= level_launches(next_k, next_n);
+  };
   const int32_t cap = o->max_workgroups > 0 && o->max_workgroups < b.grid_max ? o->max_workgroups : b.grid_max;
   int32_t size = cap;
   int64_t nf_prev = 0;  // frontier of the level before the latest record's
   int64_t d = 0;
   for (;; ++d) {
-    while (launched - consumed < want) {
+    while (launched - consumed < want || !covered()) {
+      solo_bits &= ~(1ull << (launched & 63));
       if (solo && (solo_always || solo_j + 1 < consumed)) {
         solo_j = launched;
+        solo_bits |= 1ull << (launched & 63);
         const bool deep = d >= kSoloDeep || whole;
         if (deep && lds_fits && lds_from > launched) lds_from = launched;
         b.solo = deep ? kSoloMaxLevels : kSoloLevels;
@@ -404,16 +425,16 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
     ++*rows;
     if (nn == 0) break;
     const int64_t lim = lds_fits && (d + 1 >= kSoloDeep || lds_from == 0) ? kSoloMax : kSoloMaxGlobal;
+    next_k = nk;
+    next_n = nn;
     solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, b, lim);
     in_solo = solo && (r.flags & kFlagSolo) != 0 && nn <= solo_max_of(r.launch);
     if (r.launch != latest) first_d = d;
     latest = r.launch;
     // (a whole graph's launch goes on to its level cap, and then nothing waits)
-    if (whole && solo) want = in_solo && d - first_d + 1 < kSoloMaxLevels ? 0 : 1;
+    running = whole && in_solo && d - first_d + 1 < kSoloMaxLevels;
+    if (whole && solo) want = running ? 0 : 1;
     else want = in_solo ? level_launches(nk, nn) : solo ? kSoloAhead : kAhead + level_launches(nk, nn) - 1;
-    // (launches queued before the bitmap went to LDS pass a larger frontier on)
-    if (solo && nn > kSoloMaxGlobal && lds_from > consumed)
-      want += (int)((lds_from < launched ? lds_from : launched) - consumed);
     size = launch_size(nk, nn, r.nf, nf_prev, r.disc, d, g->n, cap);
     nf_prev = r.nf;
   }
