@@ -328,8 +328,8 @@ gsw_status gsw_bfs_profile(const gsw_graph *g, int32_t source, const int32_t *ke
  * kernels and results as gsw_bfs; it calls no hipMalloc, hipFree,
  * hipHostMalloc or other allocating routine and creates no events.  Its
  * kernels' working memory (bitmaps, frontier queues, counters, level
- * control, push_edge scan arrays, the head copy of the in-arcs,
- * the device copy of the tree or schedule) is one fixed device
+ * control, push_edge scan arrays, the head copy of the in-arcs, room for the
+ * level records, the device copy of the tree or schedule) is one fixed device
  * array of GSW_NOALLOC_SCRATCH_BYTES per GPU, held from the library's first
  * use of that GPU until the process ends.  Limits (GSW_EINVAL beyond them,
  * checked before any GPU work): n <= GSW_NOALLOC_MAX_VERTICES, a tree of at
@@ -345,14 +345,15 @@ gsw_status gsw_bfs_profile(const gsw_graph *g, int32_t source, const int32_t *ke
  * serialised by a lock and each returns after its work on the stream has
  * finished; work that overlaps a call on the same GPU through any other
  * route into this array (another thread bypassing the library, a captured
- * replay still running) races with it.  The level records go to mapped
- * host memory of the graph, made at its creation (32 KiB, for graphs within
- * the limit).
+ * replay still running) races with it.  The level records go to
+ * mapped host memory, 32 KiB per GPU while graphs within the limit exist,
+ * made when the first of them is created.  Where there is none (creation does
+ * not fail for it) they are copied from device memory, a wait per read.
  */
 #define GSW_NOALLOC_MAX_VERTICES (1 << 19)
 #define GSW_NOALLOC_MAX_TREE_NODES 4095
 #define GSW_NOALLOC_MAX_SCHEDULE 4096
-#define GSW_NOALLOC_SCRATCH_BYTES 50741760 /* 48.4 MiB */
+#define GSW_NOALLOC_SCRATCH_BYTES 50774528 /* 48.4 MiB */
 gsw_status gsw_bfs_noalloc(const gsw_graph *g, const int32_t *sources, int32_t n_sources,
                            int32_t *levels, int32_t *parents, gsw_level_trace *trace,
                            int32_t trace_cap, int32_t *trace_len, const gsw_bfs_opts *opts);

@@ -311,7 +311,14 @@ namespace {
 // Waits until level d's record is in the ring.
 gsw_status wait_record(const Workspace& w, int64_t d, hipStream_t s, Record* rec) {
   bool missing = false;
-  const hipError_t e = await_record([&]() -> bool { return take_record(w.ring, d, rec); }, s, &missing);
+  hipError_t e = hipSuccess;
+  if (!w.ring_copied) {
+    e = await_record([&]() -> bool { return take_record(w.ring, d, rec); }, s, &missing);
+  } else if (!take_record(w.ring, d, rec)) {
+    e = hipMemcpyAsync(w.ring, w.d_ring, kRingBytes, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    missing = e == hipSuccess && !take_record(w.ring, d, rec);
+  }
   if (e != hipSuccess) return fail(GSW_EHIP, "level %lld: %s", (long long)d, hipGetErrorString(e));
   if (missing) return fail(GSW_EHIP, "level %lld finished without posting its record", (long long)d);
   return GSW_OK;
@@ -330,6 +337,7 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   const int64_t used = w.ring_used < 0 || w.ring_used > kBfsRing ? kBfsRing : w.ring_used;
   std::memset(w.ring, 0, (size_t)used * kBfsRec * sizeof(unsigned long long));
   w.ring_used = kBfsRing;  // until this search ends normally
+  if (w.ring_copied) GSW_HIP(hipMemsetAsync(w.d_ring, 0, kRingBytes, s));
   constexpr int kEv = Workspace::kLaunchEvents;
   if (events)
     for (hipEvent_t& e : w.lev)
@@ -624,7 +632,7 @@ gsw_status gsw_bfs_profile(const gsw_graph* cg, int32_t source, const int32_t* k
   b_solo.solo = 1;
   b_solo.solo_max = (int32_t)(w.nw <= kSoloVisSmall ? kSoloMax : kSoloMaxGlobal);
   b_solo.solo_bits = 1;  // every kernel is timed on the frontier it leaves
-  std::memset(w.ring, 0, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long));
+  std::memset(w.ring, 0, kRingBytes);
   w.ring_used = -1;  // every level reposts its record here: the next search clears the whole ring
   GSW_TRY(launch_init(g, b, g->iso, source, GSW_DEFAULT_KERNEL, 0, s));
   GSW_HIP(hipStreamSynchronize(s));

@@ -290,9 +290,8 @@ gsw_status ensure_workspace(gsw_graph* g) {
   if (!w.h_ctr) GSW_HIP(hipHostMalloc((void**)&w.h_ctr, kCtrSlot * sizeof(uint32_t), hipHostMallocDefault));
   if (!w.h_ctl) GSW_HIP(hipHostMalloc((void**)&w.h_ctl, sizeof(BfsCtl), hipHostMallocDefault));
   if (!w.ring) {
-    GSW_HIP(hipHostMalloc((void**)&w.ring, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long),
-                          hipHostMallocMapped | hipHostMallocCoherent));
-    std::memset(w.ring, 0, (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long));
+    GSW_HIP(hipHostMalloc((void**)&w.ring, kRingBytes, hipHostMallocMapped | hipHostMallocCoherent));
+    std::memset(w.ring, 0, kRingBytes);
   }
   if (!w.d_ring) GSW_HIP(hipHostGetDevicePointer((void**)&w.d_ring, w.ring, 0));
   if (!w.head_built) {
@@ -373,22 +372,53 @@ gsw_status ensure_rorigin(gsw_graph* g) {
   return build_origin(g, g->roffs, &g->rorigin);
 }
 
+namespace {
+// Each GPU's NoallocRing and the graphs that keep it.
+struct {
+  std::mutex mu;
+  NoallocRing ring[kMaxDevices];
+  int64_t graphs[kMaxDevices] = {};
+} g_rings;
+}  // namespace
+
+NoallocRing noalloc_ring(int device) {
+  if (device < 0 || device >= kMaxDevices) return NoallocRing();
+  std::lock_guard<std::mutex> lock(g_rings.mu);
+  return g_rings.ring[device];
+}
+
 }  // namespace gsw
 
 using namespace gsw;
 
 namespace {
 
-// The record ring of searches that may not allocate, so made with the graph.
-gsw_status make_noalloc_ring(gsw_graph* g) {
-  if (g->n > GSW_NOALLOC_MAX_VERTICES) return GSW_OK;
-  const size_t rb = (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long);
-  if (hipHostMalloc((void**)&g->na_ring, rb, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-      hipHostGetDevicePointer((void**)&g->d_na_ring, g->na_ring, 0) != hipSuccess) {
+// Counts a new graph; makes its GPU's ring where there is none.  A graph is
+// made without one as well: its searches then copy the records (noalloc_ring).
+void hold_noalloc_ring(gsw_graph* g) {
+  if (g->n > GSW_NOALLOC_MAX_VERTICES || g->device < 0 || g->device >= kMaxDevices) return;
+  std::lock_guard<std::mutex> lock(g_rings.mu);
+  g->holds_ring = true;
+  ++g_rings.graphs[g->device];
+  NoallocRing& r = g_rings.ring[g->device];
+  if (r.host) return;
+  if (hipHostMalloc((void**)&r.host, kRingBytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     (void)hipGetLastError();
-    return fail(GSW_ENOMEM, "mapped host memory for the level records");
+    r.host = nullptr;
+  } else if (hipHostGetDevicePointer((void**)&r.dev, r.host, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipHostFree(r.host);
+    r = NoallocRing();
   }
-  return GSW_OK;
+}
+
+void release_noalloc_ring(gsw_graph* g) {
+  if (!g->holds_ring) return;
+  std::lock_guard<std::mutex> lock(g_rings.mu);
+  if (--g_rings.graphs[g->device] > 0) return;
+  NoallocRing& r = g_rings.ring[g->device];
+  if (r.host) (void)hipHostFree(r.host);
+  r = NoallocRing();
 }
 
 void free_graph(gsw_graph* g) {
@@ -404,7 +434,7 @@ void free_graph(gsw_graph* g) {
   if (w.h_ctr) (void)hipHostFree(w.h_ctr);
   if (w.h_ctl) (void)hipHostFree(w.h_ctl);
   if (w.ring) (void)hipHostFree(w.ring);
-  if (g->na_ring) (void)hipHostFree(g->na_ring);
+  release_noalloc_ring(g);
   if (g->iso) (void)hipFree(g->iso);
   for (hipEvent_t ev : w.ev)
     if (ev) (void)hipEventDestroy(ev);
@@ -504,11 +534,11 @@ gsw_status gsw_graph_create_host(int64_t n, int64_t nnz, const int64_t* offs, co
   if (st == GSW_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(GSW_EHIP, "CSR upload");
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_origin(g);
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_rorigin(g);
-  if (st == GSW_OK) st = make_noalloc_ring(g);
   if (st != GSW_OK) {
     free_graph(g);
     return st;
   }
+  hold_noalloc_ring(g);
   *out = g;
   return GSW_OK;
 }
@@ -549,11 +579,11 @@ gsw_status gsw_graph_create_device(int64_t n, int64_t nnz, const int64_t* d_offs
   if (st == GSW_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(GSW_EHIP, "transpose upload");
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_origin(g);
   if (st == GSW_OK && (flags & GSW_WITH_ORIGIN)) st = ensure_rorigin(g);
-  if (st == GSW_OK) st = make_noalloc_ring(g);
   if (st != GSW_OK) {
     free_graph(g);
     return st;
   }
+  hold_noalloc_ring(g);
   *out = g;
   return GSW_OK;
 }

@@ -125,6 +125,7 @@ struct Workspace {
   BfsCtl* h_ctl = nullptr;               // pinned staging for control-block uploads (profiling)
   unsigned long long* ring = nullptr;    // mapped host memory: per-level records
   unsigned long long* d_ring = nullptr;  // the same memory as seen by the device
+  bool ring_copied = false;              // ... or device memory, copied to `ring` for the host to read
   unsigned long long* d_tree = nullptr;  // device copy of the tree's nodes (packed) ...
   int32_t* d_thr = nullptr;              // ... and integer thresholds
   int32_t tree_cap = 0;                  // nodes the device copy has room for
@@ -173,9 +174,7 @@ struct gsw_graph {
   unsigned long long* heavy = nullptr;
   int64_t n_heavy = -1;
   gsw::CcWorkspace* cc = nullptr; // connected components, allocated on first use
-  // gsw_bfs_noalloc's level records: mapped host memory, host and device view
-  // (graphs of up to GSW_NOALLOC_MAX_VERTICES)
-  unsigned long long *na_ring = nullptr, *d_na_ring = nullptr;
+  bool holds_ring = false;        // counted among the graphs that keep their GPU's NoallocRing
   hipStream_t stream = nullptr;   // library stream for this graph
   std::mutex mu;
 };
@@ -370,6 +369,7 @@ constexpr int kBfsRing = 256;
 // queued behind it, may all run before the host reads on.
 static_assert(3 * kSoloMaxLevels <= kBfsRing, "no record is overwritten before it is read");
 constexpr int kBfsRec = 16;
+constexpr size_t kRingBytes = (size_t)kBfsRing * kBfsRec * sizeof(unsigned long long);
 enum : int {
   kRecKernel = 0,   // kernel that ran level d
   kRecFlags = 1,    // its trace flags
@@ -479,6 +479,15 @@ gsw_status bfs_rows_locked(gsw_graph* g, const int32_t* sources, int32_t count, 
                            const gsw_tree* tree, hipStream_t s, bool wait = true,
                            bool hubs = false);
 hipStream_t pick_stream(gsw_graph* g, void* user_stream);
+// Mapped host memory for the level records of gsw_bfs_noalloc on a GPU: made
+// with a graph, since the search may not, shared by all graphs, since such
+// searches run one at a time, and given back with the last graph that it may
+// search.  Null members where there was no such memory.
+constexpr int kMaxDevices = 64;
+struct NoallocRing {
+  unsigned long long *host = nullptr, *dev = nullptr;
+};
+NoallocRing noalloc_ring(int device);
 
 bool kernel_is_pull(int k);
 // The kernel of base `base` and the count variant of k.

@@ -5,7 +5,8 @@
 // in-arcs, the device copies of a tree or schedule -- lives in one file-scope
 // device array of fixed size, laid out for graphs of up to
 // GSW_NOALLOC_MAX_VERTICES vertices; the level records go to mapped host memory
-// that the graph was created with.  The search itself is gsw_bfs's, level
+// made with the GPU's first graph, or, where none could be had, to the array,
+// from which the host loop copies them.  The search itself is gsw_bfs's, level
 // kernels and host loop: eight launches at a time with a copy of their records
 // and a wait in between cost a source 40 us more.
 #include <hip/hip_runtime.h>
@@ -22,13 +23,12 @@ constexpr int64_t kMaxN = GSW_NOALLOC_MAX_VERTICES;
 constexpr int64_t kMaxNw = (kMaxN + 63) / 64;
 constexpr int32_t kMaxTree = GSW_NOALLOC_MAX_TREE_NODES;
 constexpr int32_t kMaxSched = GSW_NOALLOC_MAX_SCHEDULE;
-constexpr int kMaxDevices = 64;
 
 constexpr size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Byte offsets of the regions inside the array, each 256-byte aligned.
 struct Layout {
-  size_t vis, bm[3], iso, ctl, done, q[2], ctr, actr, scan, ebeg, bsum, head, tree, sched, total;
+  size_t vis, bm[3], iso, ctl, done, q[2], ctr, actr, scan, ebeg, bsum, head, ring, tree, sched, total;
 };
 
 constexpr Layout make_layout() {
@@ -55,6 +55,7 @@ constexpr Layout make_layout() {
   L.ebeg = take((size_t)kMaxN * sizeof(int64_t));
   L.bsum = take((size_t)((kMaxN + 1023) / 1024 + 1) * sizeof(int64_t));
   L.head = take((size_t)kMaxN * kHeadArcs * sizeof(int32_t));
+  L.ring = take(kRingBytes);
   L.tree = take((size_t)(kMaxTree + 1) * (sizeof(unsigned long long) + sizeof(int32_t)));
   L.sched = take((size_t)kMaxSched * sizeof(int32_t));
   L.total = at;
@@ -80,9 +81,11 @@ DeviceScratch g_dev[kMaxDevices];
 // host-side tree buffers below are one per process.
 std::mutex g_mu;
 
-// Host buffers for specialising a tree (sized for the largest tree accepted).
+// Host buffers for specialising a tree (sized for the largest tree accepted)
+// and for copied records.
 int32_t h_order[kMaxTree], h_newid[kMaxTree], h_stack[kMaxTree + 1], h_thr[kMaxTree];
 unsigned long long h_nodes[kMaxTree + kMaxTree / 2 + 2];  // the thresholds follow the nodes for one upload
+unsigned long long h_ring[kRingBytes / sizeof(unsigned long long)];
 
 gsw_status device_scratch(int device, DeviceScratch** out) {
   if (device < 0 || device >= kMaxDevices) return fail(GSW_EINVAL, "device %d out of range", device);
@@ -189,8 +192,10 @@ extern "C" gsw_status gsw_bfs_noalloc(const gsw_graph* cg, const int32_t* source
   const hipStream_t s = pick_stream(g, opts->stream);
   Workspace w;
   scratch_workspace(ds->ptr, g->n, &w);
-  w.ring = g->na_ring;
-  w.d_ring = g->d_na_ring;
+  const NoallocRing ring = noalloc_ring(g->device);
+  w.ring_copied = !ring.host;
+  w.ring = ring.host ? ring.host : h_ring;
+  w.d_ring = ring.host ? ring.dev : reinterpret_cast<unsigned long long*>(ds->ptr + kLayout.ring);
   w.tick_ms = ds->tick_ms;
   unsigned long long* iso = reinterpret_cast<unsigned long long*>(ds->ptr + kLayout.iso);
   // graph-derived buffers, rebuilt every call (the array is shared by every graph)

@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <vector>
 
 #include "../../paper_1708_01159_amd/csrc/gsw_internal.h"
@@ -27,6 +28,9 @@ struct Device {
   int64_t launches = 0, solo_levels = 0, handed_back = 0;
 };
 Device dev;
+
+size_t pinned = 0, pinned_room = (size_t)1 << 40;  // bytes of host memory held, and left
+std::map<void*, size_t> pinned_size;
 
 inline int next_kernel(const gsw::BfsPolicy& p, int32_t d) {
   if (p.policy == GSW_POLICY_FIXED) return p.fixed;
@@ -144,8 +148,21 @@ hipError_t hipFree(void* p) {
   std::free(p);
   return hipSuccess;
 }
-hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { return hipMalloc(p, bytes); }
-hipError_t hipHostFree(void* p) { return hipFree(p); }
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
+  *p = nullptr;
+  if (bytes > fake::pinned_room) return hipErrorOutOfMemory;
+  fake::pinned_room -= bytes;
+  fake::pinned += bytes;
+  hipMalloc(p, bytes);
+  fake::pinned_size[*p] = bytes;
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  fake::pinned -= fake::pinned_size[p];
+  fake::pinned_room += fake::pinned_size[p];
+  fake::pinned_size.erase(p);
+  return hipFree(p);
+}
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
   *d = h;
   return hipSuccess;
@@ -158,6 +175,19 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
   std::memcpy(d, s, n);
   return hipSuccess;
 }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
+  std::memset(d, v, n);
+  return hipSuccess;
+}
+// (the one device array: the scratch memory of gsw_bfs_noalloc)
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  static unsigned char* array = static_cast<unsigned char*>(std::calloc(1, GSW_NOALLOC_SCRATCH_BYTES));
+  *p = array;
+  return hipSuccess;
+}
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 // Everything queued has run: a host that still waits for a record waits for good.
 hipError_t hipStreamQuery(hipStream_t) {
   fake::dev.stalled = true;
