@@ -418,7 +418,13 @@ __device__ constexpr int64_t long_row() {
 // arcs, are taken four at a time, a quarter of the wave each (16 lanes, four
 // arcs per lane in flight).  Quarter q works on the row of the q-th set lane
 // of `rows`, or on none (owner -1).
+// (Top-down up to kMsPushMid: a row has no early exit there, and four of more
+// arcs take a quarter wave each as many steps as they take the wave one after
+// another, and more where their lengths differ.  A directed graph of 16384
+// vertices, 64 sources: 441 us at 512, 331 at 128, 353 with whole waves from
+// 33 arcs on.)
 constexpr int64_t kMsMid = 512;
+constexpr int64_t kMsPushMid = 128;
 struct Quarter {
   int owner, sub;
   int64_t beg, end;
@@ -470,26 +476,40 @@ __device__ __forceinline__ u64 pull_rows_quarter(const MsArgs& a, u64 rows, u64 
   return mine;
 }
 
-// Pushes the word f of every lane in `rows` along its row.
+// Pushes the word f of every lane in `rows` (rows of at most kMsPushMid arcs)
+// along its row; the last one, where it is alone, with the whole wave.
 __device__ __forceinline__ void push_rows_quarter(const MsArgs& a, u64 rows, u64 f, int64_t lane_beg,
                                                   int64_t lane_end) {
-  while (rows) {
+  while (rows & (rows - 1ull)) {
     const Quarter q(rows, lane_beg, lane_end);
     const u64 fw = __shfl(f, q.owner < 0 ? 0 : q.owner);
     push_arcs(a, fw, 0, q.beg + q.sub, q.end, 16);
     rows = drop_four(rows);
+  }
+  if (rows) {
+    const int owner = __ffsll((long long)rows) - 1;
+    const int64_t beg = __shfl((long long)lane_beg, owner), end = __shfl((long long)lane_end, owner);
+    push_arcs(a, __shfl(f, owner), 0, beg + lane_id(), end, 64);
   }
 }
 
 // Pushes the words f (word j, the same in every group) along [beg, end) with
 // the whole wave: group gi taking arcs gi, gi + 64/G, ... with all words, or,
 // where only a few words push, all lanes one word after another.
-constexpr int kMsLight = 3;  // words
+// (At most half a group's words: lanes side by side that take one word each
+// read one line for all of them.  Both words of two spread over the lanes one
+// after the other: 128 sources on a directed graph of 262144 vertices 1.23 ms,
+// each by its own lane 0.99; 100 sources top-down on a random graph of 700001
+// 3.09 and 2.06.)
+template <int G>
+__device__ constexpr int light_words() {
+  return G / 2 < 3 ? G / 2 : 3;
+}
 constexpr int kMsFew = 16;   // frontier vertices of a bitmap word
 template <int G>
 __device__ __forceinline__ void push_row_wave(const MsArgs& a, const Wave<G>& w, u64 f, int64_t beg, int64_t end) {
   u64 nz = __ballot(f != 0ull) & Wave<G>::kGroup;
-  if (G > 1 && __popcll(nz) <= kMsLight) {
+  if (G > 1 && __popcll(nz) <= light_words<G>()) {
     for (; nz; nz &= nz - 1ull) {
       const int jj = __ffsll((long long)nz) - 1;
       push_arcs(a, __shfl(f, jj), jj, beg + w.lane, end, 64);
@@ -534,10 +554,10 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
       const int64_t deg = end - beg;
       const bool own = words && deg <= kMsLong;
       // few frontier vertices in the word would leave most lanes idle
-      const bool light = G > 1 ? __popc(words) <= kMsLight : cnt <= kMsFew;
+      const bool light = G > 1 ? __popc(words) <= light_words<G>() : cnt <= kMsFew;
       if (own && !light && f) push_arcs(a, f, j, beg, end, 1);
       if constexpr (G == 1)
-        push_rows_quarter(a, __ballot(f != 0ull && deg <= kMsMid && (light || deg > kMsLong)), f, beg, end);
+        push_rows_quarter(a, __ballot(f != 0ull && deg <= kMsPushMid && (light || deg > kMsLong)), f, beg, end);
       if constexpr (G > 1) {
         uint32_t left = own && light ? words : 0u;
         while (__any(left != 0u)) {
@@ -548,7 +568,7 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
         }
       }
       // medium rows
-      u64 lm = __ballot(deg > (G == 1 ? kMsMid : kMsLong) && deg <= kMsHeavy && j == 0);
+      u64 lm = __ballot(deg > (G == 1 ? kMsPushMid : kMsLong) && deg <= kMsHeavy && j == 0);
       while (lm) {
         const int src = __ffsll((long long)lm) - 1;
         lm &= lm - 1ull;
