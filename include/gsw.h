@@ -367,7 +367,8 @@ typedef struct {
   float push_to_pull;  /* per source: switch it to bottom-up when its frontier's arcs exceed
                           this fraction of the arcs it has not reached yet (and the sources
                           that would push all together, when their frontiers' arcs, added
-                          source by source, exceed half this fraction of all arcs) ... */
+                          source by source, exceed half this fraction of all arcs, or a
+                          tenth of all arcs where it is below its default) ... */
   float pull_to_push;  /* ... and back to top-down when they fall below this fraction of all arcs */
   int32_t device_ptrs; /* 1: levels (and wide_levels) are device memory; 0: host */
   int32_t graph;       /* 1: replay a captured two-level HIP graph; 0: launch each kernel */

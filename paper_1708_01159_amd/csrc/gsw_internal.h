@@ -390,6 +390,20 @@ __host__ __device__ inline unsigned long long rec_tag(long long d) {
   return (unsigned long long)(((d + 1) & 0x7fff) | 0x8000) << 48;
 }
 
+// Batched BFS: the sources that would push go bottom-up together when their
+// frontiers' arcs, added source by source, exceed this fraction of all arcs.
+// From the default push_to_pull on, half of it (R-MAT scale 20, 1024 sources,
+// us per batch at 10, 3 and 0.5 times: 4900, 4800 and 4300; 64 sources on a
+// random graph of 700001 vertices 1040, 760 and 740).  Below it the sources
+// with large frontiers pull by their own rule and those left push few arcs, so
+// the fraction does not follow it down: 16 sources on R-MAT scale 20 at 0.03
+// 831 us with half of it, 654 with a tenth of all arcs, 712 without this rule;
+// 8 at 0.01 801, 627 and 654; 3 at 0.003 601, 523 and 528.
+constexpr float kMsPushToPull = 0.07f;
+__host__ __device__ inline double ms_together(double push_to_pull) {
+  return push_to_pull < (double)kMsPushToPull ? 0.1 : 0.5 * push_to_pull;
+}
+
 // Kernel launchers (gsw_kernels.hip).
 // iso: bitmap of the vertices without in-arcs (they start visited), or null.
 gsw_status launch_init(const gsw_graph* g, const BfsBase& b, const unsigned long long* iso, int32_t source,

@@ -727,12 +727,9 @@ __global__ void __launch_bounds__(kMsMaxBlock, G >= 4 ? 6 : 4) k_ms_level(MsArgs
 // pulling sources, and one with a small frontier would make every vertex
 // scan its whole row), top-down again once they fall below to_push of all
 // arcs.  Sources that would each push go bottom-up together once the arcs
-// they would push along, source by source, exceed kMsTogether times to_pull
-// of all arcs: the second pass then looks all of them up at once, where the
-// first would read and update masks arc by arc (per call at 10, 3 and 0.5:
-// R-MAT scale 20, 1024 sources 4.9, 4.8 and 4.3 ms; 64 sources on a random
-// graph of 700001 vertices 1.04, 0.76 and 0.74 ms).
-constexpr double kMsTogether = 0.5;
+// they would push along, source by source, exceed ms_together of all arcs:
+// the second pass then looks all of them up at once, where the first would
+// read and update masks arc by arc.
 // With one mask word per vertex, masks are zero outside the frontier, and a
 // lookup reads them at once when at least one vertex in kMsDirect is in the
 // frontier: the bit saves an 8-byte gather only where it is clear, and costs
@@ -802,7 +799,7 @@ __global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats
     }
   }
   __syncthreads();
-  if (pull_ok && (double)s_pushed > kMsTogether * to_pull * (double)arcs) {
+  if (pull_ok && (double)s_pushed > ms_together(to_pull) * (double)arcs) {
     for (int k = t; k < nslots; k += kMsFinal)
       if ((s_p[k >> 6] >> (k & 63)) & 1ull) ctl->pull[k] = 1;
     __syncthreads();
@@ -1407,7 +1404,7 @@ extern "C" {
 void gsw_msbfs_opts_default(gsw_msbfs_opts* o) {
   if (!o) return;
   std::memset(o, 0, sizeof *o);
-  o->push_to_pull = 0.07f;
+  o->push_to_pull = kMsPushToPull;
   o->pull_to_push = 0.01f;
   o->graph = 1;
   o->block_size = kMsBlock;
@@ -1604,7 +1601,7 @@ struct gsw_session {
   std::vector<u64> freed;      // slots freed since the last boundary (made inert then)
   int64_t queued = 0;          // levels queued on the stream
   int64_t done = 0;            // levels whose record has been read
-  float push_to_pull = 0.07f, pull_to_push = 0.01f;
+  float push_to_pull = kMsPushToPull, pull_to_push = 0.01f;
   hipStream_t stream = nullptr;
   size_t bytes = 0;
   std::mutex mu;       // host state shared with admit / fetch / info

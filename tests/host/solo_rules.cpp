@@ -1,4 +1,5 @@
-// Rules of the single-workgroup launches that can be checked without a GPU.
+// Rules of the single-workgroup launches and of the batch's directions that can
+// be checked without a GPU.
 // Prints "ok" and exits 0 when every check holds.
 #include <cstdio>
 
@@ -29,6 +30,11 @@ int main() {
   // length, which must still be one that no sum is taken of
   const int64_t lens[] = {most + 1, 0x7ffffffell, 0x7fffffffll, 0x80000000ll, 0x100000000ll, 0x7fffffffffll};
   for (int64_t deg : lens) CHECK(solo_row_length(deg) > kSoloMaxArcs);
+  // Batched sources go bottom-up together by a rule of its own: it does not
+  // follow a push_to_pull below the default down, and one that never pulls
+  // keeps it from doing so.
+  for (float f : {0.0f, 0.0001f, 0.003f, 0.01f, 0.03f, 0.0699f}) CHECK(ms_together(f) >= 0.5 * (double)kMsPushToPull);
+  for (float f : {kMsPushToPull, 0.1f, 0.2f, 1.0f, 1e9f}) CHECK(ms_together(f) == 0.5 * (double)f);
   std::puts("ok");
   return 0;
 }

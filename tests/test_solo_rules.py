@@ -1,5 +1,5 @@
-"""Rules of the single-workgroup launches, checked on the CPU in a small
-program that includes the library's internal header."""
+"""Rules of the single-workgroup launches and of the batch's directions, checked
+on the CPU in a small program that includes the library's internal header."""
 import os
 import shutil
 import subprocess
