@@ -519,13 +519,24 @@ __device__ __forceinline__ void push_row_wave(const MsArgs& a, const Wave<G>& w,
   }
 }
 
+// Whether hub rows are looked up in chunks, for bottom-up sources qm.  One or
+// two sources in one word are found in a row's first steps, which a wave of
+// the second pass takes with nothing before it: R-MAT scale 20 in chunks and
+// there, us: 1 source 414 and 384, 2 463 and 430; but 4 (at push_to_pull 0.2 on
+// scale 18) 258 and 302.
+constexpr int kMsHubSources = 2;
+template <int G>
+__device__ __forceinline__ bool hub_chunks(u64 qm) {
+  return G > 1 || __popcll(qm) > kMsHubSources;
+}
+
 // The level's first pass.  Every frontier vertex u of a top-down source: lane
 // j pushes fr[u][j] & pmask[j] along u's arcs.  A group few of whose words
 // push (a young source has one bit in one word) spreads each such word's row
 // over its lanes instead of leaving it to the word's own lane.  Then the rows
 // of the chunk list, one chunk per wave, so that a hub's row is spread over
 // the grid: top-down as above, and bottom-up for the hub's own needs, joined
-// in its accumulator (the second pass leaves these rows out).
+// in its accumulator (the second pass then leaves these rows out).
 template <int G>
 __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
   const bool any_push = a.ctl->any_push != 0, any_pull = a.ctl->any_pull != 0;
@@ -535,6 +546,8 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
   const int j = w.j;
   const u64 pm = j < a.W ? a.ctl->pmask[j] : 0ull;
   const u64 qm = j < a.W ? a.ctl->qmask[j] : 0ull;
+  const bool hubs = hub_chunks<G>(qm);
+  if (!any_push && !hubs) return;
   const int64_t nwords = any_push ? (a.n + 63) / 64 : 0;
   for (int64_t wd = w.wave; wd < nwords; wd += w.nwaves) {
     const u64 word = a.fbm[wd];
@@ -583,7 +596,7 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
     const int64_t u = (int64_t)(ent >> 32);
     const bool in = (a.fbm[u >> 6] >> (u & 63)) & 1ull;
     const u64 fw = in && pm ? (a.fr[u * a.W + j] & pm) : 0ull;
-    const u64 need = qm ? ~a.vis[u * a.W + j] & qm : 0ull;
+    const u64 need = qm && hubs ? ~a.vis[u * a.W + j] & qm : 0ull;
     const bool push = __any(fw != 0ull), pull = __any(need != 0ull);
     if (!push && !pull) continue;
     const int64_t ci = (int64_t)(ent & 0xffffffffull);
@@ -660,7 +673,8 @@ __global__ void __launch_bounds__(kMsMaxBlock, G >= 4 ? 6 : 4) k_ms_level(MsArgs
       u64 acc = pull_row_group<G>(a, w, want && !lng && beg < end, need, beg, end);
       if constexpr (G == 1)
         acc |= pull_rows_quarter(a, __ballot(lng && end - beg <= kMsMid), need, beg, end);
-      u64 lm = __ballot(lng && end - beg > (G == 1 ? kMsMid : 0) && end - beg <= kMsHeavy && j == 0);
+      u64 lm = __ballot(lng && end - beg > (G == 1 ? kMsMid : 0) && (end - beg <= kMsHeavy || !hub_chunks<G>(qm)) &&
+                        j == 0);
       while (lm) {
         const int src = __ffsll((long long)lm) - 1;
         lm &= lm - 1ull;
