@@ -362,7 +362,7 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   // the largest degree bounds the arcs, none is ever handed back, and there
   // such launches follow one another.
   bool solo = b.solo && solo_eligible(k0, 1, 1, 1, b, kSoloMaxGlobal) &&
-              !(pol.hubs && b.deg_max > kSoloArcs && !solo_whole(b.n, b.nnz));
+              !(pol.hubs && !solo_takes(k0, 1, b.deg_max, b.deg_max) && !solo_whole(b.n, b.nnz));
   const bool whole = solo_whole(b.n, b.nnz);
   const bool solo_always = (long long)b.deg_max * kSoloMax <= kSoloMaxArcs || whole;
   int64_t solo_j = -2;  // the latest such launch

@@ -1723,9 +1723,10 @@ struct SoloLds {
   u64 esum[3];       // arcs of the level's frontier
   uint32_t cnt[3];   // next-frontier entries
   uint32_t nlong[3]; // long rows set aside
+  uint32_t longest[3];  // arcs of the longest row of at least kSoloHubMin
   int32_t go;        // wave 0's decision: the next level runs here
   int32_t next, nflags, disc;  // ... else its kernel and flags, and the vertices discovered
-  int32_t limit;     // arcs the next level may have where they are counted
+  int32_t kernel;    // the next level's kernel, for its limit where arcs are counted
   int32_t pull;      // (whole graph) the next level is bottom-up
   uint32_t fr[kSoloMax / 32];  // (whole graph) the frontier's bitmap in such a level
   // of level lv of this launch, for its record
@@ -2047,6 +2048,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     L.esum[tid] = 0ull;
     L.cnt[tid] = 0u;
     L.nlong[tid] = 0u;
+    L.longest[tid] = 0u;
   }
   const bool lds_tree = tree && p.t_nodes <= kSoloLdsTree;
   if (lds_tree && tid < p.t_nodes) {
@@ -2065,7 +2067,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
   bool leaf_push = kernel_base(leaf_next) <= last_base;  // ... which may go on here
   // frontiers whose arcs the largest degree bounds
   const int32_t bound_arcs = b.deg_max > 0 ? (int32_t)(kSoloMaxArcs / b.deg_max) : (int32_t)kSoloMax;
-  int32_t limit = solo_arc_limit(k_id, nf);
+  int32_t k_level = k_id;  // the level's kernel, in every wave
   const int32_t levels_max = b.solo;
   int levels = 0;  // completed here
   int slot = 0;
@@ -2125,6 +2127,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       L.esum[slot1] = 0ull;
       L.cnt[slot1] = 0u;
       L.nlong[slot1] = 0u;
+      L.longest[slot1] = 0u;
     }
     bool lng[kSoloSlots] = {};
     const bool filter = nf > kSoloFilter;
@@ -2136,6 +2139,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
 #pragma unroll
         for (int q = 0; q < kSoloSlots; ++q) {
           const int64_t deg = end[q] - beg[q];
+          if (check && deg >= kSoloHubMin) atomicMax(&L.longest[slot], (uint32_t)solo_row_length(deg));
           if (deg > kSoloShort) {
             const uint32_t at = atomicAdd(&L.nlong[slot], 1u);
             if (at < (uint32_t)kSoloLong) {
@@ -2160,7 +2164,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     if (!HeadOnly && !pull && (check || b.deg_max > kSoloShort)) {
       lds_barrier();
       nlong = L.nlong[slot] < (uint32_t)kSoloLong ? L.nlong[slot] : (uint32_t)kSoloLong;
-      if (check && L.esum[slot] > (u64)limit) {
+      if (check && !solo_takes(k_level, nf, (int64_t)L.esum[slot], (int64_t)L.longest[slot])) {
         // too many arcs for one workgroup: the level goes back to the level
         // kernel untouched (on the first level nothing has changed at all)
         if (lv == 0) {
@@ -2282,7 +2286,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       const int32_t next = nn > 0 ? leaf_next : kCtlDone, nflags = nn > 0 ? leaf_flags : 0;
       if (tid == 0) {
         L.go = go ? 1 : 0;
-        if (!HeadOnly && !Whole) L.limit = solo_arc_limit(leaf_next, nn);
+        if (!HeadOnly && !Whole) L.kernel = leaf_next;
         if (Whole) L.pull = kernel_base(leaf_next) == GSW_K_PULL_BITMAP ? 1 : 0;
         if (!go) {
           L.next = next;
@@ -2307,7 +2311,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     }
     lds_barrier();
     const bool go = __builtin_amdgcn_readfirstlane(L.go) != 0;
-    if (!HeadOnly && !Whole) limit = L.limit;
+    if (!HeadOnly && !Whole) k_level = __builtin_amdgcn_readfirstlane(L.kernel);
     if (Whole) pull = __builtin_amdgcn_readfirstlane(L.pull) != 0;
     levels = lv + 1;
     ++d;

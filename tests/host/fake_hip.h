@@ -5,6 +5,7 @@
 // one level or half of one, run several, or pass the slot on.
 #pragma once
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -105,7 +106,8 @@ gsw_status launch_level_solo(const gsw_graph*, const BfsBase& b, const BfsPolicy
   const int64_t bound = b.deg_max > 0 ? kSoloMaxArcs / b.deg_max : kSoloMax;
   for (int lv = 0;; ++lv) {
     if (!head_only && !whole && c.nf > bound &&
-        fake::dev.script.arcs[(size_t)c.d] > solo_arc_limit(c.kernel, (int32_t)c.nf)) {
+        !solo_takes(c.kernel, (int32_t)c.nf, fake::dev.script.arcs[(size_t)c.d],
+                    std::min<int64_t>(b.deg_max, fake::dev.script.arcs[(size_t)c.d]))) {
       ++fake::dev.handed_back;
       if (lv > 0) *cn = c;  // (untouched on the first level)
       return GSW_OK;

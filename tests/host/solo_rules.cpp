@@ -1,6 +1,7 @@
 // Rules of the single-workgroup launches and of the batch's directions that can
 // be checked without a GPU.
 // Prints "ok" and exits 0 when every check holds.
+#include <algorithm>
 #include <cstdio>
 
 #include "../../paper_1708_01159_amd/csrc/gsw_internal.h"
@@ -17,15 +18,27 @@ using namespace gsw;
 
 int main() {
   // A row of a level that a launch takes is walked over exactly its arcs: at
-  // most kSoloMaxArcs in all by the largest degree or by a count, any number
-  // up to kSoloWholeArcs on a graph searched to the end.
-  const int64_t most = kSoloMaxArcs > kSoloWholeArcs ? kSoloMaxArcs : kSoloWholeArcs;
+  // most kSoloMaxArcs in all by the largest degree or by a count, kSoloHubMax
+  // where one row is two thirds of them, any number up to kSoloWholeArcs on a graph
+  // searched to the end.
+  int64_t most = kSoloMaxArcs > kSoloWholeArcs ? kSoloMaxArcs : kSoloWholeArcs;
+  if (kSoloHubMax > most) most = kSoloHubMax;
   for (int64_t deg = 0; deg <= most; ++deg) {
     if (solo_row_length(deg) != deg) std::fprintf(stderr, "row of %lld arcs\n", (long long)deg);
     CHECK(solo_row_length(deg) == deg);
   }
   for (int k = 0; k < GSW_N_KERNELS; ++k)
-    for (int32_t nf = 1; nf <= kSoloMax; ++nf) CHECK(solo_arc_limit(k, nf) <= kSoloMaxArcs);
+    for (int32_t nf = 1; nf <= kSoloMax; ++nf) {
+      CHECK(solo_arc_limit(k, nf) <= kSoloMaxArcs);
+      CHECK(!solo_takes(k, nf, most + 1, most + 1));
+    }
+  // a hub's row that the level kernel would leave to one workgroup, alone and
+  // among others, but not where its arcs are spread over the grid
+  for (int64_t arcs : {kSoloHubMin, (int64_t)16000, (int64_t)49998, kSoloHubMax}) {
+    const int64_t most_of_it = std::max(kSoloHubMin, arcs * 7 / 10);
+    CHECK(solo_takes(GSW_K_PUSH_VERTEX, 1, arcs, arcs) && solo_takes(GSW_K_PUSH_WAVE16, 300, arcs, most_of_it));
+    CHECK(!solo_takes(GSW_K_PUSH_VERTEX, 300, arcs, arcs / 2) && !solo_takes(GSW_K_PUSH_EDGE, 1, arcs, arcs));
+  }
   // a longer row's level is handed back, by its counted arcs and not by this
   // length, which must still be one that no sum is taken of
   const int64_t lens[] = {most + 1, 0x7ffffffell, 0x7fffffffll, 0x80000000ll, 0x100000000ll, 0x7fffffffffll};

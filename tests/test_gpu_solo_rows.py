@@ -1,6 +1,7 @@
-"""A row of as many arcs as a single-workgroup launch takes (8192), one fewer
-and one more, with a row of another component behind it in the CSR: nothing
-of that component is reached."""
+"""A row of as many arcs as a single-workgroup launch takes (8192; 9216 to 65536
+where it is most of the level and its kernel would leave it to one workgroup),
+one fewer and one more, with a row of another component behind it in the CSR:
+nothing of that component is reached."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,7 @@ from paper_1708_01159_amd import gsw
 pytestmark = pytest.mark.gpu
 
 SOLO = 4  # trace flag of a level run by a single-workgroup launch
-HUB, NEXT, ROOT = 2, 3, 20001  # the row behind the hub's is the first of another component
+HUB, NEXT, ROOT = 2, 3, 70001  # the row behind the hub's is the first of another component
 
 
 def _graph(arcs, larger, sinks):
@@ -20,24 +21,24 @@ def _graph(arcs, larger, sinks):
     that the hub's arcs are counted; `sinks`: the hub's level has 15 vertices
     without out-arcs beside it (directed)."""
     leaves = arcs if sinks else arcs - 1  # (symmetric: the arc back to the root is one of the hub's)
-    src, dst = [HUB] * leaves + [NEXT] * 40, list(range(4, leaves + 4)) + list(range(13000, 13040))
+    src, dst = [HUB] * leaves + [NEXT] * 40, list(range(4, leaves + 4)) + list(range(69000, 69040))
     if larger:
-        src += [ROOT + 20] * 9000
-        dst += list(range(30000, 39000))
+        src += [ROOT + 20] * (arcs + 808)
+        dst += list(range(80000, 80000 + arcs + 808))
     src += [ROOT] * (16 if sinks else 1)
     dst += [HUB] + (list(range(ROOT + 1, ROOT + 16)) if sinks else [])
-    return gg.from_edges(60000, src, dst, symmetrize=not sinks, name="hub")
+    return gg.from_edges(160000, src, dst, symmetrize=not sinks, name="hub")
 
 
 @pytest.mark.parametrize("sinks", [False, True])
 @pytest.mark.parametrize("larger", [False, True])
-@pytest.mark.parametrize("arcs", [8191, 8192, 8193])
+@pytest.mark.parametrize("arcs", [8191, 8192, 8193, 9215, 9216, 30000, 65536, 65537])
 def test_row_of_as_many_arcs_as_one_workgroup_takes(arcs, larger, sinks):
     import torch
 
     g = _graph(arcs, larger, sinks)
     deg = g.degrees()
-    assert deg[HUB] == arcs and deg[NEXT] == 40 and deg.max() == (9000 if larger else arcs)
+    assert deg[HUB] == arcs and deg[NEXT] == 40 and deg.max() == (arcs + 808 if larger else arcs)
     G = gsw.Graph.from_csr(g.offs, g.cols)
     check = checks.check_bfs_directed if sinks else checks.check_bfs
     for s in (HUB, ROOT):
@@ -51,9 +52,9 @@ def test_row_of_as_many_arcs_as_one_workgroup_takes(arcs, larger, sinks):
                 assert np.array_equal(lv[0], ref)
                 check(g.offs, g.cols, s, lv[0], pa[0])
                 assert [t.n_frontier for t in tr] == sizes.tolist()
-                # taken by the largest degree, or counted; 8193 arcs never are
+                # taken by the largest degree, or counted
                 by_degree = sizes[hub] * int(deg.max()) <= 8192
-                counted = arcs <= (2048 if kernel == gsw.PUSH_EDGE else 8192)
+                counted = kernel != gsw.PUSH_EDGE and (arcs <= 8192 or 9216 <= arcs <= 65536)
                 assert bool(tr[hub].flags & SOLO) == (by_degree or counted)
             lv = torch.full((1, g.n), 9, dtype=torch.int32, device="cuda")
             gsw.bfs_noalloc(G, [s], lv, policy="fixed", kernel=kernel)
