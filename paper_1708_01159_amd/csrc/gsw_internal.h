@@ -317,16 +317,21 @@ constexpr int64_t kSoloVisWords = 16384;  // 64-bit words of a visited bitmap th
 __host__ __device__ inline int32_t solo_arc_limit(int k, int32_t nf) {
   return kernel_base(k) != GSW_K_PUSH_EDGE && nf <= kSoloFewRows ? (int32_t)kSoloMaxArcs : (int32_t)kSoloArcs;
 }
-// ... and a level under such a kernel of which one row is two thirds: the
-// level kernel leaves that row to one workgroup of 256 threads (us for a row
-// there and here: 9000 arcs 48 and 24, 16000 95 and 51, 40000 350 and 198,
-// 60000 589 and 337; push_edge spreads it over the grid in 9 to 20).  (From
-// kSoloHubMin arcs on: just above the common limit a level goes by that.)
+// ... and a larger level under such a kernel of which most arcs would fall to
+// one of its workgroups: that takes kPushMinPer frontier entries in a row, of
+// which `share` is the largest sum, and 256 threads walk them at half this
+// launch's rate (us there and here: one row of 9000 arcs 48 and 24, 16000 95
+// and 51, 40000 350 and 198, 60000 589 and 337; 22 rows with some 13000 arcs
+// 64 and 32; push_edge spreads them over the grid in 9 to 20).  Just above a
+// limit levels go by that: a few rows from kSoloHubMin arcs on, more from twice
+// kSoloArcs.
+constexpr int64_t kPushMinPer = 16;
 constexpr int64_t kSoloHubMin = 9216;
 constexpr int64_t kSoloHubMax = 65536;
-__host__ __device__ inline bool solo_takes(int k, int32_t nf, int64_t arcs, int64_t longest) {
+__host__ __device__ inline bool solo_takes(int k, int32_t nf, int64_t arcs, int64_t share) {
   if (arcs <= solo_arc_limit(k, nf)) return true;
-  return kernel_base(k) != GSW_K_PUSH_EDGE && longest >= kSoloHubMin && arcs <= kSoloHubMax && 2 * arcs <= 3 * longest;
+  return kernel_base(k) != GSW_K_PUSH_EDGE && arcs >= (nf <= kSoloFewRows ? kSoloHubMin : 2 * kSoloArcs) &&
+         arcs <= kSoloHubMax && 3 * arcs <= 5 * share;
 }
 // The length that a launch notes for a row it sets aside: the row's own, for
 // whatever limit a level is taken under.  (One that 32 bits do not hold is of

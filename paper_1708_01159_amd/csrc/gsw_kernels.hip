@@ -153,7 +153,7 @@ __host__ __device__ inline int64_t div_up(int64_t x, int64_t y) { return (x + y 
 // workgroup, so a small frontier holding hubs has them walked by many
 // workgroups at once instead of by the few that a full 256 entries each
 // would give it.
-constexpr int64_t kPushMinPer = 16;
+static_assert((kPushMinPer & (kPushMinPer - 1)) == 0 && kPushMinPer <= 64, "k_level_solo sums them by lanes");
 __host__ __device__ inline uint32_t push_per(int64_t n_in, int32_t grid_max) {
   const int64_t per = div_up(n_in, grid_max);
   return (uint32_t)(per < kPushMinPer ? kPushMinPer : (per > kBlock ? kBlock : per));
@@ -1723,7 +1723,7 @@ struct SoloLds {
   u64 esum[3];       // arcs of the level's frontier
   uint32_t cnt[3];   // next-frontier entries
   uint32_t nlong[3]; // long rows set aside
-  uint32_t longest[3];  // arcs of the longest row of at least kSoloHubMin
+  uint32_t share[3];    // most arcs of kPushMinPer entries in a row (solo_takes)
   int32_t go;        // wave 0's decision: the next level runs here
   int32_t next, nflags, disc;  // ... else its kernel and flags, and the vertices discovered
   int32_t kernel;    // the next level's kernel, for its limit where arcs are counted
@@ -2048,7 +2048,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     L.esum[tid] = 0ull;
     L.cnt[tid] = 0u;
     L.nlong[tid] = 0u;
-    L.longest[tid] = 0u;
+    L.share[tid] = 0u;
   }
   const bool lds_tree = tree && p.t_nodes <= kSoloLdsTree;
   if (lds_tree && tid < p.t_nodes) {
@@ -2127,7 +2127,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
       L.esum[slot1] = 0ull;
       L.cnt[slot1] = 0u;
       L.nlong[slot1] = 0u;
-      L.longest[slot1] = 0u;
+      L.share[slot1] = 0u;
     }
     bool lng[kSoloSlots] = {};
     const bool filter = nf > kSoloFilter;
@@ -2139,7 +2139,13 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
 #pragma unroll
         for (int q = 0; q < kSoloSlots; ++q) {
           const int64_t deg = end[q] - beg[q];
-          if (check && deg >= kSoloHubMin) atomicMax(&L.longest[slot], (uint32_t)solo_row_length(deg));
+          if (check) {
+            int64_t sum = deg;  // of kPushMinPer entries
+#pragma unroll
+            for (int off = 1; off < (int)kPushMinPer; off <<= 1) sum += __shfl_xor(sum, off);
+            if ((lane & (int)(kPushMinPer - 1)) == 0 && sum > kSoloArcs)
+              atomicMax(&L.share[slot], (uint32_t)solo_row_length(sum));
+          }
           if (deg > kSoloShort) {
             const uint32_t at = atomicAdd(&L.nlong[slot], 1u);
             if (at < (uint32_t)kSoloLong) {
@@ -2164,7 +2170,7 @@ __global__ void __launch_bounds__(kSoloBlock) k_level_solo(BfsBase b, BfsPolicy 
     if (!HeadOnly && !pull && (check || b.deg_max > kSoloShort)) {
       lds_barrier();
       nlong = L.nlong[slot] < (uint32_t)kSoloLong ? L.nlong[slot] : (uint32_t)kSoloLong;
-      if (check && !solo_takes(k_level, nf, (int64_t)L.esum[slot], (int64_t)L.longest[slot])) {
+      if (check && !solo_takes(k_level, nf, (int64_t)L.esum[slot], (int64_t)L.share[slot])) {
         // too many arcs for one workgroup: the level goes back to the level
         // kernel untouched (on the first level nothing has changed at all)
         if (lv == 0) {

@@ -19,7 +19,7 @@ using namespace gsw;
 int main() {
   // A row of a level that a launch takes is walked over exactly its arcs: at
   // most kSoloMaxArcs in all by the largest degree or by a count, kSoloHubMax
-  // where one row is two thirds of them, any number up to kSoloWholeArcs on a graph
+  // where a few rows hold most of them, any number up to kSoloWholeArcs on a graph
   // searched to the end.
   int64_t most = kSoloMaxArcs > kSoloWholeArcs ? kSoloMaxArcs : kSoloWholeArcs;
   if (kSoloHubMax > most) most = kSoloHubMax;
@@ -32,11 +32,10 @@ int main() {
       CHECK(solo_arc_limit(k, nf) <= kSoloMaxArcs);
       CHECK(!solo_takes(k, nf, most + 1, most + 1));
     }
-  // a hub's row that the level kernel would leave to one workgroup, alone and
-  // among others, but not where its arcs are spread over the grid
+  // a hub's row, or a few in a row, that the level kernel would leave to one
+  // workgroup, but not where its arcs are spread over the grid
   for (int64_t arcs : {kSoloHubMin, (int64_t)16000, (int64_t)49998, kSoloHubMax}) {
-    const int64_t most_of_it = std::max(kSoloHubMin, arcs * 7 / 10);
-    CHECK(solo_takes(GSW_K_PUSH_VERTEX, 1, arcs, arcs) && solo_takes(GSW_K_PUSH_WAVE16, 300, arcs, most_of_it));
+    CHECK(solo_takes(GSW_K_PUSH_VERTEX, 1, arcs, arcs) && solo_takes(GSW_K_PUSH_WAVE16, 300, arcs, arcs * 2 / 3));
     CHECK(!solo_takes(GSW_K_PUSH_VERTEX, 300, arcs, arcs / 2) && !solo_takes(GSW_K_PUSH_EDGE, 1, arcs, arcs));
   }
   // a longer row's level is handed back, by its counted arcs and not by this

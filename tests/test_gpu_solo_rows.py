@@ -60,3 +60,34 @@ def test_row_of_as_many_arcs_as_one_workgroup_takes(arcs, larger, sinks):
             gsw.bfs_noalloc(G, [s], lv, policy="fixed", kernel=kernel)
             assert np.array_equal(lv[0].cpu().numpy(), ref)
     G.close()
+
+
+@pytest.mark.parametrize("rows,arcs", [(17, 200), (17, 500), (20, 900), (22, 3000), (40, 400), (64, 64), (300, 30)])
+def test_a_few_long_rows_among_short_ones(rows, arcs):
+    """A level of `rows` long rows, then of as many short ones behind them: taken
+    where most arcs would fall to one workgroup of a lane-per-row kernel."""
+    n = 200000
+    rng = np.random.default_rng(rows)
+    front = np.arange(1, 2 * rows + 1)
+    src = np.concatenate([np.zeros(2 * rows, np.int64), np.repeat(front[:rows], arcs), front[rows:]])
+    dst = np.concatenate([front, rng.integers(2 * rows + 1, n, rows * arcs + rows)])
+    g = gg.from_edges(n, src, dst, symmetrize=False, name="few")
+    G = gsw.Graph.from_csr(g.offs, g.cols)
+    ref = oracle.levels(g.offs, g.cols, 0)
+    for kernel in (gsw.PUSH_VERTEX, gsw.PUSH_WAVE16, gsw.PUSH_EDGE):
+        for count_arcs in (False, True):
+            lv, pa, tr = gsw.bfs(G, [0, 0], policy="fixed", kernel=kernel, count_arcs=count_arcs)
+            for i in range(2):
+                assert np.array_equal(lv[i], ref)
+                checks.check_bfs_directed(g.offs, g.cols, 0, lv[i], pa[i])
+            e = int(g.degrees()[1:2 * rows + 1].sum())
+            solo = bool(tr[1].flags & SOLO)
+            if 2 * rows * int(g.degrees().max()) <= 8192:  # by the largest degree, whatever the kernel
+                assert solo
+            elif kernel == gsw.PUSH_EDGE or e > 65536:
+                assert not solo or e <= 2048
+            elif rows <= 22 and 4096 <= e <= 65536:
+                assert solo
+            elif rows >= 40 and e > 2048:
+                assert not solo
+    G.close()
