@@ -34,3 +34,20 @@ def test_long_rows_beside_each_other(rows):
                 assert np.array_equal(lv[0], ref), (length, short)
                 checks.check_bfs_directed(g.offs, g.cols, 0, lv[0], pa[0])
             G.close()
+
+
+@pytest.mark.parametrize("n,degree", [(65000, 8), (66000, 8), (300000, 2), (300000, 8), (66000, -8)])
+def test_summary_of_small_frontiers(n, degree):
+    """All levels bottom-up, with fewer and more unvisited in-arcs than a
+    summary of a small frontier is made for; degree < 0: directed."""
+    rng = np.random.default_rng(n + degree)
+    m = n * abs(degree)
+    g = gg.from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m), symmetrize=degree > 0, name="random")
+    G = gsw.Graph.from_csr(g.offs, g.cols)
+    srcs = [int(s) for s in gg.pick_sources(g, 2, 3)]
+    lv, pa, tr = gsw.bfs(G, srcs, policy="fixed", kernel=gsw.PULL_BITMAP)
+    for i, s in enumerate(srcs):
+        ref = oracle.levels(g.offs, g.cols, s)
+        assert np.array_equal(lv[i], ref)
+        (checks.check_bfs if degree > 0 else checks.check_bfs_directed)(g.offs, g.cols, s, lv[i], pa[i])
+    G.close()
