@@ -33,6 +33,7 @@ constexpr int kSoloAhead = 2;
 constexpr int32_t kSoloLevels = 32;
 constexpr int64_t kSoloDeep = 32;
 constexpr int64_t kSoloVisSmall = 2048;
+constexpr int64_t kSoloHold = 15;  // levels without one after one was handed back, at most
 
 // Launch size for queued levels: the full grid, or kSmallLaunch workgroups
 // while the search is in a quiet phase -- the latest frontier the host knows
@@ -377,6 +378,13 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
   // such launch behind it found nothing to do, 4-5 us).  Until then no more is
   // queued than the next level takes if it is the one handed back.
   bool in_solo = false;
+  // A level that is handed back has paid for its launch in vain (4-6 us), and
+  // where frontiers stay the next one would too (layers of 1500 vertices with
+  // 12 to 24 arcs each: 28.4 us a level under push_wave4, 21.6 with level
+  // kernels alone).  So after one the next such launch waits for a frontier of
+  // half the size, or for 1, 3, 7 and then kSoloHold levels, until one is taken.
+  int64_t handed = 0;             // vertices of the latest level handed back (0: one was taken since)
+  int64_t hold = 0, skipped = 0;  // levels to go by after it, and gone by
   int64_t first_d = 0, latest = 0;  // the latest record's launch and the first level it ran
   int want = solo ? (whole ? 1 : kSoloAhead + 1) : kAhead + level_launches(k0, 1) - 1;
   // Whatever `want` says, the launches queued behind the latest record must be
@@ -432,10 +440,20 @@ gsw_status run_levels(gsw_graph* g, Workspace& w, const unsigned long long* iso,
     if (r.launch + 1 > consumed) consumed = r.launch + 1;
     ++*rows;
     if (nn == 0) break;
+    if ((r.flags & kFlagSolo) != 0) {
+      handed = hold = 0;
+    } else if (solo && !solo_always && solo_j >= first_j && solo_j < r.launch && r.nf <= solo_max_of(solo_j)) {
+      handed = r.nf;
+      hold = hold < kSoloHold ? 2 * hold + 1 : hold;
+      skipped = 0;
+    } else {
+      ++skipped;
+    }
     const int64_t lim = lds_fits && (d + 1 >= kSoloDeep || lds_from == 0) ? kSoloMax : kSoloMaxGlobal;
     next_k = nk;
     next_n = nn;
-    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, b, lim);
+    solo = b.solo && solo_eligible(nk, nn, r.nf, r.disc + nn, b, lim) &&
+           (handed == 0 || 2 * nn <= handed || skipped >= hold);
     in_solo = solo && (r.flags & kFlagSolo) != 0 && nn <= solo_max_of(r.launch);
     if (r.launch != latest) first_d = d;
     latest = r.launch;

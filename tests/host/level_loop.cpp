@@ -157,6 +157,24 @@ int main() {
   doubled[0] = 1;
   doubled.insert(doubled.end(), {2049, 4096, 2048, 4096, 30, 10});
   cases.push_back({"doubled past depth 32", 900000, 3600000, 4, layers(doubled, 3), edge});
+  // Levels that are handed back one after another: few launches in vain, and
+  // short levels behind one are taken again.
+  std::vector<int32_t> even(400, 1500), hubs(400, 1);
+  even[0] = 1;
+  for (int k : {GSW_K_PUSH_EDGE, GSW_K_PUSH_WAVE4}) {
+    Case c{"1500 a level, 24 arcs a row", 700000, 16800000, 30, layers(even, 24), {k}};
+    Case h{"a path with hubs", 700000, 16800000, 100000, layers(hubs, 3), {k}};
+    for (size_t d = 5; d < hubs.size(); d += 40) h.script.arcs[d] = 100000;
+    c.n = 60000;
+    if (!run(c)) return 1;
+    const int64_t back = fake::dev.handed_back;
+    if (!run(h)) return 1;
+    if (back > 40 || fake::dev.solo_levels < 300) {
+      std::fprintf(stderr, "%lld of 400 even levels handed back; %lld of 400 on a path taken\n", (long long)back,
+                   (long long)fake::dev.solo_levels);
+      return 1;
+    }
+  }
   std::mt19937_64 rng(20);
   for (int i = 0; i < 60000; ++i) cases.push_back(random_case(rng));
   for (const Case& c : cases)
