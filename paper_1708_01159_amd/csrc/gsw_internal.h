@@ -420,6 +420,20 @@ __host__ __device__ inline double ms_together(double push_to_pull) {
   return push_to_pull < (double)kMsPushToPull ? 0.1 : 0.5 * push_to_pull;
 }
 
+// Batched BFS: whether the rows of hubs are looked up in chunks by the first
+// pass, for `pulling` bottom-up sources of W mask words; `small`: some of them
+// would not pull by its own frontier.  One or two sources with large frontiers
+// are found in a row's first steps, which a wave of the second pass takes with
+// nothing before it: R-MAT scale 20 in chunks and there, us: 1 source 414 and
+// 384, 2 463 and 430; but 4 (at push_to_pull 0.2 on scale 18) 258 and 302.  Where
+// a frontier is small a wave may walk whole rows in vain, one after another:
+// 400000 vertices, 40 hubs of some 7600 arcs in one word of the bitmap, two
+// sources that go bottom-up together 4042 us there, 370 in chunks.
+constexpr int kMsHubSources = 2;
+__host__ __device__ inline bool ms_hub_chunks(int W, int pulling, bool small) {
+  return W > 1 || pulling > kMsHubSources || small;
+}
+
 // Kernel launchers (gsw_kernels.hip).
 // iso: bitmap of the vertices without in-arcs (they start visited), or null.
 gsw_status launch_init(const gsw_graph* g, const BfsBase& b, const unsigned long long* iso, int32_t source,

@@ -87,6 +87,7 @@ struct MsCtl {
   double to_push;        // top-down again once frontier arcs < to_push x all arcs
   u64 arcs;              // arcs of the graph
   int32_t any_push, any_pull;
+  int32_t hubs;          // hub rows are looked up in chunks by this level's first pass
   int32_t direct;        // one mask word: bottom-up lookups skip the frontier bitmap this level
   long long d;           // this level's index (a session counts levels for as long as it lives)
   int32_t pull_ok;       // bottom-up allowed (symmetric graph)
@@ -519,17 +520,6 @@ __device__ __forceinline__ void push_row_wave(const MsArgs& a, const Wave<G>& w,
   }
 }
 
-// Whether hub rows are looked up in chunks, for bottom-up sources qm.  One or
-// two sources in one word are found in a row's first steps, which a wave of
-// the second pass takes with nothing before it: R-MAT scale 20 in chunks and
-// there, us: 1 source 414 and 384, 2 463 and 430; but 4 (at push_to_pull 0.2 on
-// scale 18) 258 and 302.
-constexpr int kMsHubSources = 2;
-template <int G>
-__device__ __forceinline__ bool hub_chunks(u64 qm) {
-  return G > 1 || __popcll(qm) > kMsHubSources;
-}
-
 // The level's first pass.  Every frontier vertex u of a top-down source: lane
 // j pushes fr[u][j] & pmask[j] along u's arcs.  A group few of whose words
 // push (a young source has one bit in one word) spreads each such word's row
@@ -546,7 +536,7 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
   const int j = w.j;
   const u64 pm = j < a.W ? a.ctl->pmask[j] : 0ull;
   const u64 qm = j < a.W ? a.ctl->qmask[j] : 0ull;
-  const bool hubs = hub_chunks<G>(qm);
+  const bool hubs = a.ctl->hubs != 0;
   if (!any_push && !hubs) return;
   const int64_t nwords = any_push ? (a.n + 63) / 64 : 0;
   for (int64_t wd = w.wave; wd < nwords; wd += w.nwaves) {
@@ -635,6 +625,7 @@ __global__ void __launch_bounds__(kMsMaxBlock, G >= 4 ? 6 : 4) k_ms_level(MsArgs
   const int j = w.j;
   const bool lane_live = j < a.W;
   const MsCtl* ctl = a.ctl;
+  const bool hubs = G > 1 || ctl->hubs != 0;
   const long long d = ctl->d;
   const bool any_push = ctl->any_push != 0, any_pull = ctl->any_pull != 0;
   const u64 qm = lane_live ? ctl->qmask[j] : 0ull;
@@ -673,8 +664,7 @@ __global__ void __launch_bounds__(kMsMaxBlock, G >= 4 ? 6 : 4) k_ms_level(MsArgs
       u64 acc = pull_row_group<G>(a, w, want && !lng && beg < end, need, beg, end);
       if constexpr (G == 1)
         acc |= pull_rows_quarter(a, __ballot(lng && end - beg <= kMsMid), need, beg, end);
-      u64 lm = __ballot(lng && end - beg > (G == 1 ? kMsMid : 0) && (end - beg <= kMsHeavy || !hub_chunks<G>(qm)) &&
-                        j == 0);
+      u64 lm = __ballot(lng && end - beg > (G == 1 ? kMsMid : 0) && (end - beg <= kMsHeavy || !hubs) && j == 0);
       while (lm) {
         const int src = __ffsll((long long)lm) - 1;
         lm &= lm - 1ull;
@@ -756,6 +746,7 @@ __global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats
                                                           u64* ring, int64_t n) {
   __shared__ u64 s_act[kMaxWords], s_p[kMaxWords], s_q[kMaxWords];
   __shared__ u64 s_v, s_e, s_pushed;
+  __shared__ int s_small;  // a bottom-up source's frontier is small
   const int t = threadIdx.x;
   const int W = ctl->W, nslots = ctl->nslots;
   const long long d = ctl->d;
@@ -787,6 +778,7 @@ __global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats
       s_v = v;
       s_e = e;
       s_pushed = 0ull;
+      s_small = 0;
     }
   }
   __syncthreads();
@@ -808,6 +800,7 @@ __global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats
       else if (!p && (double)ef > to_pull * unexplored) p = 1;
       else if (p && (double)ef < to_push * (double)arcs) p = 0;
       ctl->pull[k] = p;
+      if (p && (double)ef <= to_pull * unexplored) s_small = 1;
       atomicOr(p ? &s_q[k >> 6] : &s_p[k >> 6], 1ull << (k & 63));
       if (!p) atomicAdd(&s_pushed, ef);
     }
@@ -821,6 +814,7 @@ __global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats
       s_q[t] |= s_p[t];
       s_p[t] = 0ull;
     }
+    if (t == 0) s_small = 1;
     __syncthreads();
   }
   u64* rec = ring + (size_t)(d % kRing) * kRecWords;
@@ -837,6 +831,7 @@ __global__ void __launch_bounds__(kMsFinal) k_ms_finalize(MsCtl* ctl, u64* stats
     }
     ctl->any_push = p != 0ull;
     ctl->any_pull = q != 0ull;
+    ctl->hubs = ms_hub_chunks(W, __popcll(q), s_small != 0);
     ctl->direct = W == 1 && s_v * kMsDirect > (u64)n;
     ctl->d = d + 1;
     __hip_atomic_store(rec + 1, s_v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -47,6 +47,12 @@ int main() {
   // keeps it from doing so.
   for (float f : {0.0f, 0.0001f, 0.003f, 0.01f, 0.03f, 0.0699f}) CHECK(ms_together(f) >= 0.5 * (double)kMsPushToPull);
   for (float f : {kMsPushToPull, 0.1f, 0.2f, 1.0f, 1e9f}) CHECK(ms_together(f) == 0.5 * (double)f);
+  // Hub rows of a batch: by one wave only for one or two sources that pull by
+  // their own frontiers.
+  for (int pulling = 0; pulling <= 64; ++pulling) {
+    CHECK(ms_hub_chunks(1, pulling, true) && ms_hub_chunks(2, pulling, false));
+    CHECK(ms_hub_chunks(1, pulling, false) == (pulling > 2));
+  }
   std::puts("ok");
   return 0;
 }
