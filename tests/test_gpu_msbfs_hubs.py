@@ -51,3 +51,26 @@ def test_hub_rows_of_a_session():
             assert np.array_equal(ss.fetch(k), oracle.levels(g.offs, g.cols, v)), v
     ss.close()
     G.close()
+
+
+@pytest.mark.parametrize("degree", [33, 40, 62, 66, 128, 129, 200])
+def test_long_rows_in_one_word(degree):
+    """Few to many rows beside each other that one lane, a quarter wave or a wave
+    looks up, found early, late and not at all: a path of 90 vertices with leaves."""
+    for beside in (1, 3, 15, 17, 31, 33, 64, 90):
+        k = 90
+        per = [degree - 2 if i % 64 < beside else 3 for i in range(k)]
+        spine = np.arange(k)
+        leaf = np.repeat(spine, per)
+        g = gg.from_edges(k + leaf.size, np.concatenate([spine[:-1], leaf]),
+                          np.concatenate([spine[1:], np.arange(k, k + leaf.size)]), name="caterpillar")
+        G = gsw.Graph.from_csr(g.offs, g.cols)
+        rng = np.random.default_rng(beside)
+        for B in (1, 2, 40):
+            srcs = rng.integers(0, g.n, B).astype(np.int32)
+            ref, ok = oracle.msbfs_levels(g.offs, g.cols, srcs)
+            assert ok
+            for p in (None, 0.0001):
+                lv, _ = gsw.msbfs(G, srcs, push_to_pull=p)
+                assert np.array_equal(lv, ref), (beside, B, p)
+        G.close()
