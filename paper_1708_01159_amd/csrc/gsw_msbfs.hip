@@ -505,16 +505,19 @@ __device__ __forceinline__ void push_rows_quarter(const MsArgs& a, u64 rows, u64
 // read one line for all of them.  Both words of two spread over the lanes one
 // after the other: 128 sources on a directed graph of 262144 vertices 1.23 ms,
 // each by its own lane 0.99; 100 sources top-down on a random graph of 700001
-// 3.09 and 2.06.)
+// 3.09 and 2.06.  But up to kMsFewVertices there are at most two waves with
+// work to a compute unit, and the steps count: 100 sources on 16384 vertices
+// 0.43 and 0.49, on 32768 0.47 and 0.51, on 65536 0.54 and 0.52.)
+constexpr int64_t kMsFewVertices = 32768;
 template <int G>
-__device__ constexpr int light_words() {
-  return G / 2 < 3 ? G / 2 : 3;
+__device__ __forceinline__ int light_words(int64_t n) {
+  return n <= kMsFewVertices || G >= 6 ? 3 : G / 2;
 }
 constexpr int kMsFew = 16;   // frontier vertices of a bitmap word
 template <int G>
 __device__ __forceinline__ void push_row_wave(const MsArgs& a, const Wave<G>& w, u64 f, int64_t beg, int64_t end) {
   u64 nz = __ballot(f != 0ull) & Wave<G>::kGroup;
-  if (G > 1 && __popcll(nz) <= light_words<G>()) {
+  if (G > 1 && __popcll(nz) <= light_words<G>(a.n)) {
     for (; nz; nz &= nz - 1ull) {
       const int jj = __ffsll((long long)nz) - 1;
       push_arcs(a, __shfl(f, jj), jj, beg + w.lane, end, 64);
@@ -561,7 +564,7 @@ __global__ void __launch_bounds__(kMsMaxBlock) k_ms_push(MsArgs a) {
       const int64_t deg = end - beg;
       const bool own = words && deg <= kMsLong;
       // few frontier vertices in the word would leave most lanes idle
-      const bool light = G > 1 ? __popc(words) <= light_words<G>() : cnt <= kMsFew;
+      const bool light = G > 1 ? __popc(words) <= light_words<G>(a.n) : cnt <= kMsFew;
       if (own && !light && f) push_arcs(a, f, j, beg, end, 1);
       if constexpr (G == 1)
         push_rows_quarter(a, __ballot(f != 0ull && deg <= kMsPushMid && (light || deg > kMsLong)), f, beg, end);

@@ -14,11 +14,11 @@ pytestmark = pytest.mark.gpu
 LENGTHS = [0, 1, 4, 5, 16, 31, 32, 33, 64, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 1300]
 
 
-def _graph(directed):
+def _graph(directed, n):
     """Roots 0..., each with a row of one of the lengths; words of 64 ids hold
     one row that is not short, two, three, four, five or many."""
     rng = np.random.default_rng(17)
-    n, src, dst, at = 9001, [], [], 0
+    src, dst, at = [], [], 0
     for many in (1, 2, 3, 4, 5, 20):
         for k in range(len(LENGTHS)):
             for i in range(many):
@@ -32,9 +32,9 @@ def _graph(directed):
     return gg.from_edges(n, s[keep], d[keep], symmetrize=not directed, name="rows"), np.arange(0, at, 64) % n
 
 
-@pytest.mark.parametrize("directed", [True, False])
-def test_push_rows_of_every_length(directed):
-    g, roots = _graph(directed)
+@pytest.mark.parametrize("directed,n", [(True, 9001), (False, 9001), (True, 32768), (True, 32769)])
+def test_push_rows_of_every_length(directed, n):
+    g, roots = _graph(directed, n)
     G = gsw.Graph.from_csr(g.offs, g.cols)
     rng = np.random.default_rng(18)
     # one source, a few, all of a word, part of two, three and four words, all of 16
