@@ -134,7 +134,10 @@ __device__ __forceinline__ u64 valid_bits(int j, int W, int B) {
 
 
 // Level d+1 for the sources in `m` (word j) at vertex v.  Only v's group
-// writes v's words, so the planes need no atomics.  Past the cap nothing is
+// writes v's words in a launch, but an atomic whose result nobody waits for
+// costs a step less than reading the word first, for each digit: 300 sources on
+// a small world of 100000 vertices, 25 levels, 3.75 -> 3.21 ms, on a binary tree
+// of 200000 1.70 -> 1.57, 128 on it 0.94 -> 0.90.  Past the cap nothing is
 // written: such sources are rerun or the call fails.
 __device__ __forceinline__ void write_levels(const MsArgs& a, long long d, int64_t v, int j, u64 m) {
   if (a.dist) {
@@ -149,7 +152,7 @@ __device__ __forceinline__ void write_levels(const MsArgs& a, long long d, int64
   if (d + 1 > GSW_MSBFS_LEVEL_CAP) return;
   for (int dig = (int)(d + 1); dig != 0; dig &= dig - 1) {
     const int p = __ffs(dig) - 1;
-    a.plane[((int64_t)p * a.n + v) * a.W + j] |= m;
+    atomicOr(a.plane + ((int64_t)p * a.n + v) * a.W + j, m);
   }
 }
 
