@@ -304,7 +304,7 @@ def level_times(G, s, reps):
     from paper_1708_01159_amd import gsw, train
 
     times, fr, ks = gsw.bfs_profile(G, int(s), reps=reps, advance_kernel=-1)
-    _, _, tr = gsw.bfs(G, [int(s)], policy="fixed", kernel=gsw.PUSH_VERTEX, parents=False, time_levels=True,
+    _, _, tr = gsw.bfs(G, [int(s)], policy="fixed", kernel=gsw.PUSH_EDGE, parents=False, time_levels=True,
                        trace_cap=len(fr) + 64)
     solo = np.full(len(fr), np.nan)
     for t in tr:

@@ -155,10 +155,11 @@ SOLO_LAUNCH_SHARE_MS = 0.0005
 def solo_times(graphs, rows, log=print):
     """Per row: the device time (ms) of the row's level when the search runs
     it in a single-workgroup launch, NaN when it does not.  One search per
-    (graph, source) with push_vertex at every level and device-stamped level
+    (graph, source) with push_edge at every level and device-stamped level
     times; BFS level sets do not depend on the kernel, so its level d is the
     row's level d, and every queue-driven top-down kernel runs such a level
-    the same way."""
+    the same way.  (Under the others a workgroup also takes levels of a hub's
+    row, which push_edge spreads over the grid in a fraction of that time.)"""
     import torch  # noqa: F401  (one HIP runtime: torch's)
 
     out = np.full(len(rows["level"]), np.nan)
@@ -174,7 +175,7 @@ def solo_times(graphs, rows, log=print):
         G = gsw.Graph.from_csr(g.offs, g.cols, flags=flags)
         n_solo = 0
         for s, items in want[name].items():
-            _, _, tr = gsw.bfs(G, [s], policy="fixed", kernel=gsw.PUSH_VERTEX, parents=False, time_levels=True,
+            _, _, tr = gsw.bfs(G, [s], policy="fixed", kernel=gsw.PUSH_EDGE, parents=False, time_levels=True,
                                trace_cap=max(d for d, _ in items) + 64)
             by_level = {t.level: t for t in tr}
             for d, i in items:
