@@ -256,7 +256,6 @@ BfsBase make_base(const gsw_graph* g, const Workspace& w, int32_t* lv, int32_t* 
   b.deg_max = dm >= 2147483647.0 ? 2147483647 : (int32_t)dm;
   b.head_ranked = w.head_ranked ? 1 : 0;
   b.head_rows = g->symmetric && !w.head_ranked ? 1 : 0;
-  b.pull_sum = b.head_rows && b.deg_max <= kHeadArcs ? -1 : pull_sum_until(g->n, g->nnz);
   b.solo_nf = solo_frontier(g->n, g->nnz, b.deg_max);
   b.solo = 0;
   b.solo_bits = 0;

@@ -272,15 +272,7 @@ struct BfsBase {
   int32_t deg_max;                 // largest out-degree (clamped to 2^31 - 1)
   int32_t head_ranked;             // head holds ranked in-arcs (bottom-up rows are then probed from their start)
   int32_t head_rows;               // head holds the rows' first out-arcs (symmetric graph, not ranked)
-  long long pull_sum;              // bottom-up: discovered vertices up to which a small frontier is summed up
 };
-
-// The vertices discovered up to which the unvisited ones have kPullSparseArcs
-// in-arcs, by the average (-1: never).
-constexpr int64_t kPullSparseArcs = 1 << 20;
-inline long long pull_sum_until(long long n, long long nnz) {
-  return nnz < kPullSparseArcs ? -1 : (long long)((double)n - (double)kPullSparseArcs * (double)n / (double)nnz);
-}
 
 // Single-workgroup multi-level launches (k_level_solo): while the frontier
 // is small, one workgroup of kSoloBlock threads runs consecutive top-down

@@ -62,6 +62,7 @@ constexpr int32_t kPullOwn = 64;                 // ... up to here, and on while
 constexpr int32_t kPullMid = 256;                // pull: longer rows are finished by the whole wave
 constexpr int kPullSum = 65536;                  // pull: bits of the LDS summary of a small frontier
 constexpr int64_t kPullSparse = 8192;            // ... of at most this many vertices
+constexpr int64_t kPullSparseArcs = 1 << 20;     // ... over at least this many arcs to look through
 constexpr int kPullChunk = 8;                    // pull: visited words (512 vertices) per wave step
 constexpr int kTreeLaneNodes = 4;                // level end: tree nodes per lane of one wave (256)
 
@@ -1241,12 +1242,13 @@ __device__ __forceinline__ PullV pull_vertex(int k, int total, int64_t w0, const
 // the frontier 98 -> 74 us, 1930 146 -> 93; R-MAT scale 22, 4145: 59 and 59
 // (few arcs are looked through there).  Making it costs every workgroup some
 // 2 us, so not where there is little to look through: few unvisited vertices'
-// in-arcs (counted by the average: pull_sum_until), or none past the heads, whose probes lie
+// in-arcs (counted by the average), or none past the heads, whose probes lie
 // beside each other on a mesh (1100 x 1100, all levels bottom-up: 29.3 ms a
 // search with it, 24.8 without; 500 x 500 9.1 and 7.9; 100000 vertices of
 // four arcs 0.81 and 0.77; 1000003 of four, random, 0.34 and 0.36).
 __device__ __forceinline__ bool pull_sparse(long long nf, long long disc, const BfsBase& b) {
-  return nf <= kPullSparse && nf * 4 <= b.nw && disc <= b.pull_sum;
+  return nf <= kPullSparse && nf * 4 <= b.nw && !(b.head_rows && b.deg_max <= kHeadArcs) &&
+         (double)(b.n - disc) * (double)b.nnz >= (double)kPullSparseArcs * (double)b.n;
 }
 __device__ __forceinline__ int pull_shift(int64_t n) {
   int s = 6;
