@@ -54,7 +54,6 @@ constexpr int kScanTile = kBlock * kScanItems;   // entries per scan block
 constexpr int kEdgeChunk = 1024;                 // push_edge: arcs per chunk (4 per lane)
 constexpr int kEdgeWin = 512;                    // push_edge: queue entries a chunk stages in LDS
 constexpr int kPullEager = 4;                    // pull: arcs of a row in flight per lane
-constexpr int kPullStep = 8;                     // ... and columns of a lane that walks its own
 constexpr int kPullGroup = 4;                    // pull: lanes per row past its head arcs
 constexpr int kPullRows = 64 / kPullGroup;       // ... and rows of a wave at a time
 constexpr int kPullMany = 24;                    // pull: with more rows than this to go on, lanes walk their own ...
@@ -1262,7 +1261,6 @@ __device__ __forceinline__ int pull_shift(int64_t n) {
 struct PullFr {
   const uint32_t* sum;
   int shift;
-  bool thin;  // at most one vertex in 16 is in the frontier
   template <bool kSparse>
   __device__ __forceinline__ u64 word(const Args& a, int32_t u) const {
     if constexpr (kSparse) {
@@ -1328,41 +1326,26 @@ __device__ __forceinline__ void pull_rows_rest(const Args& a, const PullFr& f, b
                                                int32_t& parB) {
   const int lane = lane_id();
   int32_t off0 = a.head_ranked ? 0 : kHeadArcs;
-  // own lanes take kPullStep arcs of every row a step, whose columns share a
-  // line that would be gone by the next step, and probe them all at once where
-  // the frontier is thin, else kPullEager first and the others where those
-  // missed (us a search, eight of one row at once / four of two / so: 2394076
-  // random vertices of 32 arcs 594, 652 and 624; 1000003 of them 203, 223 and
-  // 214; 4000003 of 16 arcs 432, 390 and 397).  The wave takes 32 times as many
-  // arcs of one row: past the short rows, fewer than 65 hubs beside each other
-  // are faster that way (40 rows of some 7600 arcs in one word, no neighbour in
-  // the frontier: a search of 400000 vertices 4.0 ms to the end by their lanes,
+  // own lanes take kPullEager arcs of every row a step, the wave 64 times as
+  // many of one: past the short rows, fewer than 65 hubs beside each other are
+  // faster that way (40 rows of some 7600 arcs in one word, no neighbour in the
+  // frontier: a search of 400000 vertices 4.0 ms to the end by their lanes,
   // 1.6 so, 2.6 with lanes up to 64 arcs and the wave 64 a step)
   while (__popcll(__ballot(wantA)) + __popcll(__ballot(wantB)) > (off0 < kPullOwn ? kPullMany : 64)) {
     auto walk = [&](bool want, int64_t beg, int32_t deg, int32_t& par) {
-      int32_t u[kPullStep];
+      int32_t u[kPullEager];
+      u64 fw[kPullEager];
 #pragma unroll
-      for (int q = 0; q < kPullStep; ++q) u[q] = want && off0 + q < deg ? a.rcols[beg + off0 + q] : -1;
-      u64 fw[kPullStep];
+      for (int q = 0; q < kPullEager; ++q) u[q] = want && off0 + q < deg ? a.rcols[beg + off0 + q] : -1;
 #pragma unroll
       for (int q = 0; q < kPullEager; ++q) fw[q] = f.word<kSparse>(a, u[q]);
-      if (!f.thin) {
 #pragma unroll
-        for (int q = 0; q < kPullEager; ++q)
-          if ((fw[q] >> (u[q] & 63)) & 1ull) {
-#pragma unroll
-            for (int k = kPullEager; k < kPullStep; ++k) u[k] = -1;
-          }
-      }
-#pragma unroll
-      for (int q = kPullEager; q < kPullStep; ++q) fw[q] = f.word<kSparse>(a, u[q]);
-#pragma unroll
-      for (int q = kPullStep - 1; q >= 0; --q)
+      for (int q = kPullEager - 1; q >= 0; --q)
         if ((fw[q] >> (u[q] & 63)) & 1ull) par = u[q];
     };
     walk(wantA, begA, degA, parA);
     walk(wantB, begB, degB, parB);
-    off0 += kPullStep;
+    off0 += kPullEager;
     wantA = wantA && parA < 0 && off0 < degA;
     wantB = wantB && parB < 0 && off0 < degB;
   }
@@ -1669,7 +1652,7 @@ __global__ void __launch_bounds__(kBlock, 6) k_level_auto(BfsBase b, BfsPolicy p
     }
     case GSW_K_PULL_BITMAP: {
       if (!pull_sparse(nf, c->disc, b)) {
-        body_pull<false>(a, st, lds.pull.found, PullFr{nullptr, 0, nf * 16 < b.n});
+        body_pull<false>(a, st, lds.pull.found, PullFr{nullptr, 0});
       } else {
         // the frontier's vertices are in the queue too
         queue_in_load(cpre, d & 3, qi);
@@ -1682,7 +1665,7 @@ __global__ void __launch_bounds__(kBlock, 6) k_level_auto(BfsBase b, BfsPolicy p
           atomicOr(&lds.pull.sum[x >> 5], 1u << (x & 31));
         }
         __syncthreads();
-        body_pull<true>(a, st, lds.pull.found, PullFr{lds.pull.sum, shift, true});
+        body_pull<true>(a, st, lds.pull.found, PullFr{lds.pull.sum, shift});
       }
       break;
     }
